@@ -203,7 +203,9 @@ int phimvs_patchmatch_batch(phimvs_ctx* ctx, int n_jobs, const phimvs_job* jobs,
  * with converging cameras; the split-lane path of phimvs_params.lanes > 1 has no work list
  * and ignores it).  ms is the time measured by
  * phimvs_autotune.  A new context starts with tile_rows 4, persistent, 4 workgroups per
- * compute unit, pixel order. */
+ * compute unit, order_by_depth 0; until phimvs_set_tuning or phimvs_autotune is called, a
+ * job whose sources' epipolar lines cross many of their rows takes depth order all the same
+ * (the results do not depend on it), and order_by_depth = 0 given there means pixel order. */
 typedef struct {
   int32_t tile_rows;
   int32_t persistent;

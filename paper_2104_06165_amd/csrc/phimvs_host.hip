@@ -80,7 +80,8 @@ struct phimvs_ctx {
   bool prepared = false;
   Batch single;                   // the step-wise interface's job
   Batch multi;                    // phimvs_patchmatch_batch
-  phimvs_tuning tuning{4, 1, 4, 0, 0.0};  // persistent, 4 workgroups per CU (the occupancy limit), pixel order
+  phimvs_tuning tuning{4, 1, 4, 0, 0.0};  // persistent, 4 workgroups per CU (the occupancy limit)
+  bool order_auto = true;                 // work-list order by each job's cameras until the caller sets a tuning
   size_t eval_lds_max = 0;                // largest dynamic LDS of an evaluate launch on this device
   DevBuf<float> io_a, io_b, io_c, io_d;  // staging for host inputs / outputs
   DevBuf<FilterNbr> filter_nbrs;          // neighbour table of the consistency filter
@@ -276,6 +277,48 @@ int validate_problem(phimvs_ctx* c, const Problem& P) {
   return PHIMVS_OK;
 }
 
+// Whether a job's work lists go by depth when the caller has set no tuning: the mean number
+// of rows of a source image that a reference pixel's epipolar segment crosses over the
+// depth range (at five points of the reference) is at least kDepthOrderRows.  A source
+// row's texels share cache lines (32 a line), so candidates of scattered depths cost a
+// wave's gather about a line per row they land in: with rows to cross, lanes of like depth
+// gather from fewer lines; without, pixel order does.  Whole maps of 3 iterations, pixel /
+// depth order: horizontal arcs (0-7 rows) 0.88-0.97x, camera grids of little height (86,
+// 95 rows) 0.97x, 1.04x, (158, 178, 297, 335) 1.06x-1.16x, vertical arcs (55, 125, 329,
+// 1003) 1.01x, 1.22x, 1.23x, 1.24x, camera grids (152-662 rows) 1.02x-1.25x.
+constexpr double kDepthOrderRows = 100.0;
+bool rows_scatter(const phimvs_ctx* c, const Problem& P, const double* K0i, const double* R0t) {
+  const ViewData& V0 = c->views[P.ref];
+  double rows = 0.0;
+  int n = 0;
+  for (int s : P.srcs) {
+    const ViewData& V = c->views[s];
+    double Rrel[9], Rt0[3];
+    mul33(V.R, R0t, Rrel);
+    mulv3(Rrel, V0.t, Rt0);
+    for (int k = 0; k < 5; ++k) {
+      const double fx = k == 0 ? 0.5 : (k & 1 ? 0.25 : 0.75), fy = k == 0 ? 0.5 : (k < 3 ? 0.25 : 0.75);
+      const double pix[3] = {fx * (V0.W - 1), fy * (V0.H - 1), 1.0};
+      double ray[3], far_ray[3], v[2];
+      mulv3(K0i, pix, ray);
+      mulv3(Rrel, ray, far_ray);
+      bool front = true;
+      for (int e = 0; e < 2; ++e) {
+        const double d = e ? V0.d_hi : V0.d_lo;
+        double X[3], q[3];
+        for (int i = 0; i < 3; ++i) X[i] = d * far_ray[i] + V.t[i] - Rt0[i];
+        mulv3(V.K, X, q);
+        front = front && q[2] > 0.0;
+        v[e] = front ? std::min(std::max(q[1] / q[2], 0.0), (double)(V.H - 1)) : 0.0;
+      }
+      if (!front) continue;
+      rows += std::fabs(v[1] - v[0]);
+      ++n;
+    }
+  }
+  return n > 0 && rows / n >= kDepthOrderRows;
+}
+
 // fill the problem block of one job and allocate its state
 int setup_job(phimvs_ctx* c, const Problem& P, Job& J, JobState& S) {
   const ViewData& V0 = c->views[P.ref];
@@ -321,6 +364,7 @@ int setup_job(phimvs_ctx* c, const Problem& P, Job& J, JobState& S) {
   double R0t[9];
   for (int i = 0; i < 3; ++i)
     for (int j = 0; j < 3; ++j) R0t[i * 3 + j] = V0.R[j * 3 + i];
+  A.by_depth = rows_scatter(c, P, K0i, R0t) ? 1 : 0;
   for (int k = 0; k < A.n_src; ++k) {
     const ViewData& Vj = c->views[P.srcs[k]];
     double Rrel[9], Rt0[3], trel[3], KR[9], M[9], e[3];
@@ -456,9 +500,13 @@ int run_eval(phimvs_ctx* c, Batch& b, Launch L, unsigned int* queue) {
   const bool persistent = c->tuning.persistent != 0;
   L.persistent = persistent ? 1 : 0;
   // the depth-ordered instance for the launch kinds the tuning names (mask: 1 initialisation,
-  // 2 propagation, 4 refinement)
+  // 2 propagation, 4 refinement), or where no tuning was set and a job's cameras call for it
+  // (mode 2 has no work list)
   const int kind_bit = L.mode == 0 ? 1 : (L.ncand > 3 ? 2 : 4);
   L.order_by_depth = (c->tuning.order_by_depth & kind_bit) ? 1 : 0;
+  if (c->order_auto && L.mode != 2)
+    for (const Job& J : b.jobs)
+      if (J.A.by_depth) L.order_by_depth = 2;
   L.queue = queue;
   if (c->diag & PHIMVS_DIAG_COUNT) L.count = c->diag_count;
   const bool split = b.jobs.size() == 1 && b.jobs[0].A.lanes > 1;
@@ -690,7 +738,7 @@ int run_single(phimvs_ctx* c, int ref, const int* srcs, int n_srcs, int window, 
     std::snprintf(ptrs, sizeof ptrs, "#%p#%p", (void*)b.d_jobs, (void*)b.queues.p);
     const std::string gkey = b.layout_key + "#" + std::to_string(iters) + "#" +
                              std::to_string(c->tuning.persistent) + "#" + std::to_string(c->tuning.wgs_per_cu) +
-                             "#" + std::to_string(c->tuning.order_by_depth) + ptrs;
+                             "#" + std::to_string(c->tuning.order_by_depth) + (c->order_auto ? "a" : "") + ptrs;
     rc = run_sequence_graph(c, b, gkey, iters);
   }
   if (rc) return rc;
@@ -1374,6 +1422,7 @@ int phimvs_set_tuning(phimvs_ctx* c, const phimvs_tuning* t) {
   const bool shape = t->tile_rows != c->tuning.tile_rows;
   c->tuning = *t;
   c->tuning.ms = 0.0;
+  c->order_auto = false;
   if (shape) {
     // the tile shape changes the layout of every job: rebuild on next use
     c->prepared = false;
@@ -1400,6 +1449,7 @@ int phimvs_autotune(phimvs_ctx* c, int n_jobs, const phimvs_job* jobs, int iters
                            {2, 1, 4, 0, 0}, {1, 1, 4, 0, 0}, {4, 1, 4, 1, 0}};
   const int n = (int)(sizeof(cands) / sizeof(cands[0]));
   const phimvs_tuning prev = c->tuning;
+  const bool prev_auto = c->order_auto;
   phimvs_tuning best{};
   double best_ms = HUGE_VAL;
   std::string failures;
@@ -1447,6 +1497,7 @@ int phimvs_autotune(phimvs_ctx* c, int n_jobs, const phimvs_job* jobs, int iters
   if (n_results) *n_results = std::min(*n_results, n);
   if (!(best_ms < HUGE_VAL)) {
     (void)phimvs_set_tuning(c, &prev);
+    c->order_auto = prev_auto;
     return fail(c, PHIMVS_E_DEVICE, "autotune: no configuration ran:" + failures);
   }
   int rc = phimvs_set_tuning(c, &best);

@@ -43,6 +43,8 @@ struct Args {
   int score_all;           // propagation candidates left out when they cannot win: 0 all such (equal
                            // to an earlier one, to the current plane, or to one the previous launch of
                            // the colour offered); 1 not the last kind; 2 none
+  int by_depth;            // the sources' epipolar lines cross many of their rows: work lists by depth
+                           // (launches that leave the order to the job)
   float off[kMaxTaps1D];   // tap offsets k = 0 .. 2R: s (k - R), in FP32
   float Kinv[9];
   double Kinv_d[9];
@@ -87,8 +89,8 @@ struct Launch {
   int total_tiles, total_cblk;
   int xcd_len[8];                      // evaluate tiles of each XCD's list
   int persistent;                      // evaluate: tiles pulled from per-XCD queues
-  int order_by_depth;                  // evaluate: work items of launches with <= 3 candidates per
-                                       // pixel handed out by the candidate's inverse depth
+  int order_by_depth;                  // evaluate: work items handed out by the candidate's inverse
+                                       // depth: 0 no job's, 1 every job's, 2 those of by_depth jobs
   int frac;                            // evaluate: some job uses the window-resize scheme
   int skip_current;                    // propagation candidates: drop those equal to the pixel's current
                                        // plane (only when every stored cost is its plane's own cost)

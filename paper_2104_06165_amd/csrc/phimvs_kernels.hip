@@ -983,7 +983,7 @@ __device__ __forceinline__ void eval_tile(const Job& J, const Launch& L, int til
     n_items += wave_total[w];
     if (w < wave) off += wave_total[w];
   }
-  if constexpr (!DEPTH) {
+  if (!DEPTH || (L.order_by_depth == 2 && !A.by_depth)) {
     for (unsigned m = live; m; m &= m - 1) item_lds[off++] = (uint16_t)((threadIdx.x << 3) | (__ffs(m) - 1));
   } else {
     // counting sort into kDepthBuckets (= kBlock) buckets of 1/d over [1/d_hi, 1/d_lo]:
