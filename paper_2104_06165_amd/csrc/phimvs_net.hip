@@ -6,19 +6,19 @@
 // random plane's (the gate lives in the initialisation kernel).
 //
 // Numerics: weights and activations are bfloat16, every convolution accumulates in FP32
-// on the matrix cores (v_mfma_f32_16x16x16bf16_1k).  Activations are NHWC with the
-// channel count padded to a multiple of 16.  A convolution is an implicit GEMM over
-// K = 9 taps x input channels: one wave computes 16 pixels of one image row x 16
-// output channels per matrix instruction; a workgroup of 16 waves stages the layer's
-// weights in LDS once, so only the input patches go through the texture path.  Training runs on the same kernels: the data
+// on the matrix cores.  Activations are NHWC with the channel count padded to 16 or 32.  A
+// convolution is an implicit GEMM over K = 9 taps x input channels; one wave walks down a
+// strip of 16 columns with the layer's weights in registers, so that an input row is read
+// once for the three output rows it enters.  Training runs on the same kernel: the data
 // gradient is the forward convolution with flipped, transposed weights; the weight
-// gradient accumulates (input patch)^T x (output gradient) over 16-pixel slices per
-// image row, written as per-row partial sums and reduced in a fixed order (16
-// interleaved groups of rows, then the groups in turn).
+// gradient accumulates (input patch)^T x (output gradient) over strips of 32 columns,
+// summed over the waves of a workgroup and then over the workgroups in a fixed order.
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_bfloat16.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "phimvs_net_internal.h"
 
@@ -39,218 +39,317 @@ __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint
 
 // ---------------------------------------------------------------------------- convolution
 // y[b, r, c, co] = bias[co] + sum_{t, ci} x[b, r + dy_t, c + dx_t, ci] * w[t][co][ci]
-// (zero outside the image), optionally ReLU; x: bf16 NHWC with CI channels (multiple of 16);
-// w: bf16 [9][CO][CI]; CO multiple of 16.  Output: bf16 (y16, CO channels) and / or fp32
-// (y32, first co_keep channels).  If mask16 is given the result is multiplied by
-// (mask16 > 0) (ReLU backward of the producing layer) before storing.
-constexpr int kConvBlock = 1024;  // 16 waves, each 16 pixels of a row
-constexpr int kMaxCI = 32;        // widest layer input (channels, padded)
-constexpr int kConvPad = 4;       // bf16 padding of each LDS weight row (spreads the banks)
-__global__ __launch_bounds__(kConvBlock) void conv3x3_kernel(ConvArgs a) {
-  // the weights [9][CO][CI], staged once per workgroup; each (tap, output channel) row padded
-  __shared__ uint2 wl[9 * kMaxCO * (kMaxCI + kConvPad) / 4];
-  const int q = a.CI / 4, qp = (a.CI + kConvPad) / 4;
-  {
-    const uint2* __restrict__ wg = reinterpret_cast<const uint2*>(a.wt);
-    for (int i = threadIdx.x; i < 9 * a.CO * q; i += kConvBlock) {
-      const int row = i / q, k = i - row * q;
-      wl[row * qp + k] = wg[i];
-    }
-  }
-  __syncthreads();
-  const uint16_t* ws = reinterpret_cast<const uint16_t*>(wl);
+// (zero outside the image), optionally ReLU; x: bf16 NHWC with CI channels; w: bf16
+// [9][CO][CI].  Output: bf16 (y16, CO channels) and / or fp32 (y32, the first 4 channels).
+// If mask16 is given the result is multiplied by (mask16 > 0) (ReLU backward of the
+// producing layer) before storing.  FIRST: the input is the network's own, fp32 with 5
+// channels (x32), rounded to bf16 here and stored as the layer's 16-channel bf16 input.
+//
+// Memory bounds the layer (54 MB at 800 x 533 x 32 channels: 11 us at the 5.0 TB/s of a
+// large copy; the matrix work is 3 us), so the work is split to read each row once: a wave
+// takes 16 columns x `rb` rows, holds all 9 x CI x CO weights in registers (72 VGPRs for
+// 32 x 32) and keeps three output rows in flight; a row's three shifted fragments feed all
+// of them, the next row's are loaded before this row's matrix instructions.  The weights
+// are the A operand, so that a lane ends with 4 consecutive channels of one pixel (8-byte
+// stores).  The order of every accumulation is taps, then input channels: 16x16x32 equals
+// two chained 16x16x16 over the lower and the upper 16 channels, bit for bit.
+// 800 x 533, 32 -> 32 channels: 47 us with a wave per 16 pixels of one row (each pixel read for
+// all nine taps, weights from LDS), 21 us so (2.6 TB/s); 8 x 267 x 400: 91 -> 36 us.
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+template <int CI>
+struct Frag;  // one lane's share of 16 columns (or output channels) x CI input channels
+template <>
+struct Frag<16> {
+  uint2 v;
+};
+template <>
+struct Frag<32> {
+  uint4 v;
+};
+__device__ __forceinline__ v4f mfma(const Frag<16>& a, const Frag<16>& b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(v4s, a.v), __builtin_bit_cast(v4s, b.v), c, 0, 0,
+                                                   0);
+}
+__device__ __forceinline__ v4f mfma(const Frag<32>& a, const Frag<32>& b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a.v), __builtin_bit_cast(v8b, b.v), c, 0, 0, 0);
+}
+
+constexpr int kConvBlock = 256;  // 4 waves on neighbouring strips
+template <int CI, int CO, bool FIRST>
+__global__ __launch_bounds__(kConvBlock) __attribute__((amdgpu_waves_per_eu(3))) void conv3x3_kernel(ConvArgs a, int rb, int segs, int bands) {
+  constexpr int NCO = CO / 16, KL = CI / 4;  // output blocks; input channels of one lane
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int segs = (a.w + 15) / 16;
-  const int task = blockIdx.x * (kConvBlock / 64) + wave;  // (b, r, seg)
-  if (task >= a.B * a.h * segs) return;
+  const int task = blockIdx.x * (kConvBlock / 64) + wave;  // (b, band, seg)
+  if (task >= a.B * bands * segs) return;
   const int seg = task % segs;
-  const int br = task / segs;
-  const int r = br % a.h, b = br / a.h;
-  const int c0 = seg * 16;
-  const int lr = lane & 15, lk = lane >> 4;  // row / column of the fragment, K group
-  v4f acc[kMaxCO / 16];
+  const int bb = task / segs;
+  const int band = bb % bands, b = bb / bands;
+  const int r0 = band * rb, r1 = min(r0 + rb, a.h);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int c = seg * 16 + lr;  // this lane's column
+  Frag<CI> W[9][NCO];
 #pragma unroll
-  for (int i = 0; i < kMaxCO / 16; ++i) acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
-  const int nco = a.CO / 16;
-  for (int t = 0; t < 9; ++t) {
-    const int rr = r + t / 3 - 1;
-    const int cc = c0 + lr + t % 3 - 1;
-    const bool inside = rr >= 0 && rr < a.h && cc >= 0 && cc < a.w;
-    const size_t pix = ((size_t)b * a.h + (inside ? rr : 0)) * a.w + (inside ? cc : 0);
-    for (int cib = 0; cib < a.CI / 16; ++cib) {
-      const int ci = cib * 16 + lk * 4;
-      v4s A = v4s{0, 0, 0, 0};
-      if (inside) A = *reinterpret_cast<const v4s*>(a.x + pix * a.CI + ci);
+  for (int t = 0; t < 9; ++t)
 #pragma unroll
-      for (int i = 0; i < kMaxCO / 16; ++i) {
-        if (i < nco) {
-          const int co = i * 16 + lr;
-          const v4s Bf = *reinterpret_cast<const v4s*>(ws + (t * a.CO + co) * (qp * 4) + ci);
-          acc[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, Bf, acc[i], 0, 0, 0);
-        }
-      }
-    }
-  }
-  // acc[i][j]: pixel c0 + 4 lk + j, output channel 16 i + lr
+    for (int i = 0; i < NCO; ++i)
+      W[t][i].v = *reinterpret_cast<const decltype(W[t][i].v)*>(a.wt + (size_t)(t * CO + i * 16 + lr) * CI + lk * KL);
+  float bias[NCO][4];
 #pragma unroll
-  for (int i = 0; i < kMaxCO / 16; ++i) {
-    if (i >= nco) continue;
-    const int co = i * 16 + lr;
+  for (int i = 0; i < NCO; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int c = c0 + lk * 4 + j;
-      if (c >= a.w) continue;
-      float v = acc[i][j] + ((a.bias && co < a.n_bias) ? a.bias[co] : 0.f);
-      if (a.relu) v = fmaxf(v, 0.f);
-      const size_t p = ((size_t)b * a.h + r) * a.w + c;
-      if (a.mask16 && !(bf2f(a.mask16[p * a.CO + co]) > 0.f)) v = 0.f;
-      if (a.y16) a.y16[p * a.CO + co] = f2bf(v);
-      if (a.y32 && co < a.co_keep) a.y32[p * a.co_keep + co] = v;
+      const int co = i * 16 + lk * 4 + j;
+      bias[i][j] = (a.bias && co < a.n_bias) ? a.bias[co] : 0.f;
     }
-  }
-}
-
-// Weight gradient partials: for image row (b, r): P[b r][t][ci][co] = sum_c x[b, r+dy, c+dx, ci] *
-// g[b, r, c, co]; bias partial Pb[b r][co] = sum_c g[b, r, c, co].  One workgroup per image row;
-// wave k of 4 handles the taps t = k, k + 4, k + 8 for every (ci, co) block.  The row is
-// walked in chunks of 64 pixels staged in LDS by coalesced loads (the three input rows
-// and the output-gradient row); every accumulator takes its 16-pixel slices in row order.
-constexpr int kWgChunk = 64;   // pixels staged per step (4 slices of 16)
-constexpr int kWgStride = 36;  // bf16 per staged pixel: 32 channels + 4 of padding (spreads the banks)
-__global__ __launch_bounds__(256) void conv3x3_wgrad_kernel(WgradArgs a) {
-  // rows r - 1 .. r + 1 of the input (pixels c_base - 1 .. c_base + 64) and row r of the
-  // output gradient (pixels c_base .. c_base + 63), zero outside the image
-  __shared__ uint2 xs2[3 * (kWgChunk + 2) * kWgStride / 4];
-  __shared__ uint2 gs2[kWgChunk * kWgStride / 4];
-  const int br = blockIdx.x;
-  if (br >= a.B * a.h) return;
-  const int r = br % a.h, b = br / a.h;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int lr = lane & 15, lk = lane >> 4;
-  const int nci = a.CI / 16, nco = a.CO / 16;
-  const int qi = a.CI / 4, qo = a.CO / 4;
-  const uint16_t* xs = reinterpret_cast<const uint16_t*>(xs2);
-  const uint16_t* gs = reinterpret_cast<const uint16_t*>(gs2);
-  const uint2* __restrict__ xg = reinterpret_cast<const uint2*>(a.x);
-  const uint2* __restrict__ gg = reinterpret_cast<const uint2*>(a.g);
-  v4f acc[3][kMaxCO / 16][kMaxCO / 16];  // taps wave, wave + 4, wave + 8 x input block x output block
+  const bool in[3] = {c >= 1 && c - 1 < a.w, c < a.w, c + 1 < a.w};
+  // fragments of input row i (zero outside the image), columns c - 1, c, c + 1
+  auto load_row = [&](int i, Frag<CI> (&F)[3]) {
+    const bool rin = i >= 0 && i < a.h;
+    const size_t row = ((size_t)b * a.h + (rin ? i : 0)) * a.w;
 #pragma unroll
-  for (int ti = 0; ti < 3; ++ti)
+    for (int d = 0; d < 3; ++d) {
+      const bool ok = rin && in[d];
+      const size_t pix = row + (ok ? c + d - 1 : 0);
+      if constexpr (FIRST) {
+        // lanes of the first K group hold channels 0..3, the second's channel 4, the rest 0
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+        if (ok && lk == 0) {
 #pragma unroll
-    for (int u = 0; u < kMaxCO / 16; ++u)
-#pragma unroll
-      for (int v = 0; v < kMaxCO / 16; ++v) acc[ti][u][v] = v4f{0.f, 0.f, 0.f, 0.f};
-  float bias = 0.f;
-  for (int c_base = 0; c_base < a.w; c_base += kWgChunk) {
-    __syncthreads();  // the previous chunk's reads are done
-    for (int i = threadIdx.x; i < 3 * (kWgChunk + 2) * qi; i += 256) {
-      const int row = i / ((kWgChunk + 2) * qi);
-      const int rem = i - row * (kWgChunk + 2) * qi;
-      const int px = rem / qi, k = rem - px * qi;
-      const int rr = r + row - 1, cx = c_base + px - 1;
-      uint2 v = make_uint2(0u, 0u);
-      if (rr >= 0 && rr < a.h && cx >= 0 && cx < a.w) v = xg[(((size_t)b * a.h + rr) * a.w + cx) * qi + k];
-      xs2[(row * (kWgChunk + 2) + px) * (kWgStride / 4) + k] = v;
+          for (int j = 0; j < 4; ++j) x[j] = a.x32[pix * 5 + j];
+        }
+        if (ok && lk == 1) x[0] = a.x32[pix * 5 + 4];
+        F[d].v = make_uint2((uint32_t)f2bf(x[0]) | (uint32_t)f2bf(x[1]) << 16,
+                            (uint32_t)f2bf(x[2]) | (uint32_t)f2bf(x[3]) << 16);
+      } else {
+        F[d].v = decltype(F[d].v){};
+        if (ok) F[d].v = *reinterpret_cast<const decltype(F[d].v)*>(a.x + pix * CI + lk * KL);
+      }
     }
-    for (int i = threadIdx.x; i < kWgChunk * qo; i += 256) {
-      const int px = i / qo, k = i - px * qo;
-      const int c = c_base + px;
-      uint2 v = make_uint2(0u, 0u);
-      if (c < a.w) v = gg[(((size_t)b * a.h + r) * a.w + c) * qo + k];
-      gs2[px * (kWgStride / 4) + k] = v;
+  };
+  Frag<CI> F[3], N[3];
+  load_row(r0 - 1, F);
+  v4f a0[NCO], a1[NCO], a2[NCO];  // output rows i + 1, i, i - 1 of the row being read
+#pragma unroll
+  for (int i = 0; i < NCO; ++i) a1[i] = a2[i] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int i = r0 - 1; i <= r1; ++i) {
+    const bool store = i - 1 >= r0 && c < a.w;
+    const size_t p = ((size_t)b * a.h + (store ? i - 1 : 0)) * a.w + (store ? c : 0);
+    uint2 m[NCO];
+#pragma unroll
+    for (int k = 0; k < NCO; ++k) {
+      m[k] = make_uint2(0u, 0u);
+      if (a.mask16 && store) m[k] = *reinterpret_cast<const uint2*>(a.mask16 + p * CO + k * 16 + lk * 4);
     }
-    __syncthreads();
-    for (int sl = 0; sl < kWgChunk / 16; ++sl) {
-      const int lp = sl * 16;  // first pixel of the slice, relative to c_base
-      if (c_base + lp >= a.w) break;
+    if (i < r1) load_row(i + 1, N);
+    if constexpr (FIRST) {
+      if (i >= r0 && i < r1 && c < a.w)
+        *reinterpret_cast<uint2*>(a.x16 + (((size_t)b * a.h + i) * a.w + c) * 16 + lk * 4) = F[1].v;
+    }
 #pragma unroll
-      for (int ti = 0; ti < 3; ++ti) {
-        const int t = wave + 4 * ti;
-        if (t >= 9) break;
-        const int ty = t / 3, dx = t % 3 - 1;
+    for (int k = 0; k < NCO; ++k) {
+      a0[k] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int cib = 0; cib < kMaxCO / 16; ++cib) {
-          if (cib >= nci) break;
-          // A (16 ci x 16 px): lane -> ci = 16 cib + lr, pixels c + 4 lk .. + 3 (zero past the row end)
-          v4s A;
+      for (int d = 0; d < 3; ++d) {
+        a0[k] = mfma(W[d][k], F[d], a0[k]);
+        a1[k] = mfma(W[3 + d][k], F[d], a1[k]);
+        a2[k] = mfma(W[6 + d][k], F[d], a2[k]);
+      }
+    }
+    if (store) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int p = lp + lk * 4 + j;
-            A[j] = (c_base + p < a.w) ? (short)xs[(ty * (kWgChunk + 2) + p + dx + 1) * kWgStride + cib * 16 + lr] : 0;
-          }
+      for (int k = 0; k < NCO; ++k) {
+        // a2[k][j]: pixel (i - 1, c), output channel 16 k + 4 lk + j
+        float v[4];
 #pragma unroll
-          for (int cob = 0; cob < kMaxCO / 16; ++cob) {
-            if (cob >= nco) break;
-            // B (16 px x 16 co): lane -> co = 16 cob + lr, pixels c + 4 lk .. + 3
-            v4s Bf;
+        for (int j = 0; j < 4; ++j) {
+          v[j] = a2[k][j] + bias[k][j];
+          if (a.relu) v[j] = fmaxf(v[j], 0.f);
+          if (a.mask16 && !(bf2f((uint16_t)((j & 2 ? m[k].y : m[k].x) >> (j & 1 ? 16 : 0))) > 0.f)) v[j] = 0.f;
+        }
+        if (a.y16)
+          *reinterpret_cast<uint2*>(a.y16 + p * CO + k * 16 + lk * 4) =
+              make_uint2((uint32_t)f2bf(v[0]) | (uint32_t)f2bf(v[1]) << 16,
+                         (uint32_t)f2bf(v[2]) | (uint32_t)f2bf(v[3]) << 16);
+        if (a.y32 && k == 0 && lk == 0) {
+          if (a.y32_aligned) {
+            *reinterpret_cast<float4*>(a.y32 + p * 4) = make_float4(v[0], v[1], v[2], v[3]);
+          } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) Bf[j] = (short)gs[(lp + lk * 4 + j) * kWgStride + cob * 16 + lr];
-            acc[ti][cib][cob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, Bf, acc[ti][cib][cob], 0, 0, 0);
+            for (int j = 0; j < 4; ++j) a.y32[p * 4 + j] = v[j];
           }
         }
       }
     }
-    // bias partial: first wave, one lane per output channel, in pixel order
-    if (a.partial_bias && wave == 0 && lane < a.CO) {
-      const int n = min(kWgChunk, a.w - c_base);
-      for (int p = 0; p < n; ++p) bias = bias + bf2f(gs[p * kWgStride + lane]);
+#pragma unroll
+    for (int k = 0; k < NCO; ++k) {
+      a2[k] = a1[k];
+      a1[k] = a0[k];
     }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) F[d] = N[d];
   }
-  float* P = a.partial + (size_t)br * 9 * a.CI * a.CO;
-#pragma unroll
-  for (int ti = 0; ti < 3; ++ti) {
-    const int t = wave + 4 * ti;
-    if (t >= 9) break;
-#pragma unroll
-    for (int cib = 0; cib < kMaxCO / 16; ++cib) {
-      if (cib >= nci) break;
-#pragma unroll
-      for (int cob = 0; cob < kMaxCO / 16; ++cob) {
-        if (cob >= nco) break;
-        // acc[j]: ci = 16 cib + 4 lk + j, co = 16 cob + lr
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          P[((size_t)t * a.CI + cib * 16 + lk * 4 + j) * a.CO + cob * 16 + lr] = acc[ti][cib][cob][j];
-      }
-    }
-  }
-  if (a.partial_bias && wave == 0 && lane < a.CO) a.partial_bias[(size_t)br * a.CO + lane] = bias;
 }
 
-// out[i] = sum_{k < n_rows} partial[k * stride + i] in a fixed order: a workgroup of 16
-// waves takes 64 outputs, wave g sums rows g, g + 16, g + 32, ... in turn, and the 16
-// sums are added in wave order, so the result does not depend on scheduling
+// Weight gradient partials: dW[t][ci][co] = sum_{b, r, c} x[b, r + dy, c + dx, ci] * g[b, r, c, co]
+// and the bias gradient's sums of g.  One wave takes a strip of 32 columns x rb rows and all
+// 9 x CI x CO sums (144 accumulator registers for 32 x 32); walking down, each input row meets
+// the gradients of the three rows it enters.  The contraction runs over columns, which NHWC
+// scatters, so a lane loads its two channels (2 lr, 2 lr + 1) of each of its 8 columns (and one
+// either side) as dwords and pairs them up with byte permutes: row lr of the matrix
+// instruction stands for channel 2 lr (low halves) or 2 lr + 1 (high halves).  The waves of a
+// workgroup add their sums in LDS in wave order; workgroup k's go to partial + k * stride
+// ([9][CI][CO], then [CO] bias sums).
+// 8 x 267 x 400, 32 x 32 channels: 176 us with a workgroup per image row (2136 partial sums of
+// 36 KB to write and reduce, another 14 us), 81 us so (234 partial sums).
+constexpr int kWgBlock = 512;
+__device__ __forceinline__ uint32_t pair_lo(uint32_t p, uint32_t q) { return __builtin_amdgcn_perm(q, p, 0x05040100u); }
+__device__ __forceinline__ uint32_t pair_hi(uint32_t p, uint32_t q) { return __builtin_amdgcn_perm(q, p, 0x07060302u); }
+template <int CI, int CO>
+__global__ __launch_bounds__(kWgBlock) void conv3x3_wgrad_kernel(WgradArgs a, int rb, int segs, int bands) {
+  constexpr int NCI = CI / 16, NCO = CO / 16, kSums = 9 * CI * CO;
+  __shared__ float red[kSums + CO];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int task = blockIdx.x * (kWgBlock / 64) + wave;  // (b, band, seg)
+  const bool work = task < a.B * bands * segs;
+  const int seg = task % segs;
+  const int bb = task / segs;
+  const int band = bb % bands, b = work ? bb / bands : 0;
+  const int r0 = band * rb, r1 = work ? min(r0 + rb, a.h) : r0 - 2;
+  const int c0 = seg * 32 + 8 * lk;  // this lane's first column
+  v4f acc[9][NCI][NCO], accb[NCO];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int u = 0; u < NCI; ++u)
+#pragma unroll
+      for (int v = 0; v < NCO; ++v) acc[t][u][v] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int v = 0; v < NCO; ++v) accb[v] = v4f{0.f, 0.f, 0.f, 0.f};
+  // this lane's channels (two, or one) of column c of row i; zero outside the image
+  auto px = [&](const uint16_t* __restrict__ p, int C, int i, int c) -> uint32_t {
+    if (!(c >= 0 && c < a.w)) return 0u;
+    const size_t at = (((size_t)b * a.h + i) * a.w + c) * C;
+    return C == 32 ? *reinterpret_cast<const uint32_t*>(p + at + 2 * lr) : (uint32_t)p[at + lr];
+  };
+  auto load_x = [&](int i, uint32_t (&v)[10]) {
+    const bool rin = i >= 0 && i < a.h;
+#pragma unroll
+    for (int j = 0; j < 10; ++j) v[j] = rin ? px(a.x, CI, i, c0 + j - 1) : 0u;
+  };
+  auto load_g = [&](int i, uint32_t (&v)[8]) {
+    const bool rin = i >= r0 && i < r1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = rin ? px(a.g, CO, i, c0 + j) : 0u;
+  };
+  auto frag = [](const uint32_t* v, int half) {
+    Frag<32> f;
+    f.v = half ? make_uint4(pair_hi(v[0], v[1]), pair_hi(v[2], v[3]), pair_hi(v[4], v[5]), pair_hi(v[6], v[7]))
+               : make_uint4(pair_lo(v[0], v[1]), pair_lo(v[2], v[3]), pair_lo(v[4], v[5]), pair_lo(v[6], v[7]));
+    return f;
+  };
+  Frag<32> ones;
+  ones.v = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
+  Frag<32> g0[NCO], g1[NCO], g2[NCO];  // gradient rows i + 1, i, i - 1
+#pragma unroll
+  for (int v = 0; v < NCO; ++v) g1[v].v = g2[v].v = make_uint4(0u, 0u, 0u, 0u);
+  uint32_t xr[10], gr[8];
+  if (r0 <= r1) {
+    load_x(r0 - 1, xr);
+    load_g(r0, gr);
+  }
+  for (int i = r0 - 1; i <= r1; ++i) {
+    Frag<32> X[3][NCI];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int u = 0; u < NCI; ++u) X[d][u] = frag(xr + d, u);
+#pragma unroll
+    for (int v = 0; v < NCO; ++v) g0[v] = frag(gr, v);
+    if (i < r1) {
+      load_x(i + 1, xr);
+      load_g(i + 2, gr);
+    }
+#pragma unroll
+    for (int v = 0; v < NCO; ++v) {
+      accb[v] = mfma(ones, g0[v], accb[v]);
+#pragma unroll
+      for (int u = 0; u < NCI; ++u)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          acc[d][u][v] = mfma(X[d][u], g0[v], acc[d][u][v]);
+          acc[3 + d][u][v] = mfma(X[d][u], g1[v], acc[3 + d][u][v]);
+          acc[6 + d][u][v] = mfma(X[d][u], g2[v], acc[6 + d][u][v]);
+        }
+      g2[v] = g1[v];
+      g1[v] = g0[v];
+    }
+  }
+  // acc[t][u][v][j]: ci = NCI (4 lk + j) + u, co = NCO lr + v; accb[v][*]: co = NCO lr + v
+  for (int w = 0; w < kWgBlock / 64; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int u = 0; u < NCI; ++u)
+#pragma unroll
+          for (int v = 0; v < NCO; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const int e = (t * CI + NCI * (4 * lk + j) + u) * CO + NCO * lr + v;
+              red[e] = w ? red[e] + acc[t][u][v][j] : acc[t][u][v][j];
+            }
+      if (lk == 0) {
+#pragma unroll
+        for (int v = 0; v < NCO; ++v) {
+          const int e = kSums + NCO * lr + v;
+          red[e] = w ? red[e] + accb[v][0] : accb[v][0];
+        }
+      }
+    }
+    __syncthreads();
+  }
+  float* P = a.partial + (size_t)blockIdx.x * (kSums + CO);
+  for (int e = threadIdx.x; e < kSums + CO; e += kWgBlock) P[e] = red[e];
+}
+
+// The gradient of every layer from its workgroups' partial sums, in a fixed order: a
+// workgroup of 16 waves takes 64 parameters of one layer, wave g sums the partials g, g + 16,
+// g + 32, ... in turn, and the 16 sums are added in wave order, so the result does not depend
+// on scheduling.  Parameter i of a layer: weight [t][ci][co] of the unpadded shape, then bias.
 constexpr int kReduceGroups = 16;
-__global__ __launch_bounds__(kReduceGroups * 64) void reduce_rows_kernel(const float* __restrict__ partial,
-                                                                         int n_rows, int stride, int n,
-                                                                         float* __restrict__ out) {
+__global__ __launch_bounds__(kReduceGroups * 64) void reduce_grads_kernel(ReduceArgs a) {
   __shared__ float part[kReduceGroups][64];
   const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + lane;
+  int l = 0;
+  while (l + 1 < a.n_layers && (int)blockIdx.x >= a.layer[l + 1].block0) ++l;
+  const ReduceLayer& L = a.layer[l];
+  const int i = ((int)blockIdx.x - L.block0) * 64 + lane;
+  const int nw = 9 * L.cin * L.cout;
+  const bool use = i < nw + L.cout;
+  int e = 9 * L.CI * L.CO + (i - nw);
+  if (i < nw) {
+    const int t = i / (L.cin * L.cout);
+    const int rem = i - t * L.cin * L.cout;
+    const int ci = rem / L.cout;
+    e = (t * L.CI + ci) * L.CO + (rem - ci * L.cout);
+  }
+  const int stride = (9 * L.CI + 1) * L.CO;
   float s = 0.f;
-  if (i < n) {
+  if (use) {
 #pragma unroll 4
-    for (int k = g; k < n_rows; k += kReduceGroups) s += partial[(size_t)k * stride + i];
+    for (int k = g; k < L.n_partial; k += kReduceGroups) s += L.partial[(size_t)k * stride + e];
   }
   part[g][lane] = s;
   __syncthreads();
-  if (g == 0 && i < n) {
+  if (g == 0 && use) {
     float t = 0.f;
     for (int q = 0; q < kReduceGroups; ++q) t += part[q][lane];
-    out[i] = t;
+    L.grad[i] = t;
   }
 }
 
-// fp32 NHWC (C0 channels) -> bf16 NHWC (CP channels, zero padded)
-__global__ void to_bf16_kernel(const float* __restrict__ x, int n_pix, int C0, int CP, uint16_t* __restrict__ y) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (size_t)n_pix * CP) return;
-  const size_t p = i / CP;
-  const int c = (int)(i - p * CP);
-  y[i] = c < C0 ? f2bf(x[p * C0 + c]) : (uint16_t)0;
-}
-
-// master fp32 weights [9][CIN][COUT] -> bf16 forward [9][COP][CIP] and flipped [9][CIP][COP]
+// bf16 NHWC with CP channels -> fp32 NHWC with the first C
 __global__ void bf16_unpad_kernel(const uint16_t* __restrict__ x, int n_pix, int CP, int C, float* __restrict__ y) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (size_t)n_pix * C) return;
@@ -258,6 +357,7 @@ __global__ void bf16_unpad_kernel(const uint16_t* __restrict__ x, int n_pix, int
   y[i] = bf2f(x[p * CP + c]);
 }
 
+// master fp32 weights [9][CIN][COUT] -> bf16 forward [9][COP][CIP] and flipped [9][CIP][COP]
 __global__ void pack_weights_kernel(const float* __restrict__ w, int CIN, int COUT, int CIP, int COP,
                                     uint16_t* __restrict__ fwd, uint16_t* __restrict__ flip) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -269,21 +369,6 @@ __global__ void pack_weights_kernel(const float* __restrict__ w, int CIN, int CO
   fwd[((size_t)t * COP + co) * CIP + ci] = f2bf(v);
   // data gradient: g_in[ci] = sum_{t, co} g[p - off_t][co] w[t][ci][co] = conv with w'[8 - t][ci][co]
   flip[((size_t)(8 - t) * CIP + ci) * COP + co] = f2bf(v);
-}
-
-// padded weight gradient [9][CIP][COP] (+ bias [COP]) -> flat [9][CIN][COUT] then [COUT]
-__global__ void unpad_grad_kernel(const float* __restrict__ gp, const float* __restrict__ gb, int CIN, int COUT, int CIP,
-                                  int COP, float* __restrict__ g) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int nw = 9 * CIN * COUT;
-  if (i < nw) {
-    const int t = i / (CIN * COUT);
-    const int rem = i - t * CIN * COUT;
-    const int ci = rem / COUT, co = rem - ci * COUT;
-    g[i] = gp[((size_t)t * CIP + ci) * COP + co];
-  } else if (i < nw + COUT) {
-    g[i] = gb[i - nw];
-  }
 }
 
 // ---------------------------------------------------------------------------- loss
@@ -317,7 +402,10 @@ __global__ void loss_kernel(LossArgs a) {
       g[2] = k * (tg[2] - dotp * ny);
       g[3] = k * (tg[3] - dotp * nz);
     }
-    for (int c = 0; c < 16; ++c) a.grad16[(size_t)i * 16 + c] = c < 4 ? f2bf(g[c]) : (uint16_t)0;
+    uint4* o16 = reinterpret_cast<uint4*>(a.grad16 + (size_t)i * 16);
+    o16[0] = make_uint4((uint32_t)f2bf(g[0]) | (uint32_t)f2bf(g[1]) << 16,
+                        (uint32_t)f2bf(g[2]) | (uint32_t)f2bf(g[3]) << 16, 0u, 0u);
+    o16[1] = make_uint4(0u, 0u, 0u, 0u);
   }
   red[threadIdx.x] = l;
   __syncthreads();
@@ -328,17 +416,28 @@ __global__ void loss_kernel(LossArgs a) {
   if (threadIdx.x == 0) a.loss_partial[blockIdx.x] = red[0];
 }
 
-// Adam on the fp32 master weights
-__global__ void adam_kernel(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m, float* __restrict__ v,
-                            int n, float lr, float b1, float b2, float eps, float c1, float c2) {
+// Adam on the fp32 master weights, and the bf16 copies of the weights it changes (their
+// padding is zero since pack_weights_kernel and stays so)
+__global__ void adam_kernel(AdamArgs a) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  if (i >= a.n) return;
+  const float gi = a.g[i];
+  const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
+  const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  const float w = a.w[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+  a.w[i] = w;
+  int l = 0;
+  while (l + 1 < a.n_layers && i >= a.layer[l + 1].first) ++l;
+  const PackLayer& L = a.layer[l];
+  const int k = i - L.first;
+  if (k >= 9 * L.cin * L.cout) return;  // a bias
+  const int t = k / (L.cin * L.cout);
+  const int rem = k - t * L.cin * L.cout;
+  const int ci = rem / L.cout, co = rem - ci * L.cout;
+  L.fwd[((size_t)t * L.CO + co) * L.CI + ci] = f2bf(w);
+  L.flip[((size_t)(8 - t) * L.CI + ci) * L.CO + co] = f2bf(w);
 }
 
 // ---------------------------------------------------------------------------- proposal
@@ -458,20 +557,59 @@ __global__ void targets_kernel(TargetArgs a) {
 
 namespace phimvs_net_internal {
 
-hipError_t launch_conv(const ConvArgs& a, hipStream_t st) {
+namespace {
+// rows a wave walks so that `units` strip rows make at most `waves` waves (and at least one
+// row each): enough waves to fill the chip once, as long as there are rows for them
+int band_rows(int64_t strips, int h, int64_t waves) {
+  int rb = (int)std::max<int64_t>(1, (strips * h + waves - 1) / waves);
+  while (rb < h && strips * ((h + rb - 1) / rb) > waves) ++rb;
+  return std::min(rb, h);
+}
+
+template <int CI, int CO, bool FIRST>
+hipError_t conv_launch(const ConvArgs& a, hipStream_t st) {
   const int segs = (a.w + 15) / 16;
-  const int tasks = a.B * a.h * segs;
-  if (a.CI % 16 || a.CO % 16 || a.CI < 16 || a.CO < 16 || a.CI > pmn::kMaxCI || a.CO > kMaxCO)
-    return hipErrorInvalidValue;
+  // 3 waves per SIMD by registers
+  const int rb = band_rows((int64_t)a.B * segs, a.h, 3072);
+  const int bands = (a.h + rb - 1) / rb;
+  const int64_t tasks = (int64_t)a.B * bands * segs;
   constexpr int wpb = pmn::kConvBlock / 64;
-  hipLaunchKernelGGL(pmn::conv3x3_kernel, dim3((tasks + wpb - 1) / wpb), dim3(pmn::kConvBlock), 0, st, a);
+  hipLaunchKernelGGL((pmn::conv3x3_kernel<CI, CO, FIRST>), dim3((unsigned)((tasks + wpb - 1) / wpb)),
+                     dim3(pmn::kConvBlock), 0, st, a, rb, segs, bands);
   return hipGetLastError();
 }
 
-hipError_t launch_wgrad(const WgradArgs& a, hipStream_t st) {
-  if (a.CI % 16 || a.CO % 16 || a.CI < 16 || a.CO < 16 || a.CI > kMaxCO || a.CO > kMaxCO) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pmn::conv3x3_wgrad_kernel, dim3(a.B * a.h), dim3(256), 0, st, a);
+template <int CI, int CO>
+hipError_t wgrad_launch(const WgradArgs& a, int n_partial, hipStream_t st) {
+  int rb, segs, bands;
+  if (wgrad_partials(a.B, a.h, a.w, &rb, &segs, &bands) != n_partial) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((pmn::conv3x3_wgrad_kernel<CI, CO>), dim3(n_partial), dim3(pmn::kWgBlock), 0, st, a, rb, segs,
+                     bands);
   return hipGetLastError();
+}
+}  // namespace
+
+int wgrad_partials(int B, int h, int w, int* rb, int* segs, int* bands) {
+  *segs = (w + 31) / 32;
+  *rb = band_rows((int64_t)B * *segs, h, 2048);  // 2 waves per SIMD by registers
+  *bands = (h + *rb - 1) / *rb;
+  const int64_t tasks = (int64_t)B * *bands * *segs;
+  return (int)((tasks + pmn::kWgBlock / 64 - 1) / (pmn::kWgBlock / 64));
+}
+
+hipError_t launch_conv(const ConvArgs& a, hipStream_t st) {
+  if (a.x32) return a.CI == 16 && a.CO == 32 ? conv_launch<16, 32, true>(a, st) : hipErrorInvalidValue;
+  if (a.CI == 32 && a.CO == 32) return conv_launch<32, 32, false>(a, st);
+  if (a.CI == 32 && a.CO == 16) return conv_launch<32, 16, false>(a, st);
+  if (a.CI == 16 && a.CO == 32) return conv_launch<16, 32, false>(a, st);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_wgrad(const WgradArgs& a, int n_partial, hipStream_t st) {
+  if (a.CI == 32 && a.CO == 32) return wgrad_launch<32, 32>(a, n_partial, st);
+  if (a.CI == 32 && a.CO == 16) return wgrad_launch<32, 16>(a, n_partial, st);
+  if (a.CI == 16 && a.CO == 32) return wgrad_launch<16, 32>(a, n_partial, st);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_bf16_unpad(const uint16_t* x, int n_pix, int CP, int C, float* y, hipStream_t st) {
@@ -481,15 +619,8 @@ hipError_t launch_bf16_unpad(const uint16_t* x, int n_pix, int CP, int C, float*
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_rows(const float* partial, int n_rows, int stride, int n, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(pmn::reduce_rows_kernel, dim3((n + 63) / 64), dim3(pmn::kReduceGroups * 64), 0, st, partial,
-                     n_rows, stride, n, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_to_bf16(const float* x, int n_pix, int C0, int CP, uint16_t* y, hipStream_t st) {
-  const size_t n = (size_t)n_pix * CP;
-  hipLaunchKernelGGL(pmn::to_bf16_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, n_pix, C0, CP, y);
+hipError_t launch_reduce_grads(const ReduceArgs& a, int n_blocks, hipStream_t st) {
+  hipLaunchKernelGGL(pmn::reduce_grads_kernel, dim3(n_blocks), dim3(pmn::kReduceGroups * 64), 0, st, a);
   return hipGetLastError();
 }
 
@@ -500,21 +631,13 @@ hipError_t launch_pack_weights(const float* w, int CIN, int COUT, int CIP, int C
   return hipGetLastError();
 }
 
-hipError_t launch_unpad_grad(const float* gp, const float* gb, int CIN, int COUT, int CIP, int COP, float* g,
-                             hipStream_t st) {
-  const int n = 9 * CIN * COUT + COUT;
-  hipLaunchKernelGGL(pmn::unpad_grad_kernel, dim3((n + 255) / 256), dim3(256), 0, st, gp, gb, CIN, COUT, CIP, COP, g);
-  return hipGetLastError();
-}
-
 hipError_t launch_loss(const LossArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(pmn::loss_kernel, dim3((a.n_pix + 255) / 256), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_adam(float* w, const float* g, float* m, float* v, int n, float lr, float b1, float b2, float eps,
-                       float c1, float c2, hipStream_t st) {
-  hipLaunchKernelGGL(pmn::adam_kernel, dim3((n + 255) / 256), dim3(256), 0, st, w, g, m, v, n, lr, b1, b2, eps, c1, c2);
+hipError_t launch_adam(const AdamArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(pmn::adam_kernel, dim3((a.n + 255) / 256), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

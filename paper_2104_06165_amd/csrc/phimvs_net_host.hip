@@ -20,6 +20,7 @@ using namespace phimvs_net_internal;
 namespace {
 
 constexpr int kLayers = PHIMVS_NET_LAYERS;
+static_assert(kLayers <= kMaxLayers && PHIMVS_NET_IN == 5 && PHIMVS_NET_OUT == 4, "the kernels' layer tables and shapes");
 constexpr int kCin[kLayers] = {PHIMVS_NET_IN, 32, 32, 32, 32};
 constexpr int kCout[kLayers] = {32, 32, 32, 32, PHIMVS_NET_OUT};
 constexpr int kCip[kLayers] = {16, 32, 32, 32, 32};   // padded to multiples of 16
@@ -62,7 +63,7 @@ struct phimvs_net {
   int last_B = 0, last_h = 0, last_w = 0;  // shape of the last forward pass
   bool have_act = false;   // act[] hold the last forward pass
   bool have_bwd = false;   // g16[] hold the backward pass of that forward pass
-  Buf<float> out32, partial, partial_b, gpad, gbias, loss_partial, tmp_in, tmp_out;
+  Buf<float> out32, partial, loss_partial, tmp_in, tmp_out;
 };
 
 namespace {
@@ -120,7 +121,6 @@ int forward(phimvs_net* n, int B, int h, int w, const float* input, float* outpu
     if ((rc = ensure(n, n->act[l], np * kCop[l - 1]))) return rc;
   n->have_act = false;
   n->have_bwd = false;
-  NCHECK(n, launch_to_bf16(input, (int)np, PHIMVS_NET_IN, kCip[0], n->act[0].p, n->stream));
   for (int l = 0; l < kLayers; ++l) {
     ConvArgs a{};
     a.B = B;
@@ -128,7 +128,9 @@ int forward(phimvs_net* n, int B, int h, int w, const float* input, float* outpu
     a.w = w;
     a.CI = kCip[l];
     a.CO = kCop[l];
-    a.x = n->act[l].p;
+    a.x = l == 0 ? nullptr : n->act[l].p;
+    a.x32 = l == 0 ? input : nullptr;
+    a.x16 = l == 0 ? n->act[0].p : nullptr;
     a.wt = n->wfwd[l];
     a.bias = n->params + layer_offset(l) + 9LL * kCin[l] * kCout[l];
     a.n_bias = kCout[l];
@@ -137,7 +139,7 @@ int forward(phimvs_net* n, int B, int h, int w, const float* input, float* outpu
     a.mask16 = nullptr;
     a.y16 = last ? nullptr : n->act[l + 1].p;
     a.y32 = last ? output : nullptr;
-    a.co_keep = last ? PHIMVS_NET_OUT : 0;
+    a.y32_aligned = (reinterpret_cast<uintptr_t>(output) & 15) == 0 ? 1 : 0;
     NCHECK(n, launch_conv(a, n->stream));
   }
   n->last_B = B;
@@ -198,7 +200,7 @@ void phimvs_net_destroy(phimvs_net* n) {
   }
   for (auto& b : n->act) release(b);
   for (auto& b : n->g16) release(b);
-  for (auto* b : {&n->out32, &n->partial, &n->partial_b, &n->gpad, &n->gbias, &n->loss_partial, &n->tmp_in, &n->tmp_out})
+  for (auto* b : {&n->out32, &n->partial, &n->loss_partial, &n->tmp_in, &n->tmp_out})
     release(*b);
   delete n;
 }
@@ -275,11 +277,18 @@ int phimvs_net_loss_grad(phimvs_net* n, int batch, int height, int width, const 
   la.loss_partial = n->loss_partial.p;
   NCHECK(n, launch_loss(la, n->stream));
 
-  const int rows = B * h;
-  const size_t max_w = 9 * 32 * 32;
-  if ((rc = ensure(n, n->partial, (size_t)rows * max_w)) || (rc = ensure(n, n->partial_b, (size_t)rows * 32)) ||
-      (rc = ensure(n, n->gpad, max_w)) || (rc = ensure(n, n->gbias, 32)))
-    return rc;
+  // every layer's partial sums, one after the other; one launch reduces them all
+  int rb, segs, bands;
+  const int n_partial = wgrad_partials(B, h, w, &rb, &segs, &bands);
+  size_t part_off[kLayers], part_n = 0;
+  ReduceArgs ra{};
+  ra.n_layers = kLayers;
+  int blocks = 0;
+  for (int l = 0; l < kLayers; ++l) {
+    part_off[l] = part_n;
+    part_n += (size_t)n_partial * (9 * kCip[l] + 1) * kCop[l];
+  }
+  if ((rc = ensure(n, n->partial, part_n))) return rc;
   for (int l = kLayers - 1; l >= 0; --l) {
     WgradArgs wa{};
     wa.B = B;
@@ -289,14 +298,8 @@ int phimvs_net_loss_grad(phimvs_net* n, int batch, int height, int width, const 
     wa.CO = kCop[l];
     wa.x = n->act[l].p;
     wa.g = n->g16[l].p;
-    wa.partial = n->partial.p;
-    wa.partial_bias = n->partial_b.p;
-    NCHECK(n, launch_wgrad(wa, n->stream));
-    const int nwp = 9 * kCip[l] * kCop[l];
-    NCHECK(n, launch_reduce_rows(n->partial.p, rows, nwp, nwp, n->gpad.p, n->stream));
-    NCHECK(n, launch_reduce_rows(n->partial_b.p, rows, kCop[l], kCop[l], n->gbias.p, n->stream));
-    NCHECK(n, launch_unpad_grad(n->gpad.p, n->gbias.p, kCin[l], kCout[l], kCip[l], kCop[l],
-                                n->grad + layer_offset(l), n->stream));
+    wa.partial = n->partial.p + part_off[l];
+    NCHECK(n, launch_wgrad(wa, n_partial, n->stream));
     if (l == 0) break;
     // data gradient into the input of layer l, through the ReLU of layer l - 1
     ConvArgs a{};
@@ -312,9 +315,14 @@ int phimvs_net_loss_grad(phimvs_net* n, int batch, int height, int width, const 
     a.mask16 = n->act[l].p;
     a.y16 = n->g16[l - 1].p;
     a.y32 = nullptr;
-    a.co_keep = 0;
     NCHECK(n, launch_conv(a, n->stream));
   }
+  for (int l = 0; l < kLayers; ++l) {
+    ra.layer[l] = {n->partial.p + part_off[l], n->grad + layer_offset(l), n_partial, kCip[l], kCop[l], kCin[l], kCout[l],
+                   blocks};
+    blocks += (int)((layer_params(l) + 63) / 64);
+  }
+  NCHECK(n, launch_reduce_grads(ra, blocks, n->stream));
   n->have_grad = true;
   n->have_bwd = true;
   if (grad)
@@ -354,9 +362,11 @@ int phimvs_net_adam(phimvs_net* n, float lr, float beta1, float beta2, float eps
   n->adam_t += 1;
   const float c1 = (float)(1.0 - std::pow((double)beta1, (double)n->adam_t));
   const float c2 = (float)(1.0 - std::pow((double)beta2, (double)n->adam_t));
-  NCHECK(n, launch_adam(n->params, n->grad, n->adam_m, n->adam_v, (int)total_params(), lr, beta1, beta2, eps, c1, c2,
-                        n->stream));
-  return repack(n);
+  AdamArgs a{n->params, n->grad, n->adam_m, n->adam_v, (int)total_params(), lr, beta1, beta2, eps, c1, c2, kLayers, {}};
+  for (int l = 0; l < kLayers; ++l)
+    a.layer[l] = {(int)layer_offset(l), kCip[l], kCop[l], kCin[l], kCout[l], n->wfwd[l], n->wflip[l]};
+  NCHECK(n, launch_adam(a, n->stream));
+  return PHIMVS_OK;
 }
 
 int phimvs_net_targets(phimvs_net* n, int width, int height, const float* depth, const float* normal,
