@@ -19,6 +19,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "phimvs_net_internal.h"
 
@@ -35,6 +36,13 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   u += 0x7FFFu + ((u >> 16) & 1u);
   return (uint16_t)(u >> 16);
 }
+// two of them in one dword; the hardware's conversion rounds the same way (checked on every
+// float that is not NaN)
+typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f{lo, hi}), v2b));
+}
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // ---------------------------------------------------------------------------- convolution
@@ -49,12 +57,14 @@ __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint
 // large copy; the matrix work is 3 us), so the work is split to read each row once: a wave
 // takes 16 columns x `rb` rows, holds all 9 x CI x CO weights in registers (72 VGPRs for
 // 32 x 32) and keeps three output rows in flight; a row's three shifted fragments feed all
-// of them, the next row's are loaded before this row's matrix instructions.  The weights
-// are the A operand, so that a lane ends with 4 consecutive channels of one pixel (8-byte
-// stores).  The order of every accumulation is taps, then input channels: 16x16x32 equals
+// of them (the columns beside a lane's own come from its neighbours), and two rows are in
+// flight beyond the one in use.  The weights
+// are the A operand, rows permuted, so that a lane ends with consecutive channels of one pixel
+// (one 16-byte store for 32 channels).  The order of every accumulation is taps, then input channels: 16x16x32 equals
 // two chained 16x16x16 over the lower and the upper 16 channels, bit for bit.
-// 800 x 533, 32 -> 32 channels: 47 us with a wave per 16 pixels of one row (each pixel read for
-// all nine taps, weights from LDS), 21 us so (2.6 TB/s); 8 x 267 x 400: 91 -> 36 us.
+// 800 x 533, 32 -> 32 channels: 47 us with a wave per 16 pixels of one row (each pixel read
+// for all nine taps, weights from LDS), 18 us so (3.0 TB/s; 21 us with three overlapping loads a
+// row and one row in flight); 8 x 267 x 400: 91 -> 29 us (3.8 TB/s).
 typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 template <int CI>
 struct Frag;  // one lane's share of 16 columns (or output channels) x CI input channels
@@ -74,6 +84,22 @@ __device__ __forceinline__ v4f mfma(const Frag<32>& a, const Frag<32>& b, v4f c)
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a.v), __builtin_bit_cast(v8b, b.v), c, 0, 0, 0);
 }
 
+// src of the lane before (0x111) or after (0x101) within 16 lanes; `edge` at the end lane
+template <int CTRL>
+__device__ __forceinline__ uint32_t shift1(uint32_t edge, uint32_t src) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)src, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ __forceinline__ uint2 shift(uint2 e, uint2 s) {
+  return make_uint2(shift1<CTRL>(e.x, s.x), shift1<CTRL>(e.y, s.y));
+}
+template <int CTRL>
+__device__ __forceinline__ uint4 shift(uint4 e, uint4 s) {
+  return make_uint4(shift1<CTRL>(e.x, s.x), shift1<CTRL>(e.y, s.y), shift1<CTRL>(e.z, s.z), shift1<CTRL>(e.w, s.w));
+}
+
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
 constexpr int kConvBlock = 256;  // 4 waves on neighbouring strips
 template <int CI, int CO, bool FIRST>
 __global__ __launch_bounds__(kConvBlock) __attribute__((amdgpu_waves_per_eu(3))) void conv3x3_kernel(ConvArgs a, int rb, int segs, int bands) {
@@ -92,55 +118,65 @@ __global__ __launch_bounds__(kConvBlock) __attribute__((amdgpu_waves_per_eu(3)))
   for (int t = 0; t < 9; ++t)
 #pragma unroll
     for (int i = 0; i < NCO; ++i)
-      W[t][i].v = *reinterpret_cast<const decltype(W[t][i].v)*>(a.wt + (size_t)(t * CO + i * 16 + lr) * CI + lk * KL);
+      W[t][i].v = *reinterpret_cast<const decltype(W[t][i].v)*>(
+          a.wt + (size_t)(t * CO + (lr >> 2) * 4 * NCO + i * 4 + (lr & 3)) * CI + lk * KL);
   float bias[NCO][4];
 #pragma unroll
   for (int i = 0; i < NCO; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int co = i * 16 + lk * 4 + j;
+      const int co = lk * 4 * NCO + i * 4 + j;
       bias[i][j] = (a.bias && co < a.n_bias) ? a.bias[co] : 0.f;
     }
-  const bool in[3] = {c >= 1 && c - 1 < a.w, c < a.w, c + 1 < a.w};
-  // fragments of input row i (zero outside the image), columns c - 1, c, c + 1
-  auto load_row = [&](int i, Frag<CI> (&F)[3]) {
-    const bool rin = i >= 0 && i < a.h;
-    const size_t row = ((size_t)b * a.h + (rin ? i : 0)) * a.w;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const bool ok = rin && in[d];
-      const size_t pix = row + (ok ? c + d - 1 : 0);
-      if constexpr (FIRST) {
-        // lanes of the first K group hold channels 0..3, the second's channel 4, the rest 0
-        float x[4] = {0.f, 0.f, 0.f, 0.f};
-        if (ok && lk == 0) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) x[j] = a.x32[pix * 5 + j];
-        }
-        if (ok && lk == 1) x[0] = a.x32[pix * 5 + 4];
-        F[d].v = make_uint2((uint32_t)f2bf(x[0]) | (uint32_t)f2bf(x[1]) << 16,
-                            (uint32_t)f2bf(x[2]) | (uint32_t)f2bf(x[3]) << 16);
-      } else {
-        F[d].v = decltype(F[d].v){};
-        if (ok) F[d].v = *reinterpret_cast<const decltype(F[d].v)*>(a.x + pix * CI + lk * KL);
-      }
+  // A row is loaded once: each lane its own column, and the lanes at the strip's ends the
+  // column beside it; the shifted fragments come from the neighbouring lanes.
+  const bool mine = c < a.w;
+  const int ch = lr == 0 ? c - 1 : c + 1;
+  const bool edge = (lr == 0 || lr == 15) && ch >= 0 && ch < a.w;
+  // FIRST: lanes of the first K group hold channels 0..3, the second's channel 4 (the last of
+  // the four it loads), the rest 0; 16-byte loads at 4-byte alignment, rounded when used
+  typedef std::conditional_t<FIRST, f4u, decltype(Frag<CI>::v)> Raw;
+  struct Row {
+    Raw own, halo;
+  };
+  auto load_px = [&](int i, int col, bool ok, Raw& f) {
+    f = Raw{};
+    if (!ok) return;
+    const size_t pix = ((size_t)b * a.h + i) * a.w + col;
+    if constexpr (FIRST) {
+      if (lk < 2) f = *reinterpret_cast<const f4u*>(a.x32 + pix * 5 + lk);
+    } else {
+      f = *reinterpret_cast<const Raw*>(a.x + pix * CI + lk * KL);
     }
   };
-  Frag<CI> F[3], N[3];
-  load_row(r0 - 1, F);
+  auto rounded = [&](const Raw& f) {
+    if constexpr (FIRST)
+      return make_uint2(lk == 0 ? pack_bf(f[0], f[1]) : pack_bf(f[3], 0.f), lk == 0 ? pack_bf(f[2], f[3]) : 0u);
+    else
+      return f;
+  };
+  auto load_row = [&](int i, Row& r) {
+    const bool rin = i >= 0 && i < a.h;
+    load_px(i, c, rin && mine, r.own);
+    load_px(i, ch, rin && edge, r.halo);
+  };
+  Row R0, R1, R2;
+  load_row(r0 - 1, R0);
+  load_row(r0, R1);
   v4f a0[NCO], a1[NCO], a2[NCO];  // output rows i + 1, i, i - 1 of the row being read
 #pragma unroll
   for (int i = 0; i < NCO; ++i) a1[i] = a2[i] = v4f{0.f, 0.f, 0.f, 0.f};
   for (int i = r0 - 1; i <= r1; ++i) {
     const bool store = i - 1 >= r0 && c < a.w;
     const size_t p = ((size_t)b * a.h + (store ? i - 1 : 0)) * a.w + (store ? c : 0);
-    uint2 m[NCO];
-#pragma unroll
-    for (int k = 0; k < NCO; ++k) {
-      m[k] = make_uint2(0u, 0u);
-      if (a.mask16 && store) m[k] = *reinterpret_cast<const uint2*>(a.mask16 + p * CO + k * 16 + lk * 4);
-    }
-    if (i < r1) load_row(i + 1, N);
+    Frag<CO> m;  // the mask at this lane's pixel and output channels
+    m.v = decltype(m.v){};
+    if (a.mask16 && store) m.v = *reinterpret_cast<const decltype(m.v)*>(a.mask16 + p * CO + lk * 4 * NCO);
+    if (i + 2 <= r1) load_row(i + 2, R2);
+    Frag<CI> F[3];  // columns c - 1, c, c + 1
+    F[1].v = rounded(R0.own);
+    F[0].v = shift<0x111>(rounded(R0.halo), F[1].v);
+    F[2].v = shift<0x101>(rounded(R0.halo), F[1].v);
     if constexpr (FIRST) {
       if (i >= r0 && i < r1 && c < a.w)
         *reinterpret_cast<uint2*>(a.x16 + (((size_t)b * a.h + i) * a.w + c) * 16 + lk * 4) = F[1].v;
@@ -156,20 +192,20 @@ __global__ __launch_bounds__(kConvBlock) __attribute__((amdgpu_waves_per_eu(3)))
       }
     }
     if (store) {
+      // a2[k][j]: pixel (i - 1, c), output channel 4 NCO lk + 4 k + j
+      uint32_t mw[2 * NCO], o[2 * NCO];
+      __builtin_memcpy(mw, &m, sizeof mw);
 #pragma unroll
       for (int k = 0; k < NCO; ++k) {
-        // a2[k][j]: pixel (i - 1, c), output channel 16 k + 4 lk + j
         float v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           v[j] = a2[k][j] + bias[k][j];
           if (a.relu) v[j] = fmaxf(v[j], 0.f);
-          if (a.mask16 && !(bf2f((uint16_t)((j & 2 ? m[k].y : m[k].x) >> (j & 1 ? 16 : 0))) > 0.f)) v[j] = 0.f;
+          if (a.mask16 && !(bf2f((uint16_t)(mw[2 * k + j / 2] >> (j & 1 ? 16 : 0))) > 0.f)) v[j] = 0.f;
         }
-        if (a.y16)
-          *reinterpret_cast<uint2*>(a.y16 + p * CO + k * 16 + lk * 4) =
-              make_uint2((uint32_t)f2bf(v[0]) | (uint32_t)f2bf(v[1]) << 16,
-                         (uint32_t)f2bf(v[2]) | (uint32_t)f2bf(v[3]) << 16);
+        o[2 * k] = pack_bf(v[0], v[1]);
+        o[2 * k + 1] = pack_bf(v[2], v[3]);
         if (a.y32 && k == 0 && lk == 0) {
           if (a.y32_aligned) {
             *reinterpret_cast<float4*>(a.y32 + p * 4) = make_float4(v[0], v[1], v[2], v[3]);
@@ -179,14 +215,19 @@ __global__ __launch_bounds__(kConvBlock) __attribute__((amdgpu_waves_per_eu(3)))
           }
         }
       }
+      if (a.y16) {
+        Frag<CO> y;
+        __builtin_memcpy(&y, o, sizeof o);
+        *reinterpret_cast<decltype(y.v)*>(a.y16 + p * CO + lk * 4 * NCO) = y.v;
+      }
     }
 #pragma unroll
     for (int k = 0; k < NCO; ++k) {
       a2[k] = a1[k];
       a1[k] = a0[k];
     }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) F[d] = N[d];
+    R0 = R1;
+    R1 = R2;
   }
 }
 
@@ -194,20 +235,36 @@ __global__ __launch_bounds__(kConvBlock) __attribute__((amdgpu_waves_per_eu(3)))
 // and the bias gradient's sums of g.  One wave takes a strip of 32 columns x rb rows and all
 // 9 x CI x CO sums (144 accumulator registers for 32 x 32); walking down, each input row meets
 // the gradients of the three rows it enters.  The contraction runs over columns, which NHWC
-// scatters, so a lane loads its two channels (2 lr, 2 lr + 1) of each of its 8 columns (and one
-// either side) as dwords and pairs them up with byte permutes: row lr of the matrix
-// instruction stands for channel 2 lr (low halves) or 2 lr + 1 (high halves).  The waves of a
-// workgroup add their sums in LDS in wave order; workgroup k's go to partial + k * stride
-// ([9][CI][CO], then [CO] bias sums).
+// scatters, so a wave stages each row (34 input and 32 gradient pixels, 16-byte loads, the
+// next row's in flight) in its own part of LDS and reads it back through the transposing LDS
+// read: lane lr of 16 gets channel lr of 4 columns.  The waves of a workgroup add their sums in
+// LDS in wave order; workgroup k's go to partial + k * stride ([9][CI][CO], then [CO] bias sums).
 // 8 x 267 x 400, 32 x 32 channels: 176 us with a workgroup per image row (2136 partial sums of
-// 36 KB to write and reduce, another 14 us), 81 us so (234 partial sums).
+// 36 KB to write and reduce, another 14 us); 81 us with these strips and dwords of two channels
+// gathered and paired up per lane; 56 us through the transposing read; 28 us (234 partial sums)
+// with the waves' sums added by the whole workgroup instead of by one wave after the other.
 constexpr int kWgBlock = 512;
-__device__ __forceinline__ uint32_t pair_lo(uint32_t p, uint32_t q) { return __builtin_amdgcn_perm(q, p, 0x05040100u); }
-__device__ __forceinline__ uint32_t pair_hi(uint32_t p, uint32_t q) { return __builtin_amdgcn_perm(q, p, 0x07060302u); }
+typedef __attribute__((address_space(3))) v4s* LdsV4s;
+// columns 8 lk + p0 .. + 7 of channels ch0 + lr from a staged row of C channels per pixel
+template <int C>
+__device__ __forceinline__ Frag<32> read_columns(const uint16_t* row, int p0, int ch0, int lr, int lk) {
+  const uint16_t* at = row + (8 * lk + p0 + lr / 4) * C + ch0 + 4 * (lr & 3);
+  const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsV4s)at);
+  const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsV4s)(at + 4 * C));
+  Frag<32> f;
+  __builtin_memcpy(&f.v.x, &lo, 8);
+  __builtin_memcpy(&f.v.z, &hi, 8);
+  return f;
+}
 template <int CI, int CO>
 __global__ __launch_bounds__(kWgBlock) void conv3x3_wgrad_kernel(WgradArgs a, int rb, int segs, int bands) {
   constexpr int NCI = CI / 16, NCO = CO / 16, kSums = 9 * CI * CO;
-  __shared__ float red[kSums + CO];
+  // 16-byte chunks of a staged row: the input's 34 pixels, the gradient's 32; per lane
+  constexpr int kXc = 34 * CI / 8, kGc = 32 * CO / 8, kXl = (kXc + 63) / 64, kGl = kGc / 64;
+  // a wave's staged rows; after the last row, the sums of three taps of every wave
+  constexpr int kWaves = kWgBlock / 64, kRegs = 3 * NCI * NCO * 4;
+  constexpr int kStageBytes = kWaves * (kXc + kGc) * 16, kRedBytes = kWaves * (kRegs + NCO) * 64 * 4;
+  __shared__ uint4 lds[(kStageBytes > kRedBytes ? kStageBytes : kRedBytes) / 16];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int lr = lane & 15, lk = lane >> 4;
   const int task = blockIdx.x * (kWgBlock / 64) + wave;  // (b, band, seg)
@@ -216,7 +273,8 @@ __global__ __launch_bounds__(kWgBlock) void conv3x3_wgrad_kernel(WgradArgs a, in
   const int bb = task / segs;
   const int band = bb % bands, b = work ? bb / bands : 0;
   const int r0 = band * rb, r1 = work ? min(r0 + rb, a.h) : r0 - 2;
-  const int c0 = seg * 32 + 8 * lk;  // this lane's first column
+  uint4* xs = lds + wave * (kXc + kGc);
+  uint4* gs = xs + kXc;
   v4f acc[9][NCI][NCO], accb[NCO];
 #pragma unroll
   for (int t = 0; t < 9; ++t)
@@ -226,50 +284,65 @@ __global__ __launch_bounds__(kWgBlock) void conv3x3_wgrad_kernel(WgradArgs a, in
       for (int v = 0; v < NCO; ++v) acc[t][u][v] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int v = 0; v < NCO; ++v) accb[v] = v4f{0.f, 0.f, 0.f, 0.f};
-  // this lane's channels (two, or one) of column c of row i; zero outside the image
-  auto px = [&](const uint16_t* __restrict__ p, int C, int i, int c) -> uint32_t {
-    if (!(c >= 0 && c < a.w)) return 0u;
-    const size_t at = (((size_t)b * a.h + i) * a.w + c) * C;
-    return C == 32 ? *reinterpret_cast<const uint32_t*>(p + at + 2 * lr) : (uint32_t)p[at + lr];
-  };
-  auto load_x = [&](int i, uint32_t (&v)[10]) {
-    const bool rin = i >= 0 && i < a.h;
+  // this lane's chunks of a row: element offset within the row, and whether the column exists
+  int xo[kXl], go[kGl];
+  bool xi[kXl], gi[kGl];
 #pragma unroll
-    for (int j = 0; j < 10; ++j) v[j] = rin ? px(a.x, CI, i, c0 + j - 1) : 0u;
-  };
-  auto load_g = [&](int i, uint32_t (&v)[8]) {
-    const bool rin = i >= r0 && i < r1;
+  for (int k = 0; k < kXl; ++k) {
+    const int q = lane + 64 * k, c = seg * 32 - 1 + q / (CI / 8);
+    xi[k] = q < kXc && c >= 0 && c < a.w;
+    xo[k] = xi[k] ? c * CI + (q % (CI / 8)) * 8 : 0;
+  }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = rin ? px(a.g, CO, i, c0 + j) : 0u;
-  };
-  auto frag = [](const uint32_t* v, int half) {
-    Frag<32> f;
-    f.v = half ? make_uint4(pair_hi(v[0], v[1]), pair_hi(v[2], v[3]), pair_hi(v[4], v[5]), pair_hi(v[6], v[7]))
-               : make_uint4(pair_lo(v[0], v[1]), pair_lo(v[2], v[3]), pair_lo(v[4], v[5]), pair_lo(v[6], v[7]));
-    return f;
+  for (int k = 0; k < kGl; ++k) {
+    const int q = lane + 64 * k, c = seg * 32 + q / (CO / 8);
+    gi[k] = c < a.w;
+    go[k] = gi[k] ? c * CO + (q % (CO / 8)) * 8 : 0;
+  }
+  uint4 xr[kXl], gr[kGl];
+  // input row i and gradient row i + 1 (zero outside the image, and outside the band)
+  auto load_rows = [&](int i) {
+    const bool xin = i >= 0 && i < a.h, gin = i + 1 >= r0 && i + 1 < r1;
+    const uint16_t* xp = a.x + ((size_t)b * a.h + (xin ? i : 0)) * a.w * CI;
+    const uint16_t* gp = a.g + ((size_t)b * a.h + (gin ? i + 1 : 0)) * a.w * CO;
+#pragma unroll
+    for (int k = 0; k < kXl; ++k) {
+      xr[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (xin && xi[k]) xr[k] = *reinterpret_cast<const uint4*>(xp + xo[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kGl; ++k) {
+      gr[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (gin && gi[k]) gr[k] = *reinterpret_cast<const uint4*>(gp + go[k]);
+    }
   };
   Frag<32> ones;
   ones.v = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
   Frag<32> g0[NCO], g1[NCO], g2[NCO];  // gradient rows i + 1, i, i - 1
 #pragma unroll
   for (int v = 0; v < NCO; ++v) g1[v].v = g2[v].v = make_uint4(0u, 0u, 0u, 0u);
-  uint32_t xr[10], gr[8];
-  if (r0 <= r1) {
-    load_x(r0 - 1, xr);
-    load_g(r0, gr);
-  }
+  if (r0 <= r1) load_rows(r0 - 1);
   for (int i = r0 - 1; i <= r1; ++i) {
+    // the staged row is this wave's own: its LDS operations stay in order
+#pragma unroll
+    for (int k = 0; k < kXl; ++k)
+      if (lane + 64 * k < kXc) xs[lane + 64 * k] = xr[k];
+#pragma unroll
+    for (int k = 0; k < kGl; ++k) gs[lane + 64 * k] = gr[k];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (i < r1) load_rows(i + 1);
     Frag<32> X[3][NCI];
 #pragma unroll
     for (int d = 0; d < 3; ++d)
 #pragma unroll
-      for (int u = 0; u < NCI; ++u) X[d][u] = frag(xr + d, u);
+      for (int u = 0; u < NCI; ++u)
+        X[d][u] = read_columns<CI>(reinterpret_cast<const uint16_t*>(xs), d, 16 * u, lr, lk);
 #pragma unroll
-    for (int v = 0; v < NCO; ++v) g0[v] = frag(gr, v);
-    if (i < r1) {
-      load_x(i + 1, xr);
-      load_g(i + 2, gr);
-    }
+    for (int v = 0; v < NCO; ++v)
+      g0[v] = read_columns<CO>(reinterpret_cast<const uint16_t*>(gs), 0, 16 * v, lr, lk);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int v = 0; v < NCO; ++v) {
       accb[v] = mfma(ones, g0[v], accb[v]);
@@ -285,32 +358,38 @@ __global__ __launch_bounds__(kWgBlock) void conv3x3_wgrad_kernel(WgradArgs a, in
       g1[v] = g0[v];
     }
   }
-  // acc[t][u][v][j]: ci = NCI (4 lk + j) + u, co = NCO lr + v; accb[v][*]: co = NCO lr + v
-  for (int w = 0; w < kWgBlock / 64; ++w) {
-    if (wave == w) {
-#pragma unroll
-      for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int u = 0; u < NCI; ++u)
-#pragma unroll
-          for (int v = 0; v < NCO; ++v)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int e = (t * CI + NCI * (4 * lk + j) + u) * CO + NCO * lr + v;
-              red[e] = w ? red[e] + acc[t][u][v][j] : acc[t][u][v][j];
-            }
-      if (lk == 0) {
-#pragma unroll
-        for (int v = 0; v < NCO; ++v) {
-          const int e = kSums + NCO * lr + v;
-          red[e] = w ? red[e] + accb[v][0] : accb[v][0];
-        }
-      }
-    }
-    __syncthreads();
-  }
+  // The waves' sums, three taps at a time: every wave lays its registers out lane by lane, then
+  // the workgroup adds them in wave order.  Register ((t, u, v), j) of lane (lr, lk) is the sum of
+  // tap t, ci = 16 u + 4 lk + j, co = 16 v + lr; accb[v] of a lane with lk = 0 the bias's co.
+  float* red = reinterpret_cast<float*>(lds);
   float* P = a.partial + (size_t)blockIdx.x * (kSums + CO);
-  for (int e = threadIdx.x; e < kSums + CO; e += kWgBlock) P[e] = red[e];
+#pragma unroll
+  for (int ty = 0; ty < 3; ++ty) {
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int u = 0; u < NCI; ++u)
+#pragma unroll
+        for (int v = 0; v < NCO; ++v)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            red[(wave * (kRegs + NCO) + ((d * NCI + u) * NCO + v) * 4 + j) * 64 + lane] = acc[3 * ty + d][u][v][j];
+#pragma unroll
+    for (int v = 0; v < NCO; ++v) red[(wave * (kRegs + NCO) + kRegs + v) * 64 + lane] = accb[v][0];
+    __syncthreads();
+    for (int i = threadIdx.x; i < (kRegs + (ty == 0 ? NCO : 0)) * 64; i += kWgBlock) {
+      float s = red[i];
+      for (int w = 1; w < kWaves; ++w) s = s + red[w * (kRegs + NCO) * 64 + i];
+      const int reg = i >> 6, l15 = i & 15, l4 = (i >> 4) & 3;
+      if (reg >= kRegs) {
+        if (l4 == 0) P[kSums + 16 * (reg - kRegs) + l15] = s;
+        continue;
+      }
+      const int j = reg & 3, v = (reg >> 2) % NCO, u = (reg >> 2) / NCO % NCI, d = (reg >> 2) / (NCO * NCI);
+      P[((3 * ty + d) * CI + 16 * u + 4 * l4 + j) * CO + 16 * v + l15] = s;
+    }
+  }
 }
 
 // The gradient of every layer from its workgroups' partial sums, in a fixed order: a
@@ -403,8 +482,7 @@ __global__ void loss_kernel(LossArgs a) {
       g[3] = k * (tg[3] - dotp * nz);
     }
     uint4* o16 = reinterpret_cast<uint4*>(a.grad16 + (size_t)i * 16);
-    o16[0] = make_uint4((uint32_t)f2bf(g[0]) | (uint32_t)f2bf(g[1]) << 16,
-                        (uint32_t)f2bf(g[2]) | (uint32_t)f2bf(g[3]) << 16, 0u, 0u);
+    o16[0] = make_uint4(pack_bf(g[0], g[1]), pack_bf(g[2], g[3]), 0u, 0u);
     o16[1] = make_uint4(0u, 0u, 0u, 0u);
   }
   red[threadIdx.x] = l;
