@@ -288,7 +288,7 @@ void phimvs_default_fuse_params(phimvs_fuse_params* p);
  *   owner   (int64 per pixel): the concatenated index of the point the pixel ended in,
  *           -1 for pixels without depth.
  * All arithmetic is FP64.  Work is queued on the context's stream; the library keeps
- * scratch of 5 bytes per concatenated pixel.  p = NULL uses the default threshold. */
+ * scratch of 12 bytes per concatenated pixel.  p = NULL uses the default threshold. */
 int phimvs_fuse(phimvs_ctx* ctx, int n_maps, const phimvs_depth_map* maps, const phimvs_fuse_params* p,
                 float* points, int32_t* support, int64_t* owner);
 

@@ -2,14 +2,31 @@
 // walks the maps in order and, within a map, its pixels one by one; a later pixel only
 // sees what earlier ones deleted.  Within one map's step the only state that changes is
 // the deletion of pixels of later maps, and a pixel of map j is deleted by the first pixel
-// (row-major) of map i that passes the test against it.  So each step is two launches:
-// every pixel of map i tests its candidate in each later map and claims it with an atomic
-// minimum of its own index; then every pixel merges exactly the candidates it won.  The
-// result equals the sequential walk.  All arithmetic is FP64, each expression in the order
-// written, so both launches compute the same candidate for a pixel.
+// (row-major) of map i that passes the test against it.  With a pixel's key its index in the
+// concatenated maps, the pixel that deletes q is therefore the live one of the smallest key
+// that passes, and one atomic minimum per test settles it for good: a claim of an earlier
+// step is smaller than any later one's, and a claimed pixel is dead from the next step on.
+// So each step is one launch (every live pixel of map i claims its candidates), and one
+// launch at the end turns every pixel that nobody claimed into a point with the candidates
+// it won, and writes each output once.  The result equals the sequential walk.
+//
+// All results are FP64 evaluations of the expressions in the order written (back_project,
+// project_round, the squared distance).  The tests bound the work: FP64 instructions, about
+// 200 for a pixel and a later map in that form (two camera chains through the world and two
+// divisions).  They are decided by a shorter one, X_j = d A (x, y, 1) + t with A = R_j R_i^T
+// K_i^-1 from a table and the distance taken in camera j, together with a bound of the
+// difference between the two; a lane whose test lies within that bound of the other
+// outcome (a rounding boundary of the pixel position, the distance limit) takes the
+// expressions as written, so the decisions are theirs.  Nine 961 x 640 maps (5.5 M pixels):
+// 422 us with both launches in every step (init 47, claims refilled 64, claim 142, merge 154 us)
+// and the written form throughout, 302 us so (init 12, claim 181, merge 84 us: the merge issues
+// FP64 on 75% of its cycles; the first claim launch, 50 us, has 18 us of atomics, which memory
+// carries out).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "phimvs_internal.h"
 
@@ -18,6 +35,8 @@ namespace pmu {
 using namespace phimvs_internal;
 
 constexpr int kBlock = 256;
+constexpr int kGroup = 4;
+constexpr uint64_t kFree = ~0ull;  // claim of a pixel nobody has taken
 
 // pixel (x, y) at depth d of a map's camera -> world point: R^T (d K^-1 (x, y, 1) - t)
 __device__ __forceinline__ void back_project(const FuseMap& m, int x, int y, double d, double* Xw) {
@@ -42,113 +61,295 @@ __device__ __forceinline__ bool project_round(const FuseMap& m, const double* Xw
   return true;
 }
 
-__global__ __launch_bounds__(kBlock) void fuse_init_kernel(FuseMap m, uint8_t* __restrict__ alive,
-                                                           float* __restrict__ points, int32_t* __restrict__ support,
-                                                           int64_t* __restrict__ owner) {
-  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t n = (int64_t)m.W * m.H;
-  if (p >= n) return;
-  const int64_t g = m.off + p;
-  alive[g] = m.depth[p] > 0.0f ? 1 : 0;
-  support[g] = 0;
-  owner[g] = -1;
-  points[3 * g] = 0.0f;
-  points[3 * g + 1] = 0.0f;
-  points[3 * g + 2] = 0.0f;
+// ---------------------------------------------------------------------------- the short form
+// Pair (i, j): pixel (x, y) of map i at depth d is X = d A (x, y, 1) + t in camera j and p = d P
+// (x, y, 1) + s on its image, A = R_j R_i^T K_i^-1, t = t_j - R_j R_i^T t_i, P = K_j A, s = K_j t.
+// A point differs between the two forms by at most delta = c0 + c1 d in any coordinate: 512 x
+// 2^-53 of the magnitudes that enter (the forms are a few 3-term products of them, each within
+// a few units), and p by kn delta with kn the row's sum of magnitudes in K_j, counted four
+// times here.  cu and cv bound the position's share of that for positions inside image j or
+// within a pixel of it, eu and ev the quotient's own rounding.
+__device__ void make_pair(const FuseMap& a, const FuseMap& b, FusePair& o) {
+  double R[9], kn[3];
+  for (int r = 0; r < 3; ++r)
+    for (int c = 0; c < 3; ++c)
+      R[3 * r + c] = b.R[3 * r] * a.R[3 * c] + b.R[3 * r + 1] * a.R[3 * c + 1] + b.R[3 * r + 2] * a.R[3 * c + 2];
+  double ray = 0.0, ti = 0.0, tj = 0.0;
+  for (int r = 0; r < 3; ++r) {
+    for (int c = 0; c < 3; ++c)
+      o.A[3 * r + c] = R[3 * r] * a.Kinv[c] + R[3 * r + 1] * a.Kinv[3 + c] + R[3 * r + 2] * a.Kinv[6 + c];
+    o.t[r] = b.t[r] - (R[3 * r] * a.t[0] + R[3 * r + 1] * a.t[1] + R[3 * r + 2] * a.t[2]);
+    ray += fabs(a.Kinv[3 * r]) * a.W + fabs(a.Kinv[3 * r + 1]) * a.H + fabs(a.Kinv[3 * r + 2]);
+    ti += fabs(a.t[r]);
+    tj += fabs(b.t[r]);
+    kn[r] = fabs(b.K[3 * r]) + fabs(b.K[3 * r + 1]) + fabs(b.K[3 * r + 2]);
+  }
+  for (int r = 0; r < 3; ++r) {
+    for (int c = 0; c < 3; ++c)
+      o.P[3 * r + c] = b.K[3 * r] * o.A[c] + b.K[3 * r + 1] * o.A[3 + c] + b.K[3 * r + 2] * o.A[6 + c];
+    o.s[r] = b.K[3 * r] * o.t[0] + b.K[3 * r + 1] * o.t[1] + b.K[3 * r + 2] * o.t[2];
+  }
+  o.c0 = 512.0 * 0x1p-53 * (ti + tj);
+  o.c1 = 512.0 * 0x1p-53 * ray;
+  o.kw = 4.0 * kn[2];
+  o.cu = 4.0 * (kn[0] + (b.W + 1) * kn[2]);
+  o.cv = 4.0 * (kn[1] + (b.H + 1) * kn[2]);
+  o.eu = 0x1p-46 * (b.W + 2);
+  o.ev = 0x1p-46 * (b.H + 2);
 }
 
-__global__ __launch_bounds__(kBlock) void fuse_fill_kernel(int32_t* __restrict__ a, int64_t n, int32_t v) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) a[i] = v;
+// 1 / x to within a few units in the last place (x normal)
+__device__ __forceinline__ double rcp_near(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
 }
 
-// every live pixel of map i claims, in each later map, the candidate that passes the test
-__global__ __launch_bounds__(kBlock) void fuse_claim_kernel(const FuseMap* __restrict__ maps, int n_maps, int i,
-                                                            double tau, const uint8_t* __restrict__ alive,
-                                                            int32_t* __restrict__ claim) {
-  const FuseMap& mi = maps[i];
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p >= mi.W * mi.H || !alive[mi.off + p]) return;
-  const int y = p / mi.W, x = p - y * mi.W;
-  const double d = mi.depth[p];
-  double Xi[3];
-  back_project(mi, x, y, d, Xi);
-  const double lim = tau * d;
-  for (int j = i + 1; j < n_maps; ++j) {
-    const FuseMap& mj = maps[j];
-    int qx, qy;
-    if (!project_round(mj, Xi, qx, qy)) continue;
-    const int64_t q = (int64_t)qy * mj.W + qx;
-    if (!alive[mj.off + q]) continue;
-    double Yw[3];
-    back_project(mj, qx, qy, (double)mj.depth[q], Yw);
-    const double e0 = Yw[0] - Xi[0], e1 = Yw[1] - Xi[1], e2 = Yw[2] - Xi[2];
-    if (!(e0 * e0 + e1 * e1 + e2 * e2 < lim * lim)) continue;
-    atomicMin(&claim[mj.off + q], p);
+// The pixel of map j nearest to the projection of pixel (x, y) of map i at depth d: 1 found
+// (qx, qy), 0 none, -1 too close to call.
+__device__ __forceinline__ int project_short(const FuseMap& mj, const FusePair& P, double px, double py, double d,
+                                             double delta, int& qx, int& qy) {
+  double p[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    p[k] = __builtin_fma(d, __builtin_fma(P.P[3 * k], px, __builtin_fma(P.P[3 * k + 1], py, P.P[3 * k + 2])), P.s[k]);
+  const double e2 = P.kw * delta;
+  if (!(p[2] > e2)) return p[2] < -e2 ? 0 : -1;
+  const double r = rcp_near(p[2]);
+  const double u = p[0] * r, v = p[1] * r, rd = delta * r;
+  const double mu = __builtin_fma(rd, P.cu, P.eu), mv = __builtin_fma(rd, P.cv, P.ev);
+  // with these below 1/4, a position more than a pixel outside is outside in either form
+  if (!(mu < 0.25 && mv < 0.25)) return -1;
+  if (!(u >= -1.0 && u <= (double)mj.W && v >= -1.0 && v <= (double)mj.H)) return 0;
+  const double xs = u + 0.5, ys = v + 0.5;
+  const double xr = floor(xs), yr = floor(ys);
+  const double fx = xs - xr, fy = ys - yr;
+  if (!(fx >= mu && fx <= 1.0 - mu && fy >= mv && fy <= 1.0 - mv)) return -1;
+  qx = (int)xr;
+  qy = (int)yr;
+  return (unsigned)qx < (unsigned)mj.W && (unsigned)qy < (unsigned)mj.H ? 1 : 0;
+}
+
+// s / n, rounded once: a quotient by the rounded reciprocal and one correction by its remainder
+// is the correctly rounded quotient (Markstein) where nothing over- or underflows
+__device__ __forceinline__ double div_by(double s, double n, double rn) {
+  const double q = s * rn;
+  const double c = __builtin_fma(__builtin_fma(-n, q, s), rn, q);
+  return fabs(s) < 0x1p900 && fabs(s) > 0x1p-900 ? c : s / n;
+}
+
+__global__ __launch_bounds__(kBlock) void fuse_pairs_kernel(const FuseMap* __restrict__ maps, int n_maps, int row0,
+                                                            int rows, FusePair* __restrict__ pairs) {
+  const int k = blockIdx.x * kBlock + threadIdx.x;
+  const int i = row0 + k / n_maps, j = k % n_maps;
+  if (k < rows * n_maps && j > i) make_pair(maps[i], maps[j], pairs[k]);
+}
+
+// claims of every pixel free; the first rows of the pair table
+__global__ __launch_bounds__(kBlock) void fuse_init_kernel(const FuseMap* __restrict__ maps, int n_maps, int rows,
+                                                           FusePair* __restrict__ pairs, uint64_t* __restrict__ claim,
+                                                           int64_t total) {
+  const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (k < (int64_t)rows * n_maps) {
+    const int i = (int)(k / n_maps), j = (int)(k % n_maps);
+    if (j > i) make_pair(maps[i], maps[j], pairs[k]);
+  }
+  if (2 * k + 1 < total) {
+    reinterpret_cast<ulonglong2*>(claim)[k] = make_ulonglong2(kFree, kFree);
+  } else if (2 * k < total) {
+    claim[2 * k] = kFree;
   }
 }
 
-// every live pixel of map i becomes a point with the candidates it won, which are deleted
-__global__ __launch_bounds__(kBlock) void fuse_merge_kernel(const FuseMap* __restrict__ maps, int n_maps, int i,
-                                                            uint8_t* __restrict__ alive,
-                                                            const int32_t* __restrict__ claim,
+// every live pixel of map i claims, in each later map, the candidate that passes the test;
+// passed: which of the next 32 maps it found one in
+__global__ __launch_bounds__(kBlock) void fuse_claim_kernel(const FuseMap* __restrict__ maps, int n_maps, int i,
+                                                            const FusePair* __restrict__ row, double tau,
+                                                            uint64_t* __restrict__ claim,
+                                                            uint32_t* __restrict__ passed) {
+  const FuseMap& mi = maps[i];
+  const int x = blockIdx.x * kBlock + threadIdx.x, y = blockIdx.y;
+  if (x >= mi.W) return;
+  const int64_t p = (int64_t)y * mi.W + x, g = mi.off + p;
+  const float df = mi.depth[p];
+  if (!(df > 0.0f) || claim[g] != kFree) return;
+  const double d = df, px = (double)x, py = (double)y;
+  const double lim = tau * d, lim2 = lim * lim;
+  uint32_t bits = 0;
+  // kGroup maps at a time, so that their gathers are in flight together and no gather waits
+  // for an atomic of the map before
+  for (int j0 = i + 1; j0 < n_maps; j0 += kGroup) {
+    int found[kGroup];
+    int64_t at[kGroup];
+    int qx[kGroup], qy[kGroup];
+    float dq[kGroup];
+    uint64_t cl[kGroup];
+#pragma unroll
+    for (int k = 0; k < kGroup; ++k) {
+      found[k] = 0;
+      dq[k] = 0.0f;
+      cl[k] = 0;
+      at[k] = 0;
+      if (j0 + k >= n_maps) continue;
+      const FuseMap& mj = maps[j0 + k];
+      const FusePair& P = row[j0 + k];
+      found[k] = project_short(mj, P, px, py, d, __builtin_fma(P.c1, d, P.c0), qx[k], qy[k]);
+      if (found[k] < 0) {
+        double Xi[3];
+        back_project(mi, x, y, d, Xi);
+        found[k] = project_round(mj, Xi, qx[k], qy[k]) ? 2 : 0;
+      }
+      if (found[k]) {
+        const int q = qy[k] * mj.W + qx[k];
+        dq[k] = mj.depth[q];
+        at[k] = mj.off + q;
+        // a claim only ever gets smaller, so one below this pixel's key already has the
+        // candidate (an ordinary load, which may show an older value)
+        cl[k] = claim[at[k]];
+      }
+    }
+    bool pass[kGroup];
+#pragma unroll
+    for (int k = 0; k < kGroup; ++k) {
+      pass[k] = false;
+      if (!found[k] || !(dq[k] > 0.0f) || cl[k] < (uint64_t)g) continue;
+      const FuseMap& mj = maps[j0 + k];
+      const FusePair& P = row[j0 + k];
+      if (found[k] == 1) {
+        // the candidate's point in camera j
+        const double dd = dq[k], qxd = (double)qx[k], qyd = (double)qy[k];
+        double e2 = 0.0, mag = 0.0;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+          const double X =
+              __builtin_fma(d, __builtin_fma(P.A[3 * r], px, __builtin_fma(P.A[3 * r + 1], py, P.A[3 * r + 2])), P.t[r]);
+          const double Y =
+              dd * __builtin_fma(mj.Kinv[3 * r], qxd, __builtin_fma(mj.Kinv[3 * r + 1], qyd, mj.Kinv[3 * r + 2]));
+          const double e = Y - X;
+          mag += fabs(Y);
+          e2 = __builtin_fma(e, e, e2);
+        }
+        // both points through both forms; |e| is near lim where it matters, or below 21 dl
+        const double dl = 2.0 * __builtin_fma(P.c1, d, P.c0) + 512.0 * 0x1p-53 * mag;
+        const double m = 64.0 * dl * lim + 0x1p-40 * lim2 + 512.0 * dl * dl;
+        pass[k] = e2 < lim2;
+        if (!(fabs(e2 - lim2) > m)) found[k] = 2;
+      }
+      if (found[k] == 2) {
+        double Xi[3], Yw[3];
+        back_project(mi, x, y, d, Xi);
+        back_project(mj, qx[k], qy[k], (double)dq[k], Yw);
+        const double e0 = Yw[0] - Xi[0], e1 = Yw[1] - Xi[1], ez = Yw[2] - Xi[2];
+        pass[k] = e0 * e0 + e1 * e1 + ez * ez < lim * lim;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kGroup; ++k) {
+      if (!pass[k]) continue;
+      atomicMin((unsigned long long*)&claim[at[k]], (unsigned long long)g);
+      if (j0 + k - i <= 32) bits |= 1u << (j0 + k - i - 1);
+    }
+  }
+  passed[g] = bits;
+}
+
+// every pixel of maps [i0, i0 + gridDim.z) that nobody claimed becomes a point with the
+// candidates it won
+__global__ __launch_bounds__(kBlock) void fuse_merge_kernel(const FuseMap* __restrict__ maps, int n_maps, int i0,
+                                                            const FusePair* __restrict__ pairs,
+                                                            const uint64_t* __restrict__ claim,
+                                                            const uint32_t* __restrict__ passed,
                                                             float* __restrict__ points, int32_t* __restrict__ support,
                                                             int64_t* __restrict__ owner) {
+  const int i = i0 + blockIdx.z;
   const FuseMap& mi = maps[i];
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  const int64_t g = mi.off + p;
-  // a pixel of map i is only read and written by its own thread here
-  if (p >= mi.W * mi.H || !alive[g]) return;
-  const int y = p / mi.W, x = p - y * mi.W;
-  const double d = mi.depth[p];
-  double Xi[3];
-  back_project(mi, x, y, d, Xi);
-  double sum[3] = {Xi[0], Xi[1], Xi[2]};
-  int count = 1;
-  for (int j = i + 1; j < n_maps; ++j) {
-    const FuseMap& mj = maps[j];
-    int qx, qy;
-    if (!project_round(mj, Xi, qx, qy)) continue;
-    const int64_t q = (int64_t)qy * mj.W + qx;
-    // a claim by p means q was live and passed the test in the claim launch
-    if (claim[mj.off + q] != p) continue;
-    double Yw[3];
-    back_project(mj, qx, qy, (double)mj.depth[q], Yw);
-    alive[mj.off + q] = 0;
-    owner[mj.off + q] = g;
-    for (int k = 0; k < 3; ++k) sum[k] = sum[k] + Yw[k];
-    ++count;
+  const int x = blockIdx.x * kBlock + threadIdx.x, y = blockIdx.y;
+  if (x >= mi.W || y >= mi.H) return;
+  const int64_t p = (int64_t)y * mi.W + x, g = mi.off + p;
+  const float df = mi.depth[p];
+  const uint64_t c = claim[g];
+  float o[3] = {0.0f, 0.0f, 0.0f};
+  int count = 0;
+  int64_t own = df > 0.0f ? (int64_t)c : -1;
+  if (df > 0.0f && c == kFree) {
+    own = g;
+    const double d = df;
+    double Xi[3];
+    back_project(mi, x, y, d, Xi);
+    double sum[3] = {Xi[0], Xi[1], Xi[2]};
+    count = 1;
+    const uint32_t bits = i + 1 < n_maps ? passed[g] : 0u;
+    // as above, the gathers of kGroup maps in flight together
+    for (int j0 = i + 1; j0 < n_maps; j0 += kGroup) {
+      int qx[kGroup], qy[kGroup];
+      uint64_t cl[kGroup];
+      float dq[kGroup];
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        cl[k] = kFree;
+        dq[k] = 0.0f;
+        const int j = j0 + k;
+        if (j >= n_maps || (j - i <= 32 && !(bits >> (j - i - 1) & 1u))) continue;
+        const FuseMap& mj = maps[j];
+        const FusePair& P = pairs[(int64_t)(i - i0) * n_maps + j];
+        int found = project_short(mj, P, (double)x, (double)y, d, __builtin_fma(P.c1, d, P.c0), qx[k], qy[k]);
+        if (found < 0) found = project_round(mj, Xi, qx[k], qy[k]) ? 1 : 0;
+        if (!found) continue;
+        const int q = qy[k] * mj.W + qx[k];
+        cl[k] = claim[mj.off + q];
+        dq[k] = mj.depth[q];
+      }
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        // a claim by this pixel means q was live and passed the test
+        if (cl[k] != (uint64_t)g) continue;
+        double Yw[3];
+        back_project(maps[j0 + k], qx[k], qy[k], (double)dq[k], Yw);
+        for (int r = 0; r < 3; ++r) sum[r] = sum[r] + Yw[r];
+        ++count;
+      }
+    }
+    const double n = (double)count, rn = 1.0 / n;
+    for (int k = 0; k < 3; ++k) o[k] = (float)div_by(sum[k], n, rn);
   }
-  alive[g] = 0;
-  owner[g] = g;
+  owner[g] = own;
   support[g] = count;
-  for (int k = 0; k < 3; ++k) points[3 * g + k] = (float)(sum[k] / (double)count);
+  for (int k = 0; k < 3; ++k) points[3 * g + k] = o[k];
 }
 
 }  // namespace pmu
 
 namespace phimvs_internal {
 
-hipError_t launch_fuse(const FuseMap* h_maps, const FuseMap* d_maps, int n_maps, double tau, uint8_t* alive,
-                       int32_t* claim, float* points, int32_t* support, int64_t* owner, hipStream_t st) {
+// rows of the pair table held at a time
+static int fuse_rows(int n_maps) { return std::min(n_maps, std::max(1, 65536 / n_maps)); }
+
+size_t fuse_pairs(int n_maps) { return (size_t)fuse_rows(n_maps) * n_maps; }
+
+hipError_t launch_fuse(const FuseMap* h_maps, const FuseMap* d_maps, int n_maps, double tau, FusePair* pairs,
+                       uint64_t* claim, uint32_t* passed, float* points, int32_t* support, int64_t* owner,
+                       hipStream_t st) {
+  using pmu::kBlock;
   const int64_t total = h_maps[n_maps - 1].off + (int64_t)h_maps[n_maps - 1].W * h_maps[n_maps - 1].H;
-  for (int v = 0; v < n_maps; ++v) {
-    const int64_t n = (int64_t)h_maps[v].W * h_maps[v].H;
-    hipLaunchKernelGGL(pmu::fuse_init_kernel, dim3((unsigned)((n + pmu::kBlock - 1) / pmu::kBlock)),
-                       dim3(pmu::kBlock), 0, st, h_maps[v], alive, points, support, owner);
-  }
-  for (int i = 0; i < n_maps; ++i) {
-    const int64_t n = (int64_t)h_maps[i].W * h_maps[i].H;
-    const unsigned blocks = (unsigned)((n + pmu::kBlock - 1) / pmu::kBlock);
-    if (i + 1 < n_maps) {
-      const int64_t rest = total - h_maps[i + 1].off;
-      hipLaunchKernelGGL(pmu::fuse_fill_kernel, dim3((unsigned)((rest + pmu::kBlock - 1) / pmu::kBlock)),
-                         dim3(pmu::kBlock), 0, st, claim + h_maps[i + 1].off, rest, INT32_MAX);
-      hipLaunchKernelGGL(pmu::fuse_claim_kernel, dim3(blocks), dim3(pmu::kBlock), 0, st, d_maps, n_maps, i, tau,
-                         (const uint8_t*)alive, claim);
+  const int rows = fuse_rows(n_maps);
+  const int64_t init = std::max<int64_t>((total + 1) / 2, (int64_t)rows * n_maps);
+  hipLaunchKernelGGL(pmu::fuse_init_kernel, dim3((unsigned)((init + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, d_maps,
+                     n_maps, rows, pairs, claim, total);
+  for (int i0 = 0; i0 < n_maps; i0 += rows) {
+    const int nr = std::min(rows, n_maps - i0);
+    if (i0 > 0)
+      hipLaunchKernelGGL(pmu::fuse_pairs_kernel, dim3((unsigned)((nr * n_maps + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                         st, d_maps, n_maps, i0, nr, pairs);
+    int wmax = 1, hmax = 1;
+    for (int i = i0; i < i0 + nr; ++i) {
+      wmax = std::max(wmax, h_maps[i].W);
+      hmax = std::max(hmax, h_maps[i].H);
+      if (i + 1 < n_maps)
+        hipLaunchKernelGGL(pmu::fuse_claim_kernel, dim3((unsigned)((h_maps[i].W + kBlock - 1) / kBlock), h_maps[i].H),
+                           dim3(kBlock), 0, st, d_maps, n_maps, i, pairs + (size_t)(i - i0) * n_maps, tau, claim, passed);
     }
-    hipLaunchKernelGGL(pmu::fuse_merge_kernel, dim3(blocks), dim3(pmu::kBlock), 0, st, d_maps, n_maps, i, alive,
-                       (const int32_t*)claim, points, support, owner);
+    hipLaunchKernelGGL(pmu::fuse_merge_kernel, dim3((unsigned)((wmax + kBlock - 1) / kBlock), hmax, nr), dim3(kBlock), 0,
+                       st, d_maps, n_maps, i0, pairs, claim, passed, points, support, owner);
   }
   return hipGetLastError();
 }

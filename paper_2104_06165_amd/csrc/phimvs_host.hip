@@ -86,10 +86,9 @@ struct phimvs_ctx {
   DevBuf<float> io_a, io_b, io_c, io_d;  // staging for host inputs / outputs
   DevBuf<FilterNbr> filter_nbrs;          // neighbour table of the consistency filter
   std::vector<FilterNbr> filter_host;
-  DevBuf<FuseMap> fuse_maps;              // fusion: map table, live flags and claims
+  DevBuf<FuseMap> fuse_maps;              // fusion: map table
   std::vector<FuseMap> fuse_host;
-  DevBuf<uint8_t> fuse_alive;
-  DevBuf<int32_t> fuse_claim;
+  DevBuf<uint64_t> fuse_scratch;          // fusion: claims, pair table, tests passed
   DevBuf<uint64_t> phi_bits;              // per-direction occupancy bitmaps of the hypothesis fits
   DevBuf<uint8_t> io_u8;
   // diagnostics
@@ -840,8 +839,7 @@ void phimvs_destroy(phimvs_ctx* c) {
   release(c->io_d);
   release(c->filter_nbrs);
   release(c->fuse_maps);
-  release(c->fuse_alive);
-  release(c->fuse_claim);
+  release(c->fuse_scratch);
   release(c->phi_bits);
   release(c->io_u8);
   if (c->diag_count) (void)hipFree(c->diag_count);
@@ -1227,12 +1225,17 @@ int phimvs_fuse(phimvs_ctx* c, int n_maps, const phimvs_depth_map* maps, const p
   }
   int rc;
   if ((rc = ensure(c, c->fuse_maps, (size_t)n_maps))) return rc;
-  if ((rc = ensure(c, c->fuse_alive, (size_t)total))) return rc;
-  if ((rc = ensure(c, c->fuse_claim, (size_t)total))) return rc;
+  static_assert(sizeof(FusePair) % sizeof(uint64_t) == 0, "the pair table lies between 64-bit words");
+  const size_t pair_words = fuse_pairs(n_maps) * (sizeof(FusePair) / sizeof(uint64_t));
+  const size_t claim_words = ((size_t)total + 1) / 2 * 2;  // written 16 bytes at a time
+  if ((rc = ensure(c, c->fuse_scratch, claim_words + pair_words + ((size_t)total + 1) / 2))) return rc;
+  uint64_t* claim = c->fuse_scratch.p;
+  FusePair* pairs = reinterpret_cast<FusePair*>(claim + claim_words);
+  uint32_t* passed = reinterpret_cast<uint32_t*>(claim + claim_words + pair_words);
   HIPCHECK(c, hipMemcpyAsync(c->fuse_maps.p, c->fuse_host.data(), n_maps * sizeof(FuseMap), hipMemcpyHostToDevice,
                              c->stream));
-  HIPCHECK(c, launch_fuse(c->fuse_host.data(), c->fuse_maps.p, n_maps, p.max_rel_dist, c->fuse_alive.p,
-                          c->fuse_claim.p, points, support, owner, c->stream));
+  HIPCHECK(c, launch_fuse(c->fuse_host.data(), c->fuse_maps.p, n_maps, p.max_rel_dist, pairs, claim, passed,
+                          points, support, owner, c->stream));
   return PHIMVS_OK;
 }
 

@@ -154,10 +154,18 @@ struct FuseMap {
   int64_t off;
   const float* depth;
 };
-// the whole fusion of n_maps maps (h_maps on the host, d_maps its device copy); alive and
-// claim: scratch over the concatenated pixels
-hipError_t launch_fuse(const FuseMap* h_maps, const FuseMap* d_maps, int n_maps, double tau, uint8_t* alive,
-                       int32_t* claim, float* points, int32_t* support, int64_t* owner, hipStream_t st);
+// a pair of maps (i, j > i): pixel of i -> point in camera j (A, t) and image j (P, s), and
+// rounding bounds
+struct FusePair {
+  double A[9], t[3], P[9], s[3];
+  double c0, c1, kw, cu, cv, eu, ev;
+};
+size_t fuse_pairs(int n_maps);  // entries of the pair table
+// the whole fusion of n_maps maps (h_maps on the host, d_maps its device copy); claim, passed:
+// scratch over the concatenated pixels
+hipError_t launch_fuse(const FuseMap* h_maps, const FuseMap* d_maps, int n_maps, double tau, FusePair* pairs,
+                       uint64_t* claim, uint32_t* passed, float* points, int32_t* support, int64_t* owner,
+                       hipStream_t st);
 
 // plane hypothesis inference
 struct PhiCam {

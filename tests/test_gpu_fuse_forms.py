@@ -1,0 +1,103 @@
+"""Fusion decides its tests by a shorter arithmetic wherever that is certain, and by the
+written-out one at rounding boundaries and at the distance limit.  Maps built to sit on
+those boundaries (identical cameras, whole-pixel shifts, half-pixel shifts, distances equal
+to the limit, scenes far from the world's origin) and maps in numbers beyond one group and
+beyond the recorded tests of a pixel, against the sequential oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2104_06165_amd as pm  # noqa: E402
+
+
+def run(K, R, t, depths, tau):
+    ctx = pm.Context(0)
+    try:
+        ims = [np.zeros(d.shape, np.uint8) for d in depths]
+        ims = ims if len(ims) > 1 else ims * 2
+        n = len(ims)
+        k3 = [np.resize(np.asarray(a, np.float64), (len(depths),) + s) for a, s in ((K, (3, 3)), (R, (3, 3)), (t, (3,)))]
+        args = [np.concatenate([a, a[:n - len(depths)]]) for a in k3]
+        ctx.set_views(ims, *args, np.tile([0.5, 50.0], (n, 1)))
+        maps = [(i, torch.from_numpy(d).cuda()) for i, d in enumerate(depths)]
+        got = [x.cpu().numpy() for x in ctx.fuse(maps, tau)]
+    finally:
+        ctx.close()
+    ref = oracle.fuse(depths, *k3, tau)
+    for g, r in zip(got, ref):
+        assert np.array_equal(g, r.reshape(g.shape))
+
+
+def cams(n, f, c, R=None, t=None):
+    K = np.array([[f, 0, c[0]], [0, f, c[1]], [0, 0, 1.0]])
+    return (np.tile(K, (n, 1, 1)), np.tile(np.eye(3) if R is None else R, (n, 1, 1)),
+            np.zeros((n, 3)) if t is None else np.asarray(t, np.float64))
+
+
+def rot(rng):
+    q = np.linalg.qr(rng.standard_normal((3, 3)))[0]
+    return q * np.sign(np.linalg.det(q))
+
+
+def noisy(rng, H, W, base=4.0, spread=0.02, empty=0.1):
+    d = (base * (1 + spread * rng.standard_normal((H, W)))).astype(np.float32)
+    d[rng.random((H, W)) < empty] = 0.0
+    return d
+
+
+@pytest.mark.parametrize("shift", [0.0, 0.5, 1.0, 2.5])
+def test_positions_on_rounding_boundaries(shift):
+    # a shift of s pixels at depth 4 with f = 64: every position lands on a whole or half pixel
+    rng = np.random.default_rng(int(10 * shift))
+    K, R, t = cams(3, 64.0, (20.0, 11.0), t=[[0, 0, 0], [shift * 4 / 64, 0, 0], [0, shift * 4 / 64, 0]])
+    flat = [np.full((23, 41), 4.0, np.float32) for _ in range(3)]
+    run(K, R, t, flat, 0.01)
+    run(K, R, t, [noisy(rng, 23, 41, spread=0.004) for _ in range(3)], 0.01)
+
+
+def test_distance_on_the_limit():
+    # identical cameras, depth ratios of exactly 1 + tau and around it, on the optical axis
+    K, R, t = cams(4, 64.0, (0.0, 0.0))
+    d = [np.full((1, 64), v, np.float32) for v in (4.0, 4.0 * 1.015625, np.nextafter(np.float32(4.0625), np.float32(0)),
+                                                    np.nextafter(np.float32(4.0625), np.float32(9)))]
+    run(K, R, t, d, 0.015625)
+    run(K, R, t, d, 0.0)
+
+
+@pytest.mark.parametrize("far", [0.0, 1e3, 1e7])
+def test_scenes_away_from_the_origin(far):
+    rng = np.random.default_rng(3)
+    Q, q = rot(rng), far * rng.standard_normal(3)
+    K, R, t = cams(5, 90.0, (31.0, 17.5))
+    for i in range(5):
+        a = 0.05 * (i - 2)
+        Ri = np.array([[np.cos(a), 0, -np.sin(a)], [0, 1, 0], [np.sin(a), 0, np.cos(a)]])
+        ti = np.array([0.1 * (i - 2), 0.02 * i, 0.0])
+        R[i], t[i] = Ri @ Q.T, ti - Ri @ (Q.T @ q)
+    run(K, R, t, [noisy(rng, 36, 63) for _ in range(5)], 0.01)
+
+
+@pytest.mark.parametrize("n", [1, 2, 5, 6, 40])
+def test_numbers_of_maps(n):
+    rng = np.random.default_rng(n)
+    K, R, t = cams(n, 50.0, (15.0, 8.0), t=0.004 * rng.standard_normal((n, 3)))
+    run(K, R, t, [noisy(rng, 17, 31, empty=0.3) for _ in range(n)], 0.03)
+
+
+def test_depths_that_are_no_numbers():
+    rng = np.random.default_rng(9)
+    K, R, t = cams(3, 50.0, (15.0, 8.0), t=0.01 * rng.standard_normal((3, 3)))
+    d = [noisy(rng, 17, 31) for _ in range(3)]
+    for m in d:
+        m[rng.random(m.shape) < 0.05] = -1.0
+        m[rng.random(m.shape) < 0.05] = np.nan
+        m[rng.random(m.shape) < 0.02] = 1e-30
+        m[rng.random(m.shape) < 0.02] = 1e30
+    run(K, R, t, d, 0.01)
