@@ -84,8 +84,6 @@ struct phimvs_ctx {
   bool order_auto = true;                 // work-list order by each job's cameras until the caller sets a tuning
   size_t eval_lds_max = 0;                // largest dynamic LDS of an evaluate launch on this device
   DevBuf<float> io_a, io_b, io_c, io_d;  // staging for host inputs / outputs
-  DevBuf<FilterNbr> filter_nbrs;          // neighbour table of the consistency filter
-  std::vector<FilterNbr> filter_host;
   DevBuf<FuseMap> fuse_maps;              // fusion: map table
   std::vector<FuseMap> fuse_host;
   DevBuf<uint64_t> fuse_scratch;          // fusion: claims, pair table, tests passed
@@ -204,6 +202,61 @@ bool inv33(const double* A, double* I) {
   I[7] = (A[1] * A[6] - A[0] * A[7]) * r;
   I[8] = (A[0] * A[4] - A[1] * A[3]) * r;
   return true;
+}
+
+// the short form of the consistency test against a neighbour (its camera is filled in) and its
+// bounds (phimvs_internal.h)
+void filter_short_form(FilterNbr& nb, const ViewData& V0, const double* K0inv, double tau_r) {
+  double R0t[9], Rjt[9], R[9], N[9], A[9], B[9], Rt0[3], Rtj[3], t[3], back[3];
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j) {
+      R0t[3 * i + j] = V0.R[3 * j + i];
+      Rjt[3 * i + j] = nb.R[3 * j + i];
+    }
+  mul33(nb.R, R0t, R);
+  mul33(V0.R, Rjt, N);
+  mul33(R, K0inv, A);
+  mul33(nb.K, A, nb.P);
+  mulv3(R, V0.t, Rt0);
+  mulv3(N, nb.t, Rtj);
+  for (int i = 0; i < 3; ++i) {
+    t[i] = nb.t[i] - Rt0[i];
+    back[i] = V0.t[i] - Rtj[i];
+    nb.zr[i] = A[6 + i];
+  }
+  nb.zr[3] = t[2];
+  mulv3(nb.K, t, nb.s);
+  mul33(N, nb.Kinv, B);
+  mul33(V0.K, B, nb.Q);
+  mulv3(V0.K, back, nb.w);
+  for (int i = 0; i < 9; ++i) nb.N[i] = (float)N[i];
+  double t1 = 0.0, ray0 = 0.0, rayj = 0.0, step = 0.0, kn[3], k0[3];
+  for (int r = 0; r < 3; ++r) {
+    t1 += std::fabs(V0.t[r]) + std::fabs(nb.t[r]);
+    ray0 += std::fabs(K0inv[3 * r]) * V0.W + std::fabs(K0inv[3 * r + 1]) * V0.H + std::fabs(K0inv[3 * r + 2]);
+    rayj += std::fabs(nb.Kinv[3 * r]) * nb.W + std::fabs(nb.Kinv[3 * r + 1]) * nb.H + std::fabs(nb.Kinv[3 * r + 2]);
+    kn[r] = std::fabs(nb.K[3 * r]) + std::fabs(nb.K[3 * r + 1]) + std::fabs(nb.K[3 * r + 2]);
+    k0[r] = std::fabs(V0.K[3 * r]) + std::fabs(V0.K[3 * r + 1]) + std::fabs(V0.K[3 * r + 2]);
+    step += std::fabs(nb.Kinv[3 * r]) + std::fabs(nb.Kinv[3 * r + 1]);
+  }
+  const double u = 512.0 * 0x1p-53;
+  nb.c0 = nb.b0 = u * t1;
+  nb.c1 = u * ray0;
+  nb.kw = 4.0 * kn[2];
+  nb.cuv = 4.0 * (std::max(kn[0], kn[1]) + (std::max(nb.W, nb.H) + 1) * kn[2]);
+  // as little as lets the nearest depths be decided (more leaves more positions open: about
+  // 8 m of them), with the quotient's rounding on top
+  const double quotient = 0x1p-38 * (std::max(nb.W, nb.H) + 2);
+  nb.m = std::min(1e-3, std::max(1e-10, 4.0 * (nb.c0 / V0.d_lo + nb.c1) * nb.cuv));
+  const double m = nb.m + quotient;
+  nb.half = 0.5 - 2.0 * m;
+  nb.m2 = 2.0 * m;
+  nb.cb = u * rayj + m * step;
+  nb.b2 = rayj;
+  const double far = std::max(V0.W, V0.H) + 2.0 * tau_r + 2.0;
+  nb.qw = 4.0 * k0[2];
+  nb.qu = 4.0 * (std::max(k0[0], k0[1]) + far * k0[2]);
+  nb.qe = 0x1p-38 * far;
 }
 
 bool orthonormal(const double* R) {
@@ -837,7 +890,6 @@ void phimvs_destroy(phimvs_ctx* c) {
   release(c->io_b);
   release(c->io_c);
   release(c->io_d);
-  release(c->filter_nbrs);
   release(c->fuse_maps);
   release(c->fuse_scratch);
   release(c->phi_bits);
@@ -1158,15 +1210,12 @@ int phimvs_filter(phimvs_ctx* c, int n_maps, const phimvs_depth_map* maps, int r
   a.depth_out = depth_out;
   a.normal_out = normal_out;
   a.count_out = count_out;
-  // the previous call's table may still be in use by its launch
-  HIPCHECK(c, hipStreamSynchronize(c->stream));
-  c->filter_host.assign(std::max(n_nbrs, 1), FilterNbr{});
   for (int k = 0; k < n_nbrs; ++k) {
     if (nbrs[k] < 0 || nbrs[k] >= n_maps || nbrs[k] == ref_map || !view_ok(maps[nbrs[k]]))
       return fail(c, PHIMVS_E_ARG, "neighbour " + std::to_string(k) + ": invalid map index, view or arrays");
     const phimvs_depth_map& M = maps[nbrs[k]];
     const ViewData& V = c->views[M.view];
-    FilterNbr& nb = c->filter_host[k];
+    FilterNbr& nb = a.nbrs[k];
     for (int i = 0; i < 9; ++i) nb.K[i] = V.K[i], nb.R[i] = V.R[i];
     for (int i = 0; i < 3; ++i) nb.t[i] = V.t[i];
     if (!inv33(V.K, nb.Kinv)) return fail(c, PHIMVS_E_ARG, "singular K");
@@ -1174,13 +1223,9 @@ int phimvs_filter(phimvs_ctx* c, int n_maps, const phimvs_depth_map* maps, int r
     nb.H = V.H;
     nb.depth = M.depth;
     nb.normal = M.normal;
+    filter_short_form(nb, V0, a.Kinv, p.max_reproj_px);
   }
-  int rc;
-  if ((rc = ensure(c, c->filter_nbrs, c->filter_host.size()))) return rc;
-  HIPCHECK(c, hipMemcpyAsync(c->filter_nbrs.p, c->filter_host.data(), c->filter_host.size() * sizeof(FilterNbr),
-                             hipMemcpyHostToDevice, c->stream));
   a.n_nbrs = n_nbrs;
-  a.nbrs = c->filter_nbrs.p;
   HIPCHECK(c, launch_filter(a, c->stream));
   return PHIMVS_OK;
 }

@@ -131,6 +131,20 @@ struct FilterNbr {
   int W, H;
   const float* depth;
   const float* normal;
+  // The short form, R = R_j R_0^T: pixel (x, y) of the reference at depth d is d P (x, y, 1) + s
+  // on image j at depth d zr (x, y, 1) + zr[3]; n_0 . N n_j compares normals (N = R^T); position
+  // (u, v) of image j at depth d' is d' Q (u, v, 1) + w on the reference image.
+  double P[9], s[3], zr[4], Q[9], w[3];
+  float N[9];
+  // Bounds of its difference from the written-out form.  A point differs by c0 + c1 d (b0 + b1 d'
+  // on the way back) in any coordinate: 512 x 2^-53 of the magnitudes that enter, both forms
+  // being a few 3-term products of them.  Counted four times over, an image position inside
+  // the image or within a pixel of it differs by that over p_z times cuv (qu: within twice the
+  // re-projection threshold, and qe for the quotient), and p_z by kw (qw) times it.  m is what
+  // the test grants a position (positions that may differ by more are left open), half = 1/2 -
+  // 2 m and m2 = 2 m with the quotient's rounding; cb carries m, b2 the bilinear depth's
+  // difference into the point on the way back.
+  double c0, c1, kw, cuv, m, half, m2, b0, cb, b2, qw, qu, qe;
 };
 struct FilterArgs {
   int W, H;
@@ -138,12 +152,12 @@ struct FilterArgs {
   const float* depth;
   const float* normal;
   int n_nbrs;
-  const FilterNbr* nbrs;  // device array of n_nbrs
   double tau_d, cos_n, tau_r;
   int min_consistent;
   float* depth_out;
   float* normal_out;
   uint8_t* count_out;
+  FilterNbr nbrs[PHIMVS_MAX_SOURCES];  // with the launch: no table to copy, none to wait for
 };
 hipError_t launch_filter(const FilterArgs& a, hipStream_t st);
 
