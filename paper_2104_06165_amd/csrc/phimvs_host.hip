@@ -44,6 +44,7 @@ struct JobState {
   DevBuf<float> cost[2];
   DevBuf<float4> cand;
   DevBuf<float4> hist;           // 2 colours x 8 candidates per pixel
+  DevBuf<float> ref_sums;        // 2 colours x 3 planes
   DevBuf<float> wcol, wsp;
 };
 
@@ -56,6 +57,8 @@ struct Batch {
   int total_tiles = 0, total_cblk = 0, max_r = 0, max_taps = 0, tile_rows = 4;
   int xcd_len[8] = {};
   std::string layout_key;        // problems + tile shape the state was built for
+  bool ref_valid[2] = {false, false};   // ref_sums hold colour c's sums (an initialisation of the library's
+                                        // has run on this problem)
   bool state_exact = false;      // every stored cost is the cost of its stored plane (the library's
                                  // own initialisation and steps keep this; phimvs_set_state does not)
   bool hist_valid[2] = {false, false};  // hist[c] holds the last propagation launch of colour c since the
@@ -145,6 +148,7 @@ void release_state(JobState& s) {
   }
   release(s.cand);
   release(s.hist);
+  release(s.ref_sums);
   release(s.wcol);
   release(s.wsp);
 }
@@ -461,7 +465,10 @@ int setup_job(phimvs_ctx* c, const Problem& P, Job& J, JobState& S) {
     A.plane[k] = S.plane[k].p;
     A.cost[k] = S.cost[k].p;
   }
-  if ((rc = ensure(c, S.cand, 8 * ncol)) || (rc = ensure(c, S.hist, 16 * ncol))) return rc;
+  if ((rc = ensure(c, S.cand, 8 * ncol)) || (rc = ensure(c, S.hist, 16 * ncol)) || (rc = ensure(c, S.ref_sums, 6 * ncol)))
+    return rc;
+  A.ref_sums[0] = S.ref_sums.p;
+  A.ref_sums[1] = S.ref_sums.p + 3 * ncol;
   J.cand = S.cand.p;
   J.hist[0] = S.hist.p;
   J.hist[1] = S.hist.p + 8 * ncol;
@@ -563,7 +570,10 @@ int run_eval(phimvs_ctx* c, Batch& b, Launch L, unsigned int* queue) {
   if (c->diag & PHIMVS_DIAG_COUNT) L.count = c->diag_count;
   const bool split = b.jobs.size() == 1 && b.jobs[0].A.lanes > 1;
   const Args& A0 = b.jobs[0].A;
-  const size_t lds = split ? eval_lanes_lds_bytes(A0.lanes, A0.halo, A0.n_taps)
+  LanesPlan plan{};
+  if (split) plan = lanes_plan(A0.lanes, A0.H, A0.Wc, L.mode == 2 ? 1 : L.ncand, c->n_cu);
+  L.lanes_px = plan.px;
+  const size_t lds = split ? eval_lanes_lds_bytes(plan.px, A0.halo, A0.n_taps)
                            : eval_lds_bytes(b.tile_rows, b.max_r, b.max_taps);
   if (lds > c->eval_lds_max)
     return fail(c, PHIMVS_E_UNSUPPORTED, "evaluate launch: " + std::to_string(b.tile_rows) + "-row tiles need " +
@@ -578,7 +588,7 @@ int run_eval(phimvs_ctx* c, Batch& b, Launch L, unsigned int* queue) {
     c->diag_events.emplace_back(e0, e1);
     HIPCHECK(c, hipEventRecord(e0, c->stream));
   }
-  const hipError_t e = split ? launch_eval_lanes(b.d_jobs, L, A0.lanes, A0.H, A0.Wc, lds, c->stream)
+  const hipError_t e = split ? launch_eval_lanes(b.d_jobs, L, A0.lanes, plan.pl, A0.H, A0.Wc, lds, c->stream)
                               : launch_eval(b.d_jobs, L, grid, lds, c->stream);
   if (e != hipSuccess)
     return fail(c, PHIMVS_E_DEVICE, "evaluate launch (" + std::to_string(grid) + " workgroups, " +
@@ -603,11 +613,14 @@ int issue_sequence(phimvs_ctx* c, Batch& b, int iters, bool do_unpack, bool with
     L.colour = colour;
     L.mode = 0;
     L.ncand = with_proposal ? 2 : 1;
+    L.ref_mode = 1;
     HIPCHECK(c, launch_candidates(0, b.d_jobs, L, c->stream));
     if ((rc = run_eval(c, b, L, b.queues.p + 8 * q++))) return rc;
+    b.ref_valid[colour] = true;
   }
   b.state_exact = true;
   L.skip_current = 1;
+  L.ref_mode = 2;
   for (int it = 1; it <= iters; ++it)
     for (int colour = 0; colour < 2; ++colour) {
       L.colour = colour;
@@ -683,6 +696,7 @@ int prepare_single(phimvs_ctx* c, int ref, const int* srcs, int n_srcs, int wind
   if (key != b.layout_key || b.jobs.size() != 1) {
     release_graph(b);
     resize_jobs(b, 1);
+    b.ref_valid[0] = b.ref_valid[1] = false;
     if ((rc = setup_job(c, P, b.jobs[0], b.state[0]))) return rc;
     layout(b, c->tuning.tile_rows);
     b.layout_key = key;
@@ -701,6 +715,7 @@ int prepare_single(phimvs_ctx* c, int ref, const int* srcs, int n_srcs, int wind
 
 // after the sequence has been issued (or its graph launched): what it leaves in the state
 void sequence_done(Batch& b, int iters) {
+  b.ref_valid[0] = b.ref_valid[1] = true;
   b.state_exact = true;
   b.hist_valid[0] = b.hist_valid[1] = iters >= 1;
 }
@@ -728,6 +743,7 @@ int run_sequence_graph(phimvs_ctx* c, Batch& b, const std::string& gkey, int ite
     return fail(c, PHIMVS_E_DEVICE, std::string("hipStreamBeginCapture: ") + hipGetErrorString(eb));
   }
   rc = issue_sequence(c, b, iters, true);
+  b.ref_valid[0] = b.ref_valid[1] = false;  // recorded so far, not run
   hipGraph_t g = nullptr;
   const hipError_t ec = hipStreamEndCapture(c->stream, &g);
   c->stream = user;
@@ -740,6 +756,7 @@ int run_sequence_graph(phimvs_ctx* c, Batch& b, const std::string& gkey, int ite
   HIPCHECK(c, hipGraphInstantiate(&b.exec, b.graph, nullptr, nullptr, 0));
   b.graph_key = gkey;
   HIPCHECK(c, hipGraphLaunch(b.exec, c->stream));
+  sequence_done(b, iters);
   return PHIMVS_OK;
 }
 
@@ -991,10 +1008,12 @@ int phimvs_init_planes(phimvs_ctx* c, const float* proposal, int on_device) {
   Launch L = base_launch(b);
   L.mode = 0;
   L.ncand = prop ? 2 : 1;
+  L.ref_mode = 1;
   for (int colour = 0; colour < 2; ++colour) {
     L.colour = colour;
     HIPCHECK(c, launch_candidates(0, b.d_jobs, L, c->stream));
     if ((rc = eval_once(c, b, L))) return rc;
+    b.ref_valid[colour] = true;
   }
   if (prop) {
     b.jobs[0].planes_in = nullptr;
@@ -1017,6 +1036,7 @@ int phimvs_step(phimvs_ctx* c, int iteration, int colour, int do_propagate, int 
   L.iteration = iteration;
   L.mode = 1;
   L.skip_current = b.state_exact ? 1 : 0;
+  L.ref_mode = b.ref_valid[colour] ? 2 : 0;
   if (do_propagate) {
     L.ncand = 8;
     L.hist_mode = b.hist_valid[colour] ? 2 : 1;

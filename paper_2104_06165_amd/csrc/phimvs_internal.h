@@ -18,6 +18,10 @@ constexpr int kDepthBuckets = 256;  // inverse-depth buckets of the depth-ordere
 static_assert(kDepthBuckets == kBlock, "the bucket scan gives each thread of the workgroup one bucket");
 constexpr int kDepthBucketLds = 15 * kBlock + 8;  // their counters, after the wave totals
 constexpr int kCompactLds = kDepthBucketLds + kDepthBuckets;
+// the split-lane kernel's arrays, in floats: for a workgroup's px pixels S_w, mu_a, var_a, 8
+// costs and 8 16-bit list entries each, and the list's length
+constexpr int kLanesMaxPx = 64;
+constexpr int lanes_lds(int px) { return 15 * px + 4; }
 constexpr int kMaxTopK = PHIMVS_MAX_SOURCES;
 constexpr int kMaxTaps1D = 31;     // taps per window side
 
@@ -55,6 +59,7 @@ struct Args {
   const float* wsp;        // n_taps spatial weights
   float4* plane[2];        // colour planes (n.x, n.y, n.z, d), H*Wc each
   float* cost[2];
+  float* ref_sums[2];      // per colour: planes of S_w, mu_a, var_a, H*Wc each
   SrcDev src[PHIMVS_MAX_SOURCES];
 };
 
@@ -96,6 +101,9 @@ struct Launch {
                                        // plane (only when every stored cost is its plane's own cost)
   int hist_mode;                       // propagation candidates: 0 none; 1 record the candidates offered;
                                        // 2 also drop those the previous launch of the colour offered
+  int lanes_px;                        // split-lane evaluate: pixels per workgroup
+  int ref_mode;                        // evaluate: the pixels' reference sums 0 added up, 1 also stored in
+                                       // ref_sums, 2 loaded from there
   unsigned int* queue;                 // 8 counters, zero at launch (persistent only)
   unsigned long long* count;           // optional: + (pixel, hypothesis) pairs scored
 };
@@ -107,10 +115,16 @@ size_t eval_lds_bytes(int tile_rows, int max_radius_px, int max_taps);
 // capture); *max_dynamic receives the largest dynamic LDS a launch may then ask for
 hipError_t eval_lds_setup(size_t* max_dynamic);
 hipError_t launch_eval(const Job* d_jobs, const Launch& L, int grid, size_t lds, hipStream_t st);
-// single-job evaluate launch with `lanes` (2, 4, 8, 16) lanes per pixel (job 0 of H rows,
-// Wc compacted columns); its LDS need for a reference-tile halo and tap count
-size_t eval_lanes_lds_bytes(int lanes, int radius_px, int n_taps);
-hipError_t launch_eval_lanes(const Job* d_jobs, const Launch& L, int lanes, int H, int Wc, size_t lds,
+// single-job evaluate launch with partial sums split `lanes` (2, 4, 8, 16) ways: the plan of a
+// launch of `ncand` candidates per pixel over H rows of Wc compacted columns (px pixels per
+// workgroup, pl lanes per pair), its LDS need for a reference-tile halo and tap count, and the
+// launch (L.lanes_px = px)
+struct LanesPlan {
+  int px, pl;
+};
+LanesPlan lanes_plan(int lanes, int H, int Wc, int ncand, int n_cu);
+size_t eval_lanes_lds_bytes(int px, int radius_px, int n_taps);
+hipError_t launch_eval_lanes(const Job* d_jobs, const Launch& L, int lanes, int pl, int H, int Wc, size_t lds,
                              hipStream_t st);
 // kind 0: random initialisation (+ proposal), 1: propagation, 2: refinement candidates
 hipError_t launch_candidates(int kind, const Job* d_jobs, const Launch& L, hipStream_t st);

@@ -27,6 +27,8 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "phimvs_internal.h"
 
 namespace pmk {
@@ -199,6 +201,26 @@ __device__ __forceinline__ float colour_weight(const float* __restrict__ wcol, f
   return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(wcol) + (uint32_t)fabsf(a4));
 }
 
+// A pixel's reference sums (S_w, mu_a, var_a) depend on the image and the window alone: the
+// launches of the initialisation store them (three planes per colour) and the later launches
+// of the same sequence load them.  Adding them up again is one lane's chain of LDS reads over
+// the whole window, about 20 us of every split-lane launch at 11 x 11 taps (nothing to overlap
+// it there), 0.3-2% of a full one.
+__device__ __forceinline__ void load_ref_sums(const Args& A, int colour, size_t ncol, size_t i, float& S_w, float& mu,
+                                              float& var) {
+  const GLOBAL float* __restrict__ p = gl(A.ref_sums[colour]);
+  S_w = p[i];
+  mu = p[ncol + i];
+  var = p[2 * ncol + i];
+}
+__device__ __forceinline__ void store_ref_sums(const Args& A, int colour, size_t ncol, size_t i, float S_w, float mu,
+                                               float var) {
+  GLOBAL float* p = gl(A.ref_sums[colour]);
+  p[i] = S_w;
+  p[ncol + i] = mu;
+  p[2 * ncol + i] = var;
+}
+
 // ---------------------------------------------------------------------------- plane helpers
 // viewing ray K^-1 (x, y, 1) in float
 __device__ __forceinline__ void ray_f(const Args& A, int x, int y, float& rx, float& ry, float& rz) {
@@ -350,44 +372,78 @@ __device__ __forceinline__ void tap_pass(const Args& A, int J0, const RefPix& rp
   row(k2, qa, fxa, fya, qb, fxb, fyb);
 }
 
-// The same sums with LANES lanes sharing the pixel: lane g (its position within its aligned
-// group of LANES lanes) sums the taps t = g, g + LANES, ... in order, every tap computed
-// exactly as in tap_pass (the same fma chains; tap_pass only hoists the row's part), and the
-// partial sums are then combined by an xor butterfly: at offset o = LANES/2, ..., 1 every
-// lane adds the partial sum of lane g xor o to its own.  Addition commutes, so all lanes of
-// the group end with the same, bitwise equal, totals.  Lanes of one group always share
-// their pixel and candidate, so a butterfly partner is always active.
-template <int G, bool EXACT, bool CLAMP, int LANES>
+// the value of lane `lane ^ O` (O = 1, 2, 4 or 8; both lanes active) over the data-parallel
+// primitives: within quads, half rows of 8 or rows of 16 lanes
+template <int O>
+__device__ __forceinline__ int xor_lane(int v) {
+  if constexpr (O == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);   // quad 1 0 3 2
+  if constexpr (O == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);   // quad 2 3 0 1
+  if constexpr (O == 4)  // 7 - i of a half row, then 3 - i of a quad
+    return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf, true);
+  return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);                         // row rotated by 8
+}
+template <int O>
+__device__ __forceinline__ float xor_lane(float v) {
+  return __int_as_float(xor_lane<O>(__float_as_int(v)));
+}
+
+// The same sums split LANES ways: partial sum g covers the taps t = g, g + LANES, ... in order,
+// every tap computed exactly as in tap_pass (the same fma chains; tap_pass only hoists the row's
+// part), and the partial sums are combined by an xor butterfly: at offset o = LANES/2, ..., 1
+// every one adds its partner g xor o.  Addition commutes, so all end as the same, bitwise equal,
+// totals.  PL <= LANES lanes share the pair, lane h holding the partial sums h, h + PL, ...
+// (so the larger offsets join sums of one lane, the smaller ones lanes of an aligned group, which
+// always share their pixel and candidate).  A round covers LANES taps: all its texel loads are
+// issued, then, where a lane has but one tap a round, the next round's before this one's are
+// interpolated.  A tap past the last gathers the window's last tap again and is left out.
+template <int O, int G>
+__device__ __forceinline__ void butterfly(float (&Sb)[G], float (&Sbb)[G], float (&Sab)[G]) {
+#pragma unroll
+  for (int v = 0; v < G; ++v) {
+    Sb[v] = Sb[v] + xor_lane<O>(Sb[v]);
+    Sbb[v] = Sbb[v] + xor_lane<O>(Sbb[v]);
+    Sab[v] = Sab[v] + xor_lane<O>(Sab[v]);
+  }
+  if constexpr (O > 1) butterfly<O / 2, G>(Sb, Sbb, Sab);
+}
+template <int G, bool EXACT, bool CLAMP, int LANES, int PL>
 __device__ __forceinline__ void tap_pass_lanes(const Args& A, int J0, const RefPix& rp, const float* __restrict__ tile,
                                                int TW, const float* __restrict__ wcol, const float* __restrict__ wsp,
                                                const float (&Hm)[G][9], const float (&bc)[G], float (&Sb)[G],
                                                float (&Sbb)[G], float (&Sab)[G]) {
+  constexpr int V = LANES / PL;  // partial sums of a lane
   const int R = A.R, s = A.s;
   const int n = 2 * R + 1;
   const int T = n * n;
-  const int g = (int)(threadIdx.x % LANES);
+  const int h = (int)(threadIdx.x % PL);
   uint32_t Wq[G];
   v4i32 rs[G];
   float Wm1[G], Hm1[G];
+  float pb[V][G], pbb[V][G], pab[V][G];
 #pragma unroll
   for (int v = 0; v < G; ++v) {
-    Sb[v] = 0.0f;
-    Sbb[v] = 0.0f;
-    Sab[v] = 0.0f;
+#pragma unroll
+    for (int m = 0; m < V; ++m) pb[m][v] = pbb[m][v] = pab[m][v] = 0.0f;
     Wq[v] = (uint32_t)A.src[J0 + v].W;
     rs[v] = quad_rsrc(A.src[J0 + v].quad, (uint32_t)A.src[J0 + v].W * (uint32_t)A.src[J0 + v].H);
     Wm1[v] = A.src[J0 + v].Wm1;
     Hm1[v] = A.src[J0 + v].Hm1;
   }
-  for (int t = g; t < T; t += LANES) {
-    const int k2 = t / n, k1 = t - k2 * n;
-    const float X = rp.X0 + (float)(s * (k1 - R));
-    const float Y = rp.Y0 + (float)(s * (k2 - R));
-    const float a4 = tile[rp.tbase + (k2 * TW + k1) * s] - rp.a_c;  // 4 (a - a_c)
-    const float w = colour_weight<false>(wcol, a4) * wsp[t];
-    const float wa = w * a4;
+  // a step of PL taps, and the (row, column) of the next tap to issue
+  const int dk2 = PL / n, dk1 = PL - dk2 * n;
+  int k2 = h / n, k1 = h - k2 * n;
+  struct Tap {
     uint32_t q[G];
     float fx[G], fy[G];
+    int t, at;  // tap index (-1: past the last), LDS index of its reference value
+  };
+  auto issue = [&](Tap& o) {
+    const bool past = k2 >= n;
+    const int j1 = past ? n - 1 : k1, j2 = past ? n - 1 : k2;
+    o.t = past ? -1 : j2 * n + j1;
+    o.at = rp.tbase + (j2 * TW + j1) * s;
+    const float X = rp.X0 + (float)(s * (j1 - R));
+    const float Y = rp.Y0 + (float)(s * (j2 - R));
 #pragma unroll
     for (int v = 0; v < G; ++v) {
       const float u = __builtin_fmaf(Hm[v][0], X, __builtin_fmaf(Hm[v][1], Y, Hm[v][2]));
@@ -396,35 +452,82 @@ __device__ __forceinline__ void tap_pass_lanes(const Args& A, int J0, const RefP
       const float r = EXACT ? 1.0f / ww : rcp_nr(ww);
       const float up = CLAMP ? clampf(u * r, Wm1[v]) : u * r;
       const float vp = CLAMP ? clampf(vv * r, Hm1[v]) : vv * r;
-      fx[v] = __builtin_amdgcn_fractf(up);
-      fy[v] = __builtin_amdgcn_fractf(vp);
+      o.fx[v] = __builtin_amdgcn_fractf(up);
+      o.fy[v] = __builtin_amdgcn_fractf(vp);
       const uint32_t x0 = (uint32_t)up, y0 = (uint32_t)vp;
-      q[v] = (uint32_t)struct_buffer_load_i32(rs[v], (int)(__umul24(y0, Wq[v]) + x0), 0, 0, 0);
+      o.q[v] = (uint32_t)struct_buffer_load_i32(rs[v], (int)(__umul24(y0, Wq[v]) + x0), 0, 0, 0);
     }
+    k2 += dk2;
+    k1 += dk1;
+    if (k1 >= n) {
+      k1 -= n;
+      ++k2;
+    }
+  };
+  auto process = [&](const Tap& o, int m) {
+    if (o.t < 0) return;
+    const float a4 = tile[o.at] - rp.a_c;  // 4 (a - a_c)
+    const float w = colour_weight<false>(wcol, a4) * wsp[o.t];
+    const float wa = w * a4;
 #pragma unroll
     for (int v = 0; v < G; ++v) {
-      const float b = __builtin_fmaf(bilerp_scaled(q[v], fx[v], fy[v]), 0x1p24f, -bc[v]);
+      const float b = __builtin_fmaf(bilerp_scaled(o.q[v], o.fx[v], o.fy[v]), 0x1p24f, -bc[v]);
       const float tb = w * b;
-      Sb[v] = Sb[v] + tb;
-      Sbb[v] = __builtin_fmaf(tb, b, Sbb[v]);
-      Sab[v] = __builtin_fmaf(wa, b, Sab[v]);
+      pb[m][v] = pb[m][v] + tb;
+      pbb[m][v] = __builtin_fmaf(tb, b, pbb[m][v]);
+      pab[m][v] = __builtin_fmaf(wa, b, pab[m][v]);
+    }
+  };
+  const int rounds = (T + LANES - 1) / LANES;
+  if constexpr (V == 1) {
+    Tap a, c;
+    issue(a);
+    for (int i = 0; i < rounds; i += 2) {
+      issue(c);
+      process(a, 0);
+      issue(a);
+      process(c, 0);
+    }
+  } else {
+    for (int i = 0; i < rounds; ++i) {
+      Tap o[V];
+#pragma unroll
+      for (int m = 0; m < V; ++m) issue(o[m]);
+#pragma unroll
+      for (int m = 0; m < V; ++m) process(o[m], m);
     }
   }
 #pragma unroll
-  for (int o = LANES / 2; o >= 1; o >>= 1) {
+  for (int w = V / 2; w >= 1; w /= 2)
 #pragma unroll
-    for (int v = 0; v < G; ++v) {
-      Sb[v] = Sb[v] + __shfl_xor(Sb[v], o);
-      Sbb[v] = Sbb[v] + __shfl_xor(Sbb[v], o);
-      Sab[v] = Sab[v] + __shfl_xor(Sab[v], o);
-    }
+    for (int m = 0; m < w; ++m)
+#pragma unroll
+      for (int v = 0; v < G; ++v) {
+        pb[m][v] = pb[m][v] + pb[m + w][v];
+        pbb[m][v] = pbb[m][v] + pbb[m + w][v];
+        pab[m][v] = pab[m][v] + pab[m + w][v];
+      }
+#pragma unroll
+  for (int v = 0; v < G; ++v) {
+    Sb[v] = pb[0][v];
+    Sbb[v] = pbb[0][v];
+    Sab[v] = pab[0][v];
   }
+  butterfly<PL / 2, G>(Sb, Sbb, Sab);
+}
+
+// the least of lo and the largest of hi over a quad of lanes
+__device__ __forceinline__ void join_quad(float& lo, float& hi) {
+  lo = fminf(lo, xor_lane<1>(lo));
+  hi = fmaxf(hi, xor_lane<1>(hi));
+  lo = fminf(lo, xor_lane<2>(lo));
+  hi = fmaxf(hi, xor_lane<2>(hi));
 }
 
 // Views J0 .. J0+G-1: build H_j = M_j + e_j m^T, apply the border rule at the window
 // corners, take the centre sample, run the tap pass and finish each view's ZNCC.
 // c[g] / ok[g] receive 1 - Z and the validity.
-template <int G, bool FR, int LANES>
+template <int G, bool FR, int LANES, int PL>
 __device__ __forceinline__ void view_group(const Args& A, int J0, const RefPix& rp, const Hyp& h,
                                            const float* __restrict__ tile, int TW, const float* __restrict__ wcol,
                                            const float* __restrict__ wsp, float (&c)[G], bool (&ok)[G]) {
@@ -442,10 +545,13 @@ __device__ __forceinline__ void view_group(const Args& A, int J0, const RefPix& 
     bool inside = h.ok;
     float wmin = 3.0e38f, wmax = -3.0e38f;
     float umin = 3.0e38f, umax = -3.0e38f, vmin = 3.0e38f, vmax = -3.0e38f;
+    // (4 lanes or more sharing the pixel: a corner each, then joined across the quad)
+    constexpr bool kSplit = PL >= 4;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float X = rp.X0 + A.off[(k & 1) ? 2 * A.R : 0];
-      const float Y = rp.Y0 + A.off[(k & 2) ? 2 * A.R : 0];
+    for (int c = 0; c < (kSplit ? 1 : 4); ++c) {
+      const int k = kSplit ? (int)(threadIdx.x & 3) : c;
+      const float X = rp.X0 + ((k & 1) ? A.off[2 * A.R] : A.off[0]);
+      const float Y = rp.Y0 + ((k & 2) ? A.off[2 * A.R] : A.off[0]);
       const float u = __builtin_fmaf(Hm[g][0], X, __builtin_fmaf(Hm[g][1], Y, Hm[g][2]));
       const float v = __builtin_fmaf(Hm[g][3], X, __builtin_fmaf(Hm[g][4], Y, Hm[g][5]));
       const float w = __builtin_fmaf(Hm[g][6], X, __builtin_fmaf(Hm[g][7], Y, Hm[g][8]));
@@ -458,6 +564,15 @@ __device__ __forceinline__ void view_group(const Args& A, int J0, const RefPix& 
       umax = fmaxf(umax, up);
       vmin = fminf(vmin, vp);
       vmax = fmaxf(vmax, vp);
+    }
+    if constexpr (kSplit) {
+      int all = inside ? 1 : 0;
+      all &= xor_lane<1>(all);
+      all &= xor_lane<2>(all);
+      inside = all != 0;
+      join_quad(wmin, wmax);
+      join_quad(umin, umax);
+      join_quad(vmin, vmax);
     }
     // every tap's computed w lies within 2^-22 S of the corner range (fma error bound), so
     // the fast reciprocal is exact for the whole window when this range stays in [2^-100, 2^100]
@@ -504,11 +619,11 @@ __device__ __forceinline__ void view_group(const Args& A, int J0, const RefPix& 
   float Sb[G], Sbb[G], Sab[G];
   if constexpr (LANES > 1) {
     if (__ballot(need_exact) != 0)
-      tap_pass_lanes<G, true, true, LANES>(A, J0, rp, tile, TW, wcol, wsp, Hm, bc, Sb, Sbb, Sab);
+      tap_pass_lanes<G, true, true, LANES, PL>(A, J0, rp, tile, TW, wcol, wsp, Hm, bc, Sb, Sbb, Sab);
     else if (__ballot(need_clamp) != 0)
-      tap_pass_lanes<G, false, true, LANES>(A, J0, rp, tile, TW, wcol, wsp, Hm, bc, Sb, Sbb, Sab);
+      tap_pass_lanes<G, false, true, LANES, PL>(A, J0, rp, tile, TW, wcol, wsp, Hm, bc, Sb, Sbb, Sab);
     else
-      tap_pass_lanes<G, false, false, LANES>(A, J0, rp, tile, TW, wcol, wsp, Hm, bc, Sb, Sbb, Sab);
+      tap_pass_lanes<G, false, false, LANES, PL>(A, J0, rp, tile, TW, wcol, wsp, Hm, bc, Sb, Sbb, Sab);
   } else if (FR && A.frac) {
     // the window-resize scheme: computed tap positions X0 + off[k] are monotone in k, so they
     // stay between the corners' and the bounds above hold for them as for integer spacing
@@ -556,7 +671,7 @@ __device__ __forceinline__ void topk_insert(float (&top)[kMaxTopK], float c) {
 // Cost (Eq. 5 over the best-K valid sources) of plane (n, d) at pixel rp.  Sources are
 // scored two at a time; per_view / valid (global, optional) receive 1 - Z and the flag of
 // each source.  FR: the job may use the window-resize scheme (A.frac decides).
-template <bool FR, int LANES = 1>
+template <bool FR, int LANES = 1, int PL = LANES>
 __device__ __forceinline__ float plane_cost(const Args& A, const RefPix& rp, const float* __restrict__ tile, int TW,
                             const float* __restrict__ wcol, const float* __restrict__ wsp, float nx, float ny,
                             float nz, float d, float* per_view, uint8_t* valid) {
@@ -583,11 +698,11 @@ __device__ __forceinline__ float plane_cost(const Args& A, const RefPix& rp, con
     const int gn = NV - j0 < 2 ? 1 : 2;
     if (any) {
       if (gn == 2) {
-        view_group<2, FR, LANES>(A, j0, rp, h, tile, TW, wcol, wsp, c, ok);
+        view_group<2, FR, LANES, PL>(A, j0, rp, h, tile, TW, wcol, wsp, c, ok);
       } else {
         float c1[1];
         bool ok1[1];
-        view_group<1, FR, LANES>(A, j0, rp, h, tile, TW, wcol, wsp, c1, ok1);
+        view_group<1, FR, LANES, PL>(A, j0, rp, h, tile, TW, wcol, wsp, c1, ok1);
         c[0] = c1[0];
         ok[0] = ok1[0];
       }
@@ -903,22 +1018,28 @@ __device__ __forceinline__ void eval_tile(const Job& J, const Launch& L, int til
   rp.var_a = 0.0f;
   if (valid) {
     rp.a_c = tile_lds[(row + r) * TW + 2 * col + par + r];
-    float S_w = 0.0f, S_a4 = 0.0f, S_aa16 = 0.0f;  // S_a and S_aa, 4 and 16 times over
-    int t = 0;
-    for (int k2 = 0; k2 <= 2 * A.R; ++k2) {
-      const float* trow = tile_lds + rp.tbase + k2 * A.s * TW;
-      for (int k1 = 0; k1 <= 2 * A.R; ++k1, ++t) {
-        const float a4 = (frac ? ref_tap<true>(A, rp, tile_lds, TW, k1, k2) : trow[k1 * A.s]) - rp.a_c;
-        const float w = (frac ? colour_weight<true>(wcol, a4) : colour_weight<false>(wcol, a4)) * wsp[t];
-        const float wa4 = w * a4;
-        S_w = S_w + w;
-        S_a4 = S_a4 + wa4;
-        S_aa16 = __builtin_fmaf(wa4, a4, S_aa16);
+    const size_t ncol = (size_t)A.H * A.Wc, at = (size_t)y * A.Wc + ci;
+    if (L.ref_mode == 2) {
+      load_ref_sums(A, colour, ncol, at, rp.S_w, rp.mu_a, rp.var_a);
+    } else {
+      float S_w = 0.0f, S_a4 = 0.0f, S_aa16 = 0.0f;  // S_a and S_aa, 4 and 16 times over
+      int t = 0;
+      for (int k2 = 0; k2 <= 2 * A.R; ++k2) {
+        const float* trow = tile_lds + rp.tbase + k2 * A.s * TW;
+        for (int k1 = 0; k1 <= 2 * A.R; ++k1, ++t) {
+          const float a4 = (frac ? ref_tap<true>(A, rp, tile_lds, TW, k1, k2) : trow[k1 * A.s]) - rp.a_c;
+          const float w = (frac ? colour_weight<true>(wcol, a4) : colour_weight<false>(wcol, a4)) * wsp[t];
+          const float wa4 = w * a4;
+          S_w = S_w + w;
+          S_a4 = S_a4 + wa4;
+          S_aa16 = __builtin_fmaf(wa4, a4, S_aa16);
+        }
       }
+      rp.S_w = S_w;
+      rp.mu_a = (S_a4 * 0.25f) / S_w;
+      rp.var_a = (S_aa16 * 0.0625f) / S_w - rp.mu_a * rp.mu_a;
+      if (L.ref_mode == 1) store_ref_sums(A, colour, ncol, at, rp.S_w, rp.mu_a, rp.var_a);
     }
-    rp.S_w = S_w;
-    rp.mu_a = (S_a4 * 0.25f) / S_w;
-    rp.var_a = (S_aa16 * 0.0625f) / S_w - rp.mu_a * rp.mu_a;
     rp.ok = rp.var_a >= A.eps_v;
   }
   const int lane = threadIdx.x & 63;
@@ -1131,131 +1252,186 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   }
 }
 
-// Small references, whose pixels alone do not fill the GPU: LANES lanes share each pixel,
-// its tap sums split as in tap_pass_lanes.  A workgroup covers 256 / LANES compacted pixels
-// of one row of one colour of job 0 (single-job launches); every lane of a pixel's group
-// scores the same hypotheses and reaches the same costs, and the group's first lane
-// writes.  Modes as in eval_tile; the reference-side sums stay sequential per pixel.
-template <int LANES>
-__global__ __launch_bounds__(kBlock) void eval_lanes_kernel(const Job* __restrict__ jobs, Launch L) {
+// Small references, whose pixels alone do not fill the GPU: PL lanes share each (pixel,
+// candidate) pair, its sums split LANES ways as in tap_pass_lanes.  A workgroup covers L.lanes_px
+// compacted pixels of one row of one colour of job 0 (single-job launches); as in eval_tile the
+// non-empty pairs form a list that all its groups of PL lanes draw from, each pair's cost goes
+// to LDS and one lane per pixel selects.  Latency bounds such a launch (a pair is a chain of
+// gathers, and a CU holds 16 waves), so what counts is how many gathers are in flight and how
+// short the chain is: one group per pair rather than per pixel (eight candidates one after the
+// other), workgroups and lanes per pair planned for one round (lanes_plan), loads issued ahead, a
+// window corner per lane, butterflies over DPP, the reference sums loaded.  The order of every
+// sum is unchanged.  160 x 120, 4 sources, 11 x 11 taps, 16 lanes: propagation launches 130 -> 72
+// us, refinement 83 -> 36 us, a depth map of 3 iterations 1305 -> 864 us; 300 x 200, 8 sources: 5016 ->
+// 3532 us.
+// Modes as in eval_tile.  Dynamic LDS: lanes_lds(px) floats (reference data, costs, list), the
+// spatial weights, the reference tile.
+constexpr int kLanesBlock = 2 * kBlock;
+template <int LANES, int PL>
+__global__ __launch_bounds__(kLanesBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void eval_lanes_kernel(const Job* __restrict__ jobs, Launch L) {
   __shared__ float wcol[256];
   extern __shared__ float lds[];
   const Job& J = jobs[0];
   const Args& A = J.A;
-  constexpr int P = kBlock / LANES;
+  constexpr int G = kLanesBlock / PL;
+  const int P = L.lanes_px;
   const int tiles_x = (A.Wc + P - 1) / P;
   const int tile_y = (int)blockIdx.x / tiles_x, tile_x = (int)blockIdx.x - tile_y * tiles_x;
   const int r = A.halo;
   const int TW = 2 * P + 2 * r, TH = 1 + 2 * r;
-  float* wsp = lds;
+  float* ref_lds = lds;                                            // S_w (-1: not usable), mu_a, var_a per pixel
+  float* cost_lds = lds + 3 * P;                                   // cost of slot k of pixel p at [k][p]
+  uint16_t* item_lds = reinterpret_cast<uint16_t*>(lds + 11 * P);  // (pixel << 3 | slot)
+  int* n_list = reinterpret_cast<int*>(lds + 15 * P);
+  float* wsp = lds + lanes_lds(P);
   float* tile_lds = wsp + A.n_taps;
   const int x_org = tile_x * 2 * P - r, y_org = tile_y - r;
-  for (int i = threadIdx.x; i < 256; i += kBlock) wcol[i] = gl(A.wcol)[i];
-  for (int i = threadIdx.x; i < A.n_taps; i += kBlock) wsp[i] = gl(A.wsp)[i];
-  for (int i = threadIdx.x; i < TW * TH; i += kBlock) {
+  for (int i = threadIdx.x; i < 256; i += kLanesBlock) wcol[i] = gl(A.wcol)[i];
+  for (int i = threadIdx.x; i < A.n_taps; i += kLanesBlock) wsp[i] = gl(A.wsp)[i];
+  for (int i = threadIdx.x; i < TW * TH; i += kLanesBlock) {
     const int ty = i / TW, tx = i - ty * TW;
     const int gx = min(max(x_org + tx, 0), A.W - 1);
     const int gy = min(max(y_org + ty, 0), A.H - 1);
     const unsigned short hb = gl(reinterpret_cast<const unsigned short*>(A.ref))[(size_t)gy * A.W + gx];
     tile_lds[i] = 4.0f * __half2float(__ushort_as_half(hb));  // 4x the grey value, exact
   }
+  if (threadIdx.x == 0) *n_list = 0;
   __syncthreads();
 
-  const int slot = (int)threadIdx.x / LANES, g = (int)threadIdx.x % LANES;
-  const int lane = threadIdx.x & 63;
   const int colour = L.colour;
   const int y = tile_y;
-  const int ci = tile_x * P + slot;
   const int par = (y + colour) & 1;
+  const int n = 2 * A.R + 1;
+  // pixel p of the workgroup: its position and reference data (sums: the caller's)
+  auto pixel = [&](int p) {
+    RefPix q;
+    q.x = 2 * (tile_x * P + p) + par;
+    q.y = y;
+    q.X0 = (float)q.x;
+    q.Y0 = (float)q.y;
+    q.tbase = (r - A.s * A.R) * TW + 2 * p + par + r - A.s * A.R;  // first tap (-R, -R)
+    q.tox = x_org;
+    q.toy = y_org;
+    ray_f(A, q.x, q.y, q.rx, q.ry, q.rz);
+    q.a_c = tile_lds[r * TW + 2 * p + par + r];
+    return q;
+  };
+  const size_t plane_sz = (size_t)A.H * A.Wc;
+  const int my = (int)threadIdx.x;  // the pixel of a thread below P
+  const int ci = tile_x * P + my;
   const int x = 2 * ci + par;
-  const bool in_img = y < A.H && ci < A.Wc && x < A.W;
+  const bool in_img = my < P && y < A.H && ci < A.Wc && x < A.W;
   const bool valid = in_img && pixel_valid(A, x, y);
-  RefPix rp;
-  rp.x = x;
-  rp.y = y;
-  rp.X0 = (float)x;
-  rp.Y0 = (float)y;
-  rp.ok = false;
-  rp.tbase = (r - A.s * A.R) * TW + 2 * slot + par + r - A.s * A.R;  // first tap (-R, -R)
-  rp.tox = x_org;
-  rp.toy = y_org;
-  ray_f(A, x, y, rp.rx, rp.ry, rp.rz);
-  rp.a_c = 0.0f;
-  rp.S_w = 1.0f;
-  rp.mu_a = 0.0f;
-  rp.var_a = 0.0f;
+  const size_t cidx = (size_t)y * A.Wc + ci;
+  unsigned live = 0;  // non-empty slots (mode 2: slot 0 is the given plane)
   if (valid) {
-    rp.a_c = tile_lds[r * TW + 2 * slot + par + r];
-    float S_w = 0.0f, S_a4 = 0.0f, S_aa16 = 0.0f;
-    int t = 0;
-    for (int k2 = 0; k2 <= 2 * A.R; ++k2) {
-      const float* trow = tile_lds + rp.tbase + k2 * A.s * TW;
-      for (int k1 = 0; k1 <= 2 * A.R; ++k1, ++t) {
-        const float a4 = trow[k1 * A.s] - rp.a_c;
-        const float w = colour_weight<false>(wcol, a4) * wsp[t];
-        const float wa4 = w * a4;
-        S_w = S_w + w;
-        S_a4 = S_a4 + wa4;
-        S_aa16 = __builtin_fmaf(wa4, a4, S_aa16);
+    if (L.mode == 2) {
+      const float4 pl = ld4(reinterpret_cast<const float4*>(J.planes_in), (size_t)y * A.W + x);
+      live = __builtin_isnan(pl.w) ? 0u : 1u;
+    } else {
+      for (int k = 0; k < L.ncand; ++k)
+        if (!__builtin_isnan(gl(J.cand)[k * plane_sz + cidx].w)) live |= 1u << k;
+    }
+    const RefPix q = pixel(my);
+    float S_w = 0.0f, S_a4 = 0.0f, S_aa16 = 0.0f, mu, var;
+    if (L.ref_mode == 2) load_ref_sums(A, colour, plane_sz, cidx, S_w, mu, var);
+    for (int k2 = 0; L.ref_mode != 2 && k2 < n; ++k2) {
+      const float* trow = tile_lds + q.tbase + k2 * A.s * TW;
+      const float* wrow = wsp + k2 * n;
+      for (int k0 = 0; k0 < n; k0 += 8) {
+        // eight taps' values and weights, then their sums in order
+        float a4[8], w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a4[e] = trow[min(k0 + e, n - 1) * A.s] - q.a_c;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = colour_weight<false>(wcol, a4[e]) * wrow[min(k0 + e, n - 1)];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (k0 + e < n) {
+            const float wa4 = w[e] * a4[e];
+            S_w = S_w + w[e];
+            S_a4 = S_a4 + wa4;
+            S_aa16 = __builtin_fmaf(wa4, a4[e], S_aa16);
+          }
       }
     }
-    rp.S_w = S_w;
-    rp.mu_a = (S_a4 * 0.25f) / S_w;
-    rp.var_a = (S_aa16 * 0.0625f) / S_w - rp.mu_a * rp.mu_a;
-    rp.ok = rp.var_a >= A.eps_v;
+    if (L.ref_mode != 2) {
+      mu = (S_a4 * 0.25f) / S_w;
+      var = (S_aa16 * 0.0625f) / S_w - mu * mu;
+      if (L.ref_mode == 1) store_ref_sums(A, colour, plane_sz, cidx, S_w, mu, var);
+    }
+    ref_lds[my] = var >= A.eps_v ? S_w : -1.0f;
+    ref_lds[P + my] = mu;
+    ref_lds[2 * P + my] = var;
+    if (live) {
+      int at = atomicAdd(n_list, __popc(live));  // the list's order changes no result
+      for (unsigned m = live; m; m &= m - 1) item_lds[at++] = (uint16_t)((my << 3) | (__ffs(m) - 1));
+    }
   }
-  const bool writer = g == 0;
-
+  __syncthreads();
+  const int n_items = *n_list;
+  if (L.count && threadIdx.x == 0) atomicAdd(L.count, (unsigned long long)n_items);
+  const bool writer = threadIdx.x % PL == 0;
+  for (int i = (int)threadIdx.x / PL; i < n_items; i += G) {
+    const int item = item_lds[i];
+    const int p = item >> 3, k = item & 7;
+    RefPix q = pixel(p);
+    const float sw = ref_lds[p];
+    q.ok = sw > 0.0f;
+    q.S_w = q.ok ? sw : 1.0f;
+    q.mu_a = ref_lds[P + p];
+    q.var_a = ref_lds[2 * P + p];
+    if (L.mode == 2) {
+      const size_t at = (size_t)y * A.W + q.x;
+      const float4 h = ld4(reinterpret_cast<const float4*>(J.planes_in), at);
+      float* pv = J.per_view_out && writer ? J.per_view_out + at * A.n_src : nullptr;
+      uint8_t* vm = J.valid_out && writer ? J.valid_out + at * A.n_src : nullptr;
+      const float c = plane_cost<false, LANES, PL>(A, q, tile_lds, TW, wcol, wsp, h.x, h.y, h.z, h.w, pv, vm);
+      if (writer) gl(J.cost_out)[at] = c;
+    } else {
+      const float4 h = ld4(J.cand, k * plane_sz + (size_t)y * A.Wc + tile_x * P + p);
+      const float c = plane_cost<false, LANES, PL>(A, q, tile_lds, TW, wcol, wsp, h.x, h.y, h.z, h.w, nullptr, nullptr);
+      if (writer) cost_lds[k * P + p] = c;
+    }
+  }
   if (L.mode == 2) {
-    if (in_img) {
-      const size_t p = (size_t)y * A.W + x;
-      float c = kCmax;
-      float* pv = J.per_view_out && writer ? J.per_view_out + p * A.n_src : nullptr;
-      uint8_t* vm = J.valid_out && writer ? J.valid_out + p * A.n_src : nullptr;
-      float4 pl = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (valid) pl = ld4(reinterpret_cast<const float4*>(J.planes_in), p);
-      const bool score = valid && !__builtin_isnan(pl.w);
-      const unsigned long long bal = __ballot(score && writer);
-      if (L.count && lane == 0) atomicAdd(L.count, (unsigned long long)__popcll(bal));
-      if (score) {
-        c = plane_cost<false, LANES>(A, rp, tile_lds, TW, wcol, wsp, pl.x, pl.y, pl.z, pl.w, pv, vm);
-      } else {
-        for (int j = 0; j < A.n_src; ++j) {
-          if (pv) gl(pv)[j] = kCmax;
-          if (vm) gl(vm)[j] = 0;
-        }
+    // a plane whose depth is NaN, or a pixel whose window leaves the image
+    if (in_img && !live) {
+      const size_t at = (size_t)y * A.W + x;
+      for (int j = 0; j < A.n_src; ++j) {
+        if (J.per_view_out) gl(J.per_view_out)[at * A.n_src + j] = kCmax;
+        if (J.valid_out) gl(J.valid_out)[at * A.n_src + j] = 0;
       }
-      if (writer) gl(J.cost_out)[p] = c;
+      gl(J.cost_out)[at] = kCmax;
     }
     return;
   }
-
-  const size_t cidx = (size_t)y * A.Wc + ci;
-  const size_t plane_sz = (size_t)A.H * A.Wc;
+  __syncthreads();
+  if (L.mode == 3) {
+    if (in_img) {
+      const size_t np = (size_t)A.W * A.H, at = (size_t)y * A.W + x;
+      for (int k = 0; k < L.ncand; ++k) gl(J.cost_out)[k * np + at] = ((live >> k) & 1u) ? cost_lds[k * P + my] : kCmax;
+    }
+    return;
+  }
+  if (!in_img || (L.mode == 1 && !valid)) return;
   float4 best = make_float4(0.f, 0.f, 0.f, 0.f);
   float bc = kCmax;
-  if (L.mode == 1 && valid) {
+  if (L.mode == 1) {
     best = ld4(A.plane[colour], cidx);
     bc = gl(A.cost[colour])[cidx];
   }
+  int pick = -1;
   for (int k = 0; k < L.ncand; ++k) {
-    float4 h = make_float4(0.f, 0.f, 0.f, __int_as_float(0x7fc00000));
-    if (valid) h = ld4(J.cand, k * plane_sz + cidx);
-    const bool has = valid && !__builtin_isnan(h.w);
-    if (__ballot(has) == 0) continue;
-    // the ballot over the whole wave, before only its first lane goes on to count
-    const unsigned long long scored = __ballot(has && writer);
-    if (L.count && lane == 0) atomicAdd(L.count, (unsigned long long)__popcll(scored));
-    if (has) {
-      const float c = plane_cost<false, LANES>(A, rp, tile_lds, TW, wcol, wsp, h.x, h.y, h.z, h.w, nullptr, nullptr);
-      const bool take = L.mode == 0 ? (k == 0 || c <= bc) : (c < bc);
-      if (take) {
-        bc = c;
-        best = h;
-      }
+    if (!((live >> k) & 1u)) continue;
+    const float c = cost_lds[k * P + my];
+    const bool take = L.mode == 0 ? (k == 0 || c <= bc) : (c < bc);
+    if (take) {
+      bc = c;
+      pick = k;
     }
   }
-  if (!in_img || (L.mode == 1 && !valid) || !writer) return;
+  if (pick >= 0) best = ld4(J.cand, pick * plane_sz + cidx);
   if (!valid) {
     best = make_float4(0.f, 0.f, 0.f, 0.f);
     bc = kCmax;
@@ -1365,6 +1541,20 @@ size_t eval_lds_bytes(int tile_rows, int max_radius_px, int max_taps) {
   return sizeof(float) * ((size_t)kCompactLds + (size_t)max_taps + tw * th);
 }
 
+// the split-lane kernel for partial sums split `lanes` ways over `pl` lanes
+static const void* lanes_fn(int lanes, int pl) {
+  switch (lanes * 32 + pl) {
+    case 2 * 32 + 2: return (const void*)pmk::eval_lanes_kernel<2, 2>;
+    case 4 * 32 + 4: return (const void*)pmk::eval_lanes_kernel<4, 4>;
+    case 8 * 32 + 8: return (const void*)pmk::eval_lanes_kernel<8, 8>;
+    case 8 * 32 + 4: return (const void*)pmk::eval_lanes_kernel<8, 4>;
+    case 16 * 32 + 16: return (const void*)pmk::eval_lanes_kernel<16, 16>;
+    case 16 * 32 + 8: return (const void*)pmk::eval_lanes_kernel<16, 8>;
+    case 16 * 32 + 4: return (const void*)pmk::eval_lanes_kernel<16, 4>;
+    default: return nullptr;
+  }
+}
+
 hipError_t eval_lds_setup(size_t* max_dynamic) {
   // Tiles above 64 KiB of LDS (one-row tiles with wide windows) need the opt-in limit.  It
   // is raised here, once per device and context, for both kernel instances, to what a
@@ -1379,10 +1569,10 @@ hipError_t eval_lds_setup(size_t* max_dynamic) {
     return e;
   const size_t per_wg = std::min<size_t>((size_t)std::max(optin, per_cu), 160 * 1024);
   size_t lim = per_wg;
-  const void* fns[8] = {(const void*)pmk::eval_kernel<false, false>, (const void*)pmk::eval_kernel<true, false>,
+  const void* fns[] = {(const void*)pmk::eval_kernel<false, false>, (const void*)pmk::eval_kernel<true, false>,
                         (const void*)pmk::eval_kernel<false, true>,  (const void*)pmk::eval_kernel<true, true>,
-                        (const void*)pmk::eval_lanes_kernel<2>,      (const void*)pmk::eval_lanes_kernel<4>,
-                        (const void*)pmk::eval_lanes_kernel<8>,      (const void*)pmk::eval_lanes_kernel<16>};
+                        lanes_fn(2, 2),  lanes_fn(4, 4),  lanes_fn(8, 8),  lanes_fn(8, 4),
+                        lanes_fn(16, 16), lanes_fn(16, 8), lanes_fn(16, 4)};
   for (const void* fn : fns) {
     hipFuncAttributes a{};
     if ((e = hipFuncGetAttributes(&a, fn)) != hipSuccess) return e;
@@ -1406,25 +1596,40 @@ hipError_t launch_eval(const Job* d_jobs, const Launch& L, int grid, size_t lds,
   return hipLaunchKernel(fn, dim3(grid), dim3(kBlock), args, lds, st);
 }
 
-size_t eval_lanes_lds_bytes(int lanes, int radius_px, int n_taps) {
-  const int P = kBlock / lanes;
-  return sizeof(float) * ((size_t)n_taps + (size_t)(2 * P + 2 * radius_px) * (size_t)(1 + 2 * radius_px));
+// The split of a split-lane launch.  Workgroups of 8 waves, two of which a CU holds (128 VGPRs):
+// pixels per workgroup such that one round of workgroups covers the rows, if that leaves them
+// at most kLanesMaxPx; lanes per pair (4 at least, where a corner test is one lane's) doubled
+// as long as every pair still has lanes of its own in that round, as a launch with lanes to
+// spare is bound by the length of a pair's chain, and the part of it that does not split is
+// repeated in every lane where there are none.  160 x 120 (80 compacted columns), 16 ways: 4 / 8 /
+// 16 lanes per pair for the propagation / refinement / initialisation launches and 20 pixels per
+// workgroup, 864 us per depth map; 1124-1189 us with 16 to 64 pixels (workgroups of one size split
+// a row unevenly, or need a second round) whatever the lanes.
+LanesPlan lanes_plan(int lanes, int H, int Wc, int ncand, int n_cu) {
+  LanesPlan p;
+  const int nx = std::max({1, std::min((Wc + 7) / 8, 2 * n_cu / H), (Wc + kLanesMaxPx - 1) / kLanesMaxPx});
+  p.px = (Wc + nx - 1) / nx;
+  // about half of the propagated candidates are left out
+  const int64_t pairs = (int64_t)H * Wc * (ncand > 3 ? ncand / 2 : std::max(ncand, 1));
+  p.pl = std::min(lanes, 4);
+  while (p.pl < lanes && pairs * p.pl * 2 <= (int64_t)n_cu * 2 * pmk::kLanesBlock) p.pl *= 2;
+  return p;
 }
 
-hipError_t launch_eval_lanes(const Job* d_jobs, const Launch& L, int lanes, int H, int Wc, size_t lds,
+size_t eval_lanes_lds_bytes(int px, int radius_px, int n_taps) {
+  return sizeof(float) * ((size_t)lanes_lds(px) + (size_t)n_taps + (size_t)(2 * px + 2 * radius_px) * (size_t)(1 + 2 * radius_px));
+}
+
+hipError_t launch_eval_lanes(const Job* d_jobs, const Launch& L, int lanes, int pl, int H, int Wc, size_t lds,
                              hipStream_t st) {
-  const int P = kBlock / lanes;
+  const void* fn = lanes_fn(lanes, pl);
+  const int P = L.lanes_px;
+  if (!fn || P < 1 || P > kLanesMaxPx) return hipErrorInvalidValue;
   const long long grid = (long long)H * ((Wc + P - 1) / P);
   if (grid < 1 || grid > 0x7fffffff) return hipErrorInvalidValue;
   Launch l = L;
   void* args[] = {(void*)&d_jobs, (void*)&l};
-  const void* fn = lanes == 2 ? (const void*)pmk::eval_lanes_kernel<2>
-                   : lanes == 4 ? (const void*)pmk::eval_lanes_kernel<4>
-                   : lanes == 8 ? (const void*)pmk::eval_lanes_kernel<8>
-                   : lanes == 16 ? (const void*)pmk::eval_lanes_kernel<16>
-                                 : nullptr;
-  if (!fn) return hipErrorInvalidValue;
-  return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kBlock), args, lds, st);
+  return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(pmk::kLanesBlock), args, lds, st);
 }
 
 hipError_t launch_candidates(int kind, const Job* d_jobs, const Launch& L, hipStream_t st) {
