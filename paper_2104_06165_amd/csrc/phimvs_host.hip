@@ -30,6 +30,7 @@ struct ViewData {
   double d_lo = 0, d_hi = 0;
   __half* plain = nullptr;
   uint32_t* quad = nullptr;
+  size_t cap = 0;  // pixels both arrays hold
 };
 
 template <typename T>
@@ -43,8 +44,8 @@ struct JobState {
   DevBuf<float4> plane[2];
   DevBuf<float> cost[2];
   DevBuf<float4> cand;
-  DevBuf<float4> hist;           // 2 colours x 8 candidates per pixel
-  DevBuf<float> ref_sums;        // 2 colours x 3 planes
+  DevBuf<float4> hist;           // 2 colours x 8 candidates per pixel; behind them the reference sums, 2
+                                 // colours x 3 planes of floats
   DevBuf<float> wcol, wsp;
 };
 
@@ -126,6 +127,18 @@ int ensure(phimvs_ctx* c, DevBuf<T>& b, size_t n) {
   return PHIMVS_OK;
 }
 
+// as ensure, giving back a buffer of more than four times the need (above 64 MiB): what a larger
+// problem left behind
+template <typename T>
+int fit(phimvs_ctx* c, DevBuf<T>& b, size_t n) {
+  if (b.p && b.n / 4 > n && b.n * sizeof(T) > ((size_t)64 << 20)) {
+    HIPCHECK(c, hipFree(b.p));
+    b.p = nullptr;
+    b.n = 0;
+  }
+  return ensure(c, b, n);
+}
+
 template <typename T>
 void release(DevBuf<T>& b) {
   if (b.p) (void)hipFree(b.p);
@@ -148,7 +161,6 @@ void release_state(JobState& s) {
   }
   release(s.cand);
   release(s.hist);
-  release(s.ref_sums);
   release(s.wcol);
   release(s.wsp);
 }
@@ -461,14 +473,13 @@ int setup_job(phimvs_ctx* c, const Problem& P, Job& J, JobState& S) {
   A.wsp = S.wsp.p;
   const size_t ncol = (size_t)A.Wc * A.H;
   for (int k = 0; k < 2; ++k) {
-    if ((rc = ensure(c, S.plane[k], ncol)) || (rc = ensure(c, S.cost[k], ncol))) return rc;
+    if ((rc = fit(c, S.plane[k], ncol)) || (rc = fit(c, S.cost[k], ncol))) return rc;
     A.plane[k] = S.plane[k].p;
     A.cost[k] = S.cost[k].p;
   }
-  if ((rc = ensure(c, S.cand, 8 * ncol)) || (rc = ensure(c, S.hist, 16 * ncol)) || (rc = ensure(c, S.ref_sums, 6 * ncol)))
-    return rc;
-  A.ref_sums[0] = S.ref_sums.p;
-  A.ref_sums[1] = S.ref_sums.p + 3 * ncol;
+  if ((rc = fit(c, S.cand, 8 * ncol)) || (rc = fit(c, S.hist, 16 * ncol + (6 * ncol + 3) / 4))) return rc;
+  A.ref_sums[0] = reinterpret_cast<float*>(S.hist.p + 16 * ncol);
+  A.ref_sums[1] = A.ref_sums[0] + 3 * ncol;
   J.cand = S.cand.p;
   J.hist[0] = S.hist.p;
   J.hist[1] = S.hist.p + 8 * ncol;
@@ -694,7 +705,8 @@ int prepare_single(phimvs_ctx* c, int ref, const int* srcs, int n_srcs, int wind
   Batch& b = c->single;
   const std::string key = problem_key(P) + "@" + std::to_string(c->tuning.tile_rows);
   if (key != b.layout_key || b.jobs.size() != 1) {
-    release_graph(b);
+    // a recorded sequence stays: its key says whether it fits the new problem's launches
+    b.layout_key.clear();
     resize_jobs(b, 1);
     b.ref_valid[0] = b.ref_valid[1] = false;
     if ((rc = setup_job(c, P, b.jobs[0], b.state[0]))) return rc;
@@ -760,6 +772,25 @@ int run_sequence_graph(phimvs_ctx* c, Batch& b, const std::string& gkey, int ite
   return PHIMVS_OK;
 }
 
+// everything the recorded launches of a single-job sequence hold (the job table they read at
+// run time): geometry, launch configuration, iterations, the table's and the counters' places
+std::string sequence_key(const phimvs_ctx* c, const Batch& b, int iters) {
+  const Args& A = b.jobs[0].A;
+  const Launch L = base_launch(b);
+  std::string k;
+  auto add = [&k](long long v) { k += std::to_string(v) + ","; };
+  for (long long v : {(long long)A.W, (long long)A.H, (long long)A.lanes, (long long)A.by_depth, (long long)A.halo,
+                      (long long)A.n_taps, (long long)L.n_jobs, (long long)L.tile_rows, (long long)L.total_tiles,
+                      (long long)L.total_cblk, (long long)L.frac, (long long)b.max_r, (long long)b.max_taps,
+                      (long long)iters, (long long)c->tuning.persistent, (long long)c->tuning.wgs_per_cu,
+                      (long long)c->tuning.order_by_depth, (long long)c->order_auto})
+    add(v);
+  for (int x : L.xcd_len) add(x);
+  add((long long)reinterpret_cast<uintptr_t>(b.d_jobs));
+  add((long long)reinterpret_cast<uintptr_t>(b.queues.p));
+  return k;
+}
+
 // one depth map through the single-job batch: prepare, then the whole launch sequence
 // (replayed from a graph when there is no proposal); proposal (planes layout, optional)
 // gates the random initialisation
@@ -803,12 +834,7 @@ int run_single(phimvs_ctx* c, int ref, const int* srcs, int n_srcs, int window, 
   if (prop || c->diag) {
     rc = issue_sequence(c, b, iters, true, prop != nullptr);
   } else {
-    char ptrs[64];
-    std::snprintf(ptrs, sizeof ptrs, "#%p#%p", (void*)b.d_jobs, (void*)b.queues.p);
-    const std::string gkey = b.layout_key + "#" + std::to_string(iters) + "#" +
-                             std::to_string(c->tuning.persistent) + "#" + std::to_string(c->tuning.wgs_per_cu) +
-                             "#" + std::to_string(c->tuning.order_by_depth) + (c->order_auto ? "a" : "") + ptrs;
-    rc = run_sequence_graph(c, b, gkey, iters);
+    rc = run_sequence_graph(c, b, sequence_key(c, b, iters), iters);
   }
   if (rc) return rc;
   if (!on_device) {
@@ -895,6 +921,73 @@ static void free_views(phimvs_ctx* c) {
   c->views.clear();
 }
 
+// The scene's arrays, in the old scene's where an array holds at most twice the pixels (going
+// from scene to scene allocates nothing), and the images through one staging buffer: rows of
+// host memory go over as they lie, padding included, when that is at most twice the image
+// (row by row the copies of 1600 x 1066 images took most of the call); device images are read
+// where they are.
+static int take_views(phimvs_ctx* c, int n_views, const phimvs_image* images, const double* K, const double* R,
+                      const double* t, const double* depth_range) {
+  std::vector<ViewData> old;
+  old.swap(c->views);
+  c->views.resize(n_views);
+  size_t staged = 0;
+  for (int i = 0; i < n_views; ++i) {
+    const size_t npx = (size_t)images[i].width * images[i].height;
+    const size_t n_old = old.size();
+    for (size_t k = 0; k < n_old; ++k) {
+      ViewData& o = old[(i + k) % n_old];
+      if (o.plain && o.cap >= npx && o.cap <= 2 * npx) {
+        std::swap(c->views[i].plain, o.plain);
+        std::swap(c->views[i].quad, o.quad);
+        std::swap(c->views[i].cap, o.cap);
+        break;
+      }
+    }
+    const int64_t stride = images[i].stride_bytes ? images[i].stride_bytes : images[i].width;
+    if (!images[i].on_device)
+      staged = std::max(staged, stride <= 2 * (int64_t)images[i].width ? (size_t)stride * images[i].height : npx);
+  }
+  for (ViewData& o : old) {
+    if (o.plain) (void)hipFree(o.plain);
+    if (o.quad) (void)hipFree(o.quad);
+  }
+  int rc = staged ? fit(c, c->io_u8, staged) : PHIMVS_OK;
+  if (rc) return rc;
+  for (int i = 0; i < n_views; ++i) {
+    const phimvs_image& im = images[i];
+    ViewData& v = c->views[i];
+    v.W = im.width;
+    v.H = im.height;
+    std::memcpy(v.K, K + 9 * i, sizeof v.K);
+    std::memcpy(v.R, R + 9 * i, sizeof v.R);
+    std::memcpy(v.t, t + 3 * i, sizeof v.t);
+    v.d_lo = depth_range[2 * i];
+    v.d_hi = depth_range[2 * i + 1];
+    const size_t npx = (size_t)v.W * v.H;
+    if (!v.plain) {
+      HIPCHECK(c, hipMalloc((void**)&v.plain, npx * sizeof(__half)));
+      HIPCHECK(c, hipMalloc((void**)&v.quad, npx * sizeof(uint32_t)));
+      v.cap = npx;
+    }
+    int64_t stride = im.stride_bytes ? im.stride_bytes : im.width;
+    const uint8_t* src = static_cast<const uint8_t*>(im.data);
+    if (!im.on_device) {
+      if (stride <= 2 * (int64_t)v.W) {
+        const size_t bytes = (size_t)stride * (v.H - 1) + v.W;
+        HIPCHECK(c, hipMemcpyAsync(c->io_u8.p, src, bytes, hipMemcpyHostToDevice, c->stream));
+      } else {
+        HIPCHECK(c, hipMemcpy2DAsync(c->io_u8.p, v.W, src, stride, v.W, v.H, hipMemcpyHostToDevice, c->stream));
+        stride = v.W;
+      }
+      src = c->io_u8.p;
+    }
+    HIPCHECK(c, launch_build_view(src, stride, v.W, v.H, v.plain, v.quad, c->stream));
+  }
+  HIPCHECK(c, hipStreamSynchronize(c->stream));  // the caller's images are theirs again
+  return PHIMVS_OK;
+}
+
 void phimvs_destroy(phimvs_ctx* c) {
   if (!c) return;
   (void)hipSetDevice(c->device);
@@ -957,32 +1050,17 @@ int phimvs_set_views(phimvs_ctx* c, int n_views, const phimvs_image* images, con
       return fail(c, PHIMVS_E_ARG, "depth range of view " + std::to_string(i) + " needs 0 < d_lo < d_hi");
   }
   HIPCHECK(c, hipSetDevice(c->device));
-  HIPCHECK(c, hipStreamSynchronize(c->stream));
-  free_views(c);
-  release_batch(c->single);
+  // the old views' arrays are written over below: nothing may still read them, on any stream
+  HIPCHECK(c, hipDeviceSynchronize());
   release_batch(c->multi);
+  c->single.layout_key.clear();  // its state stays allocated for the next problem
   c->prepared = false;
-  c->views.resize(n_views);
-  for (int i = 0; i < n_views; ++i) {
-    const phimvs_image& im = images[i];
-    ViewData& v = c->views[i];
-    v.W = im.width;
-    v.H = im.height;
-    std::memcpy(v.K, K + 9 * i, sizeof v.K);
-    std::memcpy(v.R, R + 9 * i, sizeof v.R);
-    std::memcpy(v.t, t + 3 * i, sizeof v.t);
-    v.d_lo = depth_range[2 * i];
-    v.d_hi = depth_range[2 * i + 1];
-    const size_t npx = (size_t)v.W * v.H;
-    HIPCHECK(c, hipMalloc((void**)&v.plain, npx * sizeof(__half)));
-    HIPCHECK(c, hipMalloc((void**)&v.quad, npx * sizeof(uint32_t)));
-    const int64_t stride = im.stride_bytes ? im.stride_bytes : im.width;
-    int rc = ensure(c, c->io_u8, npx);
-    if (rc) return rc;
-    HIPCHECK(c, hipMemcpy2DAsync(c->io_u8.p, v.W, im.data, stride, v.W, v.H,
-                                 im.on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
-    HIPCHECK(c, launch_build_view(c->io_u8.p, v.W, v.W, v.H, v.plain, v.quad, c->stream));
-    HIPCHECK(c, hipStreamSynchronize(c->stream));
+  const int rc = take_views(c, n_views, images, K, R, t, depth_range);
+  if (rc) {
+    const std::string msg = c->err;
+    (void)hipStreamSynchronize(c->stream);
+    free_views(c);
+    return fail(c, rc, msg);
   }
   return PHIMVS_OK;
 }
