@@ -336,15 +336,18 @@ void phimvs_default_phi_params(phimvs_phi_params* p);
 /* Selection (Sec. III-E): the hypothesis maps are subsampled to half size (node (X, Y)
  * takes pixel (2X, 2Y)), the graph model (node states = hypotheses with potential
  * (C_max - C) / k1 + k2, pixels with depth = fixed states, 4-connected edges with
- * [k3 - min(1, relative depth difference)]^2) is decoded on the host by sequential
+ * [k3 - min(1, relative depth difference)]^2) is decoded by sequential
  * tree-reweighted message passing (as phimvs_phi_decode_host), the decoded half-size
  * depth is brought back to full
  * size (pixel (x, y) takes node (x / 2, y / 2)) as the reference map, and each pixel
  * without depth takes its hypothesis closest to the reference (lowest k on ties; stays
  * empty without hypothesis or reference).  Pixels with depth keep it.  depth, depth_out:
- * device H*W; hyp, cost: device planar 4*H*W.  The half-size inputs are gathered on the
- * device (9 (W+1)/2 (H+1)/2 floats of the context's scratch), copied to the host, decoded
- * there, and the decoded map goes back for the last step.  Synchronises the stream.
+ * device H*W; hyp, cost: device planar 4*H*W.  Graphs with many nodes for their length
+ * are decoded on the device (about 450 bytes of the context's scratch per node, and 10
+ * floats); small or narrow ones, those whose energies are not all finite and those that
+ * device memory does not hold are gathered (9 floats per node), copied to the host and
+ * decoded there.  Both take the same FP64 steps; the logarithms are each platform's own.
+ * Synchronises the stream.
  * PHIMVS_E_ARG also for a cost above C_max + k1 k2 at a sampled hypothesis (no positive
  * potential). */
 int phimvs_phi_select(phimvs_ctx* ctx, int width, int height, const float* depth, const float* hyp,

@@ -420,7 +420,7 @@ class Context:
         return cost
 
     def phi_select(self, depth, hyp, cost, params: Optional["PhiParams"] = None):
-        """One hypothesis per pixel without depth (graph model decoded on the host) -> depth (H, W)."""
+        """One hypothesis per pixel without depth (graph model decoded on the GPU, small ones on the host) -> depth (H, W)."""
         torch = self.torch
         self._sync_stream()
         d = depth.contiguous()

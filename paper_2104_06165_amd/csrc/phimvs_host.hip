@@ -91,6 +91,7 @@ struct phimvs_ctx {
   DevBuf<FuseMap> fuse_maps;              // fusion: map table
   std::vector<FuseMap> fuse_host;
   DevBuf<uint64_t> fuse_scratch;          // fusion: claims, pair table, tests passed
+  DevBuf<uint64_t> trw;                   // graph model of the hypothesis selection
   DevBuf<uint64_t> phi_bits;              // per-direction occupancy bitmaps of the hypothesis fits
   DevBuf<uint8_t> io_u8;
   // diagnostics
@@ -1002,6 +1003,7 @@ void phimvs_destroy(phimvs_ctx* c) {
   release(c->io_d);
   release(c->fuse_maps);
   release(c->fuse_scratch);
+  release(c->trw);
   release(c->phi_bits);
   release(c->io_u8);
   if (c->diag_count) (void)hipFree(c->diag_count);
@@ -1460,12 +1462,31 @@ int phimvs_phi_select(phimvs_ctx* c, int width, int height, const float* depth, 
   if (pp) p = *pp;
   HIPCHECK(c, hipSetDevice(c->device));
   const int W = width, H = height;
-  // half size: node (X, Y) takes pixel (2X, 2Y); the GPU gathers the nodes' inputs (depth,
-  // 4 hypotheses, 4 costs) and the host decodes
+  // half size: node (X, Y) takes pixel (2X, 2Y)
   const int W2 = (W + 1) / 2, H2 = (H + 1) / 2;
   const size_t n2 = (size_t)W2 * H2;
+  const char* invalid = "invalid PHI parameters or costs (k1 > 0, k2 > 0, k3 > 1, iterations >= 0, cost <= C_max + k1 k2)";
+  if (!(p.k1 > 0) || !(p.k2 > 0) || !(p.k3 > 1) || p.iterations < 0) return fail(c, PHIMVS_E_ARG, invalid);
+  if ((int64_t)W2 * H2 > INT32_MAX / 16)
+    return fail(c, PHIMVS_E_UNSUPPORTED, "graph model too large for the decoder (2^27 nodes or more)");
   int rc;
   if ((rc = ensure(c, c->io_a, 10 * n2))) return rc;
+  // beyond a k3 of 1e150 an edge energy can be infinite
+  if (trw_on_gpu(W2, H2) && p.k3 < 1e150 && fit(c, c->trw, trw_words(W2, H2)) == PHIMVS_OK) {
+    float* dec = c->io_a.p;
+    int *flag = nullptr, got = 0;
+    HIPCHECK(c, launch_trw(depth, hyp, cost, W, H, p.k1, p.k2, p.k3, PHIMVS_COST_MAX, p.iterations, c->trw.p, dec,
+                           &flag, c->stream));
+    // back to full size in the kernel: pixel (x, y) reads node (x / 2, y / 2)
+    HIPCHECK(c, launch_phi_select(depth, hyp, dec, W, H, flag, depth_out, c->stream));
+    HIPCHECK(c, hipMemcpyAsync(&got, flag, sizeof got, hipMemcpyDeviceToHost, c->stream));
+    HIPCHECK(c, hipStreamSynchronize(c->stream));
+    if (got & kTrwInvalid) return fail(c, PHIMVS_E_ARG, invalid);
+    if (!got) return PHIMVS_OK;
+  }
+  // a small or narrow graph, infinite energies, or no device memory for a large graph: the GPU
+  // gathers the nodes' inputs (depth, 4 hypotheses, 4 costs) and the host decodes
+  (void)hipGetLastError();  // of an allocation that failed
   float* half = c->io_a.p;
   float* dec_d = c->io_a.p + 9 * n2;
   HIPCHECK(c, launch_phi_half(depth, hyp, cost, W, H, half, c->stream));
@@ -1483,13 +1504,9 @@ int phimvs_phi_select(phimvs_ctx* c, int width, int height, const float* depth, 
   rc = phimvs_phi_decode_host(W2, H2, h.data(), h.data() + n2, h.data() + 5 * n2, p.k1, p.k2, p.k3, PHIMVS_COST_MAX,
                               p.iterations, lab.data(), dec.data());
   if (rc == PHIMVS_E_OOM) return fail(c, rc, "out of host memory in the graph-model decoder");
-  if (rc == PHIMVS_E_UNSUPPORTED) return fail(c, rc, "graph model too large for the decoder (2^27 nodes or more)");
-  if (rc != PHIMVS_OK)
-    return fail(c, PHIMVS_E_ARG,
-                "invalid PHI parameters or costs (k1 > 0, k2 > 0, k3 > 1, iterations >= 0, cost <= C_max + k1 k2)");
-  // back to full size in the kernel: pixel (x, y) reads node (x / 2, y / 2)
+  if (rc != PHIMVS_OK) return fail(c, PHIMVS_E_ARG, invalid);
   HIPCHECK(c, hipMemcpyAsync(dec_d, dec.data(), n2 * sizeof(float), hipMemcpyHostToDevice, c->stream));
-  HIPCHECK(c, launch_phi_select(depth, hyp, dec_d, W, H, depth_out, c->stream));
+  HIPCHECK(c, launch_phi_select(depth, hyp, dec_d, W, H, nullptr, depth_out, c->stream));
   HIPCHECK(c, hipStreamSynchronize(c->stream));  // the host copy of the decoded map goes out of scope
   return PHIMVS_OK;
 }

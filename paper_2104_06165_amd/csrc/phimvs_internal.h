@@ -213,9 +213,34 @@ hipError_t launch_phi_mask_cost(const float* hyp, size_t n, float cmax, float* c
 // cost planes, one after the other in half (9 (W+1)/2 (H+1)/2 floats)
 hipError_t launch_phi_half(const float* depth, const float* hyp, const float* cost, int W, int H, float* half,
                            hipStream_t st);
-// dec: the decoded half-size depth ((W+1)/2 x (H+1)/2)
-hipError_t launch_phi_select(const float* depth, const float* hyp, const float* dec, int W, int H, float* out,
-                             hipStream_t st);
+// the graph model's buffers on the GPU: W x H nodes in NB bands of rows, S steps per band,
+// `positions` places of the skewed layout (4 values per node and array, 16 per edge)
+struct TrwBuffers {
+  int W, H, NB, S;
+  int64_t positions;
+  double* er;                   // energies of the edges to the right and down, [state][neighbour's state]
+  double* ed;
+  double* un;                   // unary terms, +inf where there is no state
+  double* msg[4];               // messages from up, left, right, down
+  float* val;                   // depth of each state
+  int* info;
+  double* gamma;                // weight of a belief: 1 or 1/2
+  double* edge;                 // from band to band: [receiving band in sweep order][step][state]
+  unsigned long long* ticket;
+  int* flag;                    // kTrw... bits
+};
+bool trw_on_gpu(int W2, int H2);    // whether the GPU is the faster decoder of W2 x H2 nodes
+size_t trw_words(int W2, int H2);  // 64-bit words of scratch for W2 x H2 nodes
+// what the device flag reports: a potential that is not positive; a unary term that is infinite,
+// which the host decodes
+constexpr int kTrwInvalid = 1, kTrwInfinite = 2;
+// decodes the half-size graph of full-size maps into dec (W2 H2)
+hipError_t launch_trw(const float* depth, const float* hyp, const float* cost, int W, int H, double k1, double k2,
+                      double k3, double cost_max, int iterations, uint64_t* words, float* dec, int** flag, hipStream_t st);
+// dec: the decoded half-size depth ((W+1)/2 x (H+1)/2); skip: nullptr, or a device flag that, set,
+// leaves out as it is
+hipError_t launch_phi_select(const float* depth, const float* hyp, const float* dec, int W, int H, const int* skip,
+                             float* out, hipStream_t st);
 hipError_t launch_phi_normals(const float* depth, int W, int H, const PhiCam& cam, float* normal, hipStream_t st);
 
 // a view of a context's scene, for the proposal network's host code

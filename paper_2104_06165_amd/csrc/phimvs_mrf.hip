@@ -1,7 +1,7 @@
 // Host-side selection step of plane hypothesis inference (PHI-MVS Sec. III-E): the
 // pairwise undirected graph model over a 4-connected pixel grid, decoded by sequential
 // tree-reweighted message passing (TRW-S, Kolmogorov 2006).  The paper runs this part on
-// the CPU; so does the library.  Potentials: node states are a pixel's depth hypotheses
+// the CPU; the library does so for small graphs (phimvs_trw.hip has the others).  Potentials: node states are a pixel's depth hypotheses
 // with phi_n = (C_max - C) / k1 + k2 (Eq. 7), pixels that already have depth are fixed
 // single-state nodes (phi = 1), edges carry phi_e = [k3 - min(1, relative difference)]^2
 // (Eq. 8); decoding maximises the product, i.e. minimises the sum of -log potentials.

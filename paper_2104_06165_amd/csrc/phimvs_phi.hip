@@ -184,7 +184,9 @@ __global__ void phi_half_kernel(const float* __restrict__ depth, const float* __
 // each pixel without depth takes the hypothesis closest to the reference map: the decoded
 // half-size depth dec, pixel (x, y) reading node (x / 2, y / 2)
 __global__ void phi_select_kernel(const float* __restrict__ depth, const float* __restrict__ hyp,
-                                  const float* __restrict__ dec, int W, int H, int W2, float* __restrict__ out) {
+                                  const float* __restrict__ dec, int W, int H, int W2, const int* skip,
+                                  float* __restrict__ out) {
+  if (skip && *skip) return;
   const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y;
   if (x >= W || y >= H) return;
   const size_t p = (size_t)y * W + x, plane = (size_t)W * H;
@@ -318,11 +320,11 @@ hipError_t launch_phi_half(const float* depth, const float* hyp, const float* co
   return hipGetLastError();
 }
 
-hipError_t launch_phi_select(const float* depth, const float* hyp, const float* dec, int W, int H, float* out,
-                             hipStream_t st) {
+hipError_t launch_phi_select(const float* depth, const float* hyp, const float* dec, int W, int H, const int* skip,
+                             float* out, hipStream_t st) {
   const int W2 = (W + 1) / 2;
   hipLaunchKernelGGL(pmp::phi_select_kernel, dim3((W + 255) / 256, H), dim3(256), 0, st, depth, hyp, dec, W, H, W2,
-                     out);
+                     skip, out);
   return hipGetLastError();
 }
 

@@ -1,0 +1,87 @@
+"""The hypothesis selection's graph model on the GPU: bands of 32 rows walked by one wave each,
+chunks of 16 columns between them.  Against the oracle's plain sequential decoder, bitwise, at
+the edges of bands and chunks and on both sides of the rule that leaves small graphs to the
+host (nodes >= 20 steps); refusals and infinite potentials as with the host's decoder."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2104_06165_amd as pm  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = pm.Context(0)
+    yield c
+    c.close()
+
+
+def maps(W, H, kind, seed):
+    """depth (H, W), hyp and cost (4, H, W): continuous values, or few values (ties)."""
+    r = np.random.default_rng(seed)
+    few = kind == "few"
+    value = (lambda s: r.integers(4, 8, s)) if few else (lambda s: r.uniform(2, 6, s))
+    d = np.where(r.uniform(size=(H, W)) < 0.4, value((H, W)), 0.0).astype(np.float32)
+    h = np.where(r.uniform(size=(4, H, W)) < 0.75, value((4, H, W)), 0.0).astype(np.float32)
+    c = (0.5 * r.integers(0, 4, h.shape) if few else r.uniform(0, 2, h.shape)).astype(np.float32)
+    d[: H // 8, : W // 8] = 0
+    h[:, : H // 8, : W // 8] = 0  # no states at all
+    return d, h, c
+
+
+def select(ctx, d, h, c, **kw):
+    t = [torch.from_numpy(x).cuda() for x in (d, h, c)]
+    return ctx.phi_select(*t, pm.PhiParams(**kw)).cpu().numpy()
+
+
+# full size; the half-size graph is (W + 1) // 2 x (H + 1) // 2.  One band, one whole band, a row
+# more; whole chunks of steps and one more or less; wide, tall, many bands; left to the host
+SIZES = [(127, 61), (128, 64), (98, 66), (131, 65), (129, 128), (226, 194), (225, 191), (1601, 131), (160, 1279),
+         (62, 66), (700, 12)]
+
+
+@pytest.mark.parametrize("kind", ["any", "few"])
+@pytest.mark.parametrize("W,H", SIZES)
+def test_selection_is_the_oracles(ctx, W, H, kind):
+    d, h, c = maps(W, H, kind, W + H)
+    for it in (0, 1, 5):
+        print(f"selection {W} x {H}, {kind}, {it} iterations", flush=True)
+        g = select(ctx, d, h, c, iterations=it)
+        o = oracle.phi_select(d, h.transpose(1, 2, 0), c.transpose(1, 2, 0), iterations=it)
+        assert np.array_equal(g, o)
+
+
+def test_refused_and_infinite_potentials(ctx):
+    """A potential that is not positive refuses the call and leaves the output alone; an infinite
+    potential or an infinite edge energy decodes as on the host."""
+    W, H = 200, 192
+    d, h, c = maps(W, H, "any", 3)
+    free = np.argwhere((d[::2, ::2] <= 0) & (h[1, ::2, ::2] > 0))
+    y, x = 2 * free[len(free) // 2]
+    for cost in (2.5, np.nan):
+        bad = c.copy()
+        bad[1, y, x] = cost
+        with pytest.raises(pm.PhimvsError):
+            select(ctx, d, h, bad)
+    t = [torch.from_numpy(a).cuda() for a in (d, h, bad)]
+    out = torch.full((H, W), -7.0, device="cuda")
+    p = pm._PhiParams(1.0, 0.1, 2.0, 8)
+    rc = pm.lib().phimvs_phi_select(ctx.h, W, H, *[a.data_ptr() for a in t], pm.C.byref(p), out.data_ptr())
+    assert rc != 0 and bool((out == -7.0).all())
+    inf = c.copy()
+    inf[1, y, x] = -np.inf
+    for cost, k3 in ((inf, 2.0), (c, 1e200), (c, 1e100)):
+        lab, dec = pm.phi_decode_host(d[::2, ::2].copy(), h[:, ::2, ::2].copy(), cost[:, ::2, ::2].copy(),
+                                      pm.PhiParams(k3=k3))
+        ref = dec[np.arange(H)[:, None] // 2, np.arange(W)[None, :] // 2].astype(np.float64)
+        dist = np.where(h > 0, np.abs(h.astype(np.float64) - ref), np.inf)
+        best = np.take_along_axis(h, dist.argmin(0)[None], 0)[0]
+        want = np.where(d > 0, d, np.where((ref > 0) & np.isfinite(dist.min(0)), best, 0.0)).astype(np.float32)
+        assert np.array_equal(select(ctx, d, h, cost, k3=k3), want)
