@@ -318,10 +318,10 @@ def bench_phi(ctx, mv, jobs, outs, size=None):
     """Plane hypothesis inference (Sec. III-E) on the references (of one size class if
     given): each depth map is filtered by geometric consistency against the other
     references among its sources, its empty pixels get hypotheses, costs, a selection (graph
-    model decoded on the host) and normals, and the filled maps are filtered again against
+    model) and normals, and the filled maps are filtered again against
     each other.  Reported: completeness (pixels with depth) and accuracy against the
-    rendered depth at each stage, the GPU time of hypotheses + costs + normals and the host
-    time of the selection."""
+    rendered depth at each stage, the GPU time of hypotheses + costs + normals and the
+    time of the selection (host_selection_ms; small graphs are decoded on the host)."""
     import torch
 
     import paper_2104_06165_amd as pm

@@ -929,7 +929,7 @@ __global__ __launch_bounds__(128) void cand_prop_kernel(const Job* __restrict__ 
 // that is left empty itself equals what that one equals, so comparing with the candidates as
 // computed gives the same result.
 // A launch over 160 x 120 pixels takes 7.5 us in place of 20.5, where the one-thread form is a chain
-// of eight such steps; the map's time goes from 885 to 786 us (8 iterations, 16 lanes per pixel).
+// of eight such steps; the map's time goes from 885 to 786 us (3 iterations, 16 lanes per pixel).
 constexpr int kPropPx = 64;
 __global__ __launch_bounds__(8 * kPropPx) void cand_prop_split_kernel(const Job* __restrict__ jobs, Launch L) {
   __shared__ float4 fresh[8][kPropPx], old[8][kPropPx];
