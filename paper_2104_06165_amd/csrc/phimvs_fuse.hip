@@ -13,11 +13,12 @@
 // All results are FP64 evaluations of the expressions in the order written (back_project,
 // project_round, the squared distance).  The tests bound the work: FP64 instructions, about
 // 200 for a pixel and a later map in that form (two camera chains through the world and two
-// divisions).  They are decided by a shorter one, X_j = d A (x, y, 1) + t with A = R_j R_i^T
-// K_i^-1 from a table and the distance taken in camera j, together with a bound of the
-// difference between the two; a lane whose test lies within that bound of the other
-// outcome (a rounding boundary of the pixel position, the distance limit) takes the
-// expressions as written, so the decisions are theirs.  Nine 961 x 640 maps (5.5 M pixels):
+// divisions).  They are decided by a shorter one, the same products in another order from
+// tables (a pixel's position on image j; its point in the world, where the distance is taken:
+// nothing is assumed of the rotations, which need not be orthonormal to the last digit),
+// together with a bound of the difference between the two; a lane whose test lies within that
+// bound of the other outcome (a rounding boundary of the pixel position, the distance limit)
+// takes the expressions as written, so the decisions are theirs.  Nine 961 x 640 maps (5.5 M pixels):
 // 422 us with both launches in every step (init 47, claims refilled 64, claim 142, merge 154 us)
 // and the written form throughout, 302 us so (init 12, claim 181, merge 84 us: the merge issues
 // FP64 on 75% of its cycles; the first claim launch, 50 us, has 18 us of atomics, which memory
@@ -62,23 +63,23 @@ __device__ __forceinline__ bool project_round(const FuseMap& m, const double* Xw
 }
 
 // ---------------------------------------------------------------------------- the short form
-// Pair (i, j): pixel (x, y) of map i at depth d is X = d A (x, y, 1) + t in camera j and p = d P
-// (x, y, 1) + s on its image, A = R_j R_i^T K_i^-1, t = t_j - R_j R_i^T t_i, P = K_j A, s = K_j t.
-// A point differs between the two forms by at most delta = c0 + c1 d in any coordinate: 512 x
-// 2^-53 of the magnitudes that enter (the forms are a few 3-term products of them, each within
-// a few units), and p by kn delta with kn the row's sum of magnitudes in K_j, counted four
-// times here.  cu and cv bound the position's share of that for positions inside image j or
-// within a pixel of it, eu and ev the quotient's own rounding.
+// Pair (i, j): pixel (x, y) of map i at depth d is p = d P (x, y, 1) + s on image j, P = K_j A, s =
+// K_j t, A = R_j R_i^T K_i^-1, t = t_j - R_j R_i^T t_i.  A point in camera j differs between the two
+// forms by at most delta = c0 + c1 d in any coordinate: 512 x 2^-53 of the magnitudes that enter
+// (the forms are a few 3-term products of them, each within a few units), and p by kn delta with
+// kn the row's sum of magnitudes in K_j, counted four times here.  cu and cv bound the position's
+// share of that for positions inside image j or within a pixel of it, eu and ev the quotient's
+// own rounding.  The way to the world (FuseMap's B, w, e0, e1) is bounded in the same way.
 __device__ void make_pair(const FuseMap& a, const FuseMap& b, FusePair& o) {
-  double R[9], kn[3];
+  double R[9], A[9], t[3], kn[3];
   for (int r = 0; r < 3; ++r)
     for (int c = 0; c < 3; ++c)
       R[3 * r + c] = b.R[3 * r] * a.R[3 * c] + b.R[3 * r + 1] * a.R[3 * c + 1] + b.R[3 * r + 2] * a.R[3 * c + 2];
   double ray = 0.0, ti = 0.0, tj = 0.0;
   for (int r = 0; r < 3; ++r) {
     for (int c = 0; c < 3; ++c)
-      o.A[3 * r + c] = R[3 * r] * a.Kinv[c] + R[3 * r + 1] * a.Kinv[3 + c] + R[3 * r + 2] * a.Kinv[6 + c];
-    o.t[r] = b.t[r] - (R[3 * r] * a.t[0] + R[3 * r + 1] * a.t[1] + R[3 * r + 2] * a.t[2]);
+      A[3 * r + c] = R[3 * r] * a.Kinv[c] + R[3 * r + 1] * a.Kinv[3 + c] + R[3 * r + 2] * a.Kinv[6 + c];
+    t[r] = b.t[r] - (R[3 * r] * a.t[0] + R[3 * r + 1] * a.t[1] + R[3 * r + 2] * a.t[2]);
     ray += fabs(a.Kinv[3 * r]) * a.W + fabs(a.Kinv[3 * r + 1]) * a.H + fabs(a.Kinv[3 * r + 2]);
     ti += fabs(a.t[r]);
     tj += fabs(b.t[r]);
@@ -86,8 +87,8 @@ __device__ void make_pair(const FuseMap& a, const FuseMap& b, FusePair& o) {
   }
   for (int r = 0; r < 3; ++r) {
     for (int c = 0; c < 3; ++c)
-      o.P[3 * r + c] = b.K[3 * r] * o.A[c] + b.K[3 * r + 1] * o.A[3 + c] + b.K[3 * r + 2] * o.A[6 + c];
-    o.s[r] = b.K[3 * r] * o.t[0] + b.K[3 * r + 1] * o.t[1] + b.K[3 * r + 2] * o.t[2];
+      o.P[3 * r + c] = b.K[3 * r] * A[c] + b.K[3 * r + 1] * A[3 + c] + b.K[3 * r + 2] * A[6 + c];
+    o.s[r] = b.K[3 * r] * t[0] + b.K[3 * r + 1] * t[1] + b.K[3 * r + 2] * t[2];
   }
   o.c0 = 512.0 * 0x1p-53 * (ti + tj);
   o.c1 = 512.0 * 0x1p-53 * ray;
@@ -174,7 +175,11 @@ __global__ __launch_bounds__(kBlock) void fuse_claim_kernel(const FuseMap* __res
   const float df = mi.depth[p];
   if (!(df > 0.0f) || claim[g] != kFree) return;
   const double d = df, px = (double)x, py = (double)y;
-  const double lim = tau * d, lim2 = lim * lim;
+  const double lim = tau * d, lim2 = lim * lim, ei = __builtin_fma(mi.e1, d, mi.e0);
+  double Xs[3];  // the pixel's point
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+    Xs[r] = __builtin_fma(d, __builtin_fma(mi.B[3 * r], px, __builtin_fma(mi.B[3 * r + 1], py, mi.B[3 * r + 2])), mi.w[r]);
   uint32_t bits = 0;
   // kGroup maps at a time, so that their gathers are in flight together and no gather waits
   // for an atomic of the map before
@@ -214,23 +219,19 @@ __global__ __launch_bounds__(kBlock) void fuse_claim_kernel(const FuseMap* __res
       pass[k] = false;
       if (!found[k] || !(dq[k] > 0.0f) || cl[k] < (uint64_t)g) continue;
       const FuseMap& mj = maps[j0 + k];
-      const FusePair& P = row[j0 + k];
       if (found[k] == 1) {
-        // the candidate's point in camera j
+        // the candidate's point
         const double dd = dq[k], qxd = (double)qx[k], qyd = (double)qy[k];
-        double e2 = 0.0, mag = 0.0;
+        double e2 = 0.0;
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
-          const double X =
-              __builtin_fma(d, __builtin_fma(P.A[3 * r], px, __builtin_fma(P.A[3 * r + 1], py, P.A[3 * r + 2])), P.t[r]);
-          const double Y =
-              dd * __builtin_fma(mj.Kinv[3 * r], qxd, __builtin_fma(mj.Kinv[3 * r + 1], qyd, mj.Kinv[3 * r + 2]));
-          const double e = Y - X;
-          mag += fabs(Y);
+          const double Y = __builtin_fma(
+              dd, __builtin_fma(mj.B[3 * r], qxd, __builtin_fma(mj.B[3 * r + 1], qyd, mj.B[3 * r + 2])), mj.w[r]);
+          const double e = Y - Xs[r];
           e2 = __builtin_fma(e, e, e2);
         }
         // both points through both forms; |e| is near lim where it matters, or below 21 dl
-        const double dl = 2.0 * __builtin_fma(P.c1, d, P.c0) + 512.0 * 0x1p-53 * mag;
+        const double dl = ei + __builtin_fma(mj.e1, dd, mj.e0);
         const double m = 64.0 * dl * lim + 0x1p-40 * lim2 + 512.0 * dl * dl;
         pass[k] = e2 < lim2;
         if (!(fabs(e2 - lim2) > m)) found[k] = 2;

@@ -1366,6 +1366,15 @@ int phimvs_fuse(phimvs_ctx* c, int n_maps, const phimvs_depth_map* maps, const p
     for (int i = 0; i < 9; ++i) f.K[i] = V.K[i], f.R[i] = V.R[i];
     for (int i = 0; i < 3; ++i) f.t[i] = V.t[i];
     if (!inv33(V.K, f.Kinv)) return fail(c, PHIMVS_E_ARG, "singular K");
+    double ray = 0.0;
+    for (int r = 0; r < 3; ++r) {
+      ray += std::fabs(f.Kinv[3 * r]) * V.W + std::fabs(f.Kinv[3 * r + 1]) * V.H + std::fabs(f.Kinv[3 * r + 2]);
+      f.e0 += 512.0 * 0x1p-53 * std::fabs(f.t[r]);
+      for (int q = 0; q < 3; ++q)
+        f.B[3 * r + q] = f.R[r] * f.Kinv[q] + f.R[3 + r] * f.Kinv[3 + q] + f.R[6 + r] * f.Kinv[6 + q];
+      f.w[r] = -(f.R[r] * f.t[0] + f.R[3 + r] * f.t[1] + f.R[6 + r] * f.t[2]);
+    }
+    f.e1 = 512.0 * 0x1p-53 * ray;
     f.W = V.W;
     f.H = V.H;
     f.off = total;

@@ -178,14 +178,16 @@ hipError_t launch_filter(const FilterArgs& a, hipStream_t st);
 // depth-map fusion: one map's camera and depth, at offset `off` of the concatenated pixels
 struct FuseMap {
   double K[9], Kinv[9], R[9], t[3];
+  // the short form of the way to the world, d B (x, y, 1) + w with B = R^T K^-1 and w = -R^T t; a
+  // coordinate of it differs from the written-out form's by less than e0 + e1 d
+  double B[9], w[3], e0, e1;
   int W, H;
   int64_t off;
   const float* depth;
 };
-// a pair of maps (i, j > i): pixel of i -> point in camera j (A, t) and image j (P, s), and
-// rounding bounds
+// a pair of maps (i, j > i): pixel of i -> position on image j (P, s), and rounding bounds
 struct FusePair {
-  double A[9], t[3], P[9], s[3];
+  double P[9], s[3];
   double c0, c1, kw, cu, cv, eu, ev;
 };
 size_t fuse_pairs(int n_maps);  // entries of the pair table

@@ -135,3 +135,22 @@ def test_values_that_are_no_numbers():
         for v in (np.nan, np.inf, -np.inf, 1e30):
             x[rng.random(x.shape) < 0.02] = v
     run(K, R, t, d, m)
+
+
+@pytest.mark.parametrize("how,far", [("f32", 1e3), (6, 1e3), (4, 0.0), (4, 1e2), ("scaled", 1e3)])
+def test_rotations_that_are_not_exact(how, far):
+    """The short form is a reordering of the written-out one for any R, orthonormal or not."""
+    rng = np.random.default_rng(18)
+    K, R, t = cams(4, 280.0, (79.5, 59.5))
+    while True:
+        Q = np.linalg.qr(rng.standard_normal((3, 3)))[0]
+        Q, q = Q * np.sign(np.linalg.det(Q)), far * rng.standard_normal(3)
+        for i in range(4):
+            a = 0.05 * (i - 1)
+            Ri = np.array([[np.cos(a), 0, -np.sin(a)], [0, 1, 0], [np.sin(a), 0, np.cos(a)]]) @ Q.T
+            R[i] = Ri.astype(np.float32) if how == "f32" else (Ri * (1 + 2.4e-5 * (i - 1)) if how == "scaled" else Ri.round(how))
+            t[i] = np.array([0.1 * (i - 1), 0.02 * i, 0.0]) - Ri @ q
+        if max(np.abs(r.T @ r - np.eye(3)).max() for r in R) < 0.99e-4:
+            break
+    d, m = maps(rng, 4, 120, 160, tilt=0.3)
+    run(K, R, t, d, m, ref=1)

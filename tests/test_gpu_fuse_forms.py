@@ -101,3 +101,23 @@ def test_depths_that_are_no_numbers():
         m[rng.random(m.shape) < 0.02] = 1e-30
         m[rng.random(m.shape) < 0.02] = 1e30
     run(K, R, t, d, 0.01)
+
+
+# rotations as files hold them: rounded to float32, to a number of decimals, and scaled (all within
+# the 1e-4 that phimvs_set_views grants R^T R); far: the cameras' distance from the world's origin
+@pytest.mark.parametrize("how,far", [("f32", 1e2), ("f32", 1e5), (6, 0.0), (6, 1e3), (4, 0.0), (4, 1e2),
+                                     ("scaled", 0.0), ("scaled", 1e3)])
+def test_rotations_that_are_not_exact(how, far):
+    rng = np.random.default_rng(17)
+    K, R, t = cams(3, 280.0, (159.5, 119.5))
+    while True:
+        Q, q = rot(rng), far * rng.standard_normal(3)
+        for i in range(3):
+            a = 0.05 * (i - 1)
+            Ri = np.array([[np.cos(a), 0, -np.sin(a)], [0, 1, 0], [np.sin(a), 0, np.cos(a)]]) @ Q.T
+            R[i] = Ri.astype(np.float32) if how == "f32" else (Ri * (1 + 4.9e-5 * (i - 1)) if how == "scaled" else Ri.round(how))
+            t[i] = np.array([0.1 * (i - 1), 0.02 * i, 0.0]) - Ri @ q
+        if max(np.abs(r.T @ r - np.eye(3)).max() for r in R) < 0.99e-4:
+            break
+    # distances spread about the limit
+    run(K, R, t, [noisy(rng, 240, 320, spread=0.006, empty=0.0) for _ in range(3)], 0.01)
