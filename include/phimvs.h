@@ -344,10 +344,11 @@ void phimvs_default_phi_params(phimvs_phi_params* p);
  * empty without hypothesis or reference).  Pixels with depth keep it.  depth, depth_out:
  * device H*W; hyp, cost: device planar 4*H*W.  Graphs with many nodes for their length
  * are decoded on the device (about 450 bytes of the context's scratch per node, and 10
- * floats); small or narrow ones, those whose energies are not all finite and those that
- * device memory does not hold are gathered (9 floats per node), copied to the host and
- * decoded there.  Both take the same FP64 steps; the logarithms are each platform's own.
- * Synchronises the stream.
+ * floats); small or narrow ones, those whose energies are not all finite, those in which
+ * labels of different depth tie to within 2e-13 in energy (which rounding then decides)
+ * and those that device memory does not hold are gathered (9 floats per node), copied to
+ * the host and decoded there.  Both take the same FP64 steps but for the logarithms, which
+ * are each platform's own; the labels are the same.  Synchronises the stream.
  * PHIMVS_E_ARG also for a cost above C_max + k1 k2 at a sampled hypothesis (no positive
  * potential). */
 int phimvs_phi_select(phimvs_ctx* ctx, int width, int height, const float* depth, const float* hyp,

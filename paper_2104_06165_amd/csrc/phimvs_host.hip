@@ -1497,8 +1497,8 @@ int phimvs_phi_select(phimvs_ctx* c, int width, int height, const float* depth, 
     if (got & kTrwInvalid) return fail(c, PHIMVS_E_ARG, invalid);
     if (!got) return PHIMVS_OK;
   }
-  // a small or narrow graph, infinite energies, or no device memory for a large graph: the GPU
-  // gathers the nodes' inputs (depth, 4 hypotheses, 4 costs) and the host decodes
+  // a small or narrow graph, infinite energies, labels that hang on rounding, or no device memory
+  // for a large graph: the GPU gathers the nodes' inputs (depth, 4 hypotheses, 4 costs) and the host decodes
   (void)hipGetLastError();  // of an allocation that failed
   float* half = c->io_a.p;
   float* dec_d = c->io_a.p + 9 * n2;

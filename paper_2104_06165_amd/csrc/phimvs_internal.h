@@ -229,13 +229,13 @@ struct TrwBuffers {
   double* gamma;                // weight of a belief: 1 or 1/2
   double* edge;                 // from band to band: [receiving band in sweep order][step][state]
   unsigned long long* ticket;
-  int* flag;                    // kTrw... bits
+  int* flag;                    // kTrw... bits; behind them the largest unary term above 4, as a float
 };
 bool trw_on_gpu(int W2, int H2);    // whether the GPU is the faster decoder of W2 x H2 nodes
 size_t trw_words(int W2, int H2);  // 64-bit words of scratch for W2 x H2 nodes
 // what the device flag reports: a potential that is not positive; a unary term that is infinite,
-// which the host decodes
-constexpr int kTrwInvalid = 1, kTrwInfinite = 2;
+// labels that tie to within rounding, both of which the host decodes
+constexpr int kTrwInvalid = 1, kTrwInfinite = 2, kTrwTie = 4;
 // decodes the half-size graph of full-size maps into dec (W2 H2)
 hipError_t launch_trw(const float* depth, const float* hyp, const float* cost, int W, int H, double k1, double k2,
                       double k3, double cost_max, int iterations, uint64_t* words, float* dec, int** flag, hipStream_t st);

@@ -1,8 +1,9 @@
 // Selection step of plane hypothesis inference on the GPU (PHI-MVS Sec. III-E): the graph
 // model of phimvs_mrf.hip (node states, potentials, sequential tree-reweighted message passing
 // in raster order, labelling in raster order), with the same FP64 operations in the same order
-// per node, so the labels are the host decoder's (the logarithms are each platform's own: an
-// ulp of an energy can only tell labels apart that tie to within rounding).
+// per node.  Only the logarithms are each platform's own (3% of them differ, by an ulp), which
+// can tell apart labels that tie to within rounding; where a node has such a tie the result is
+// not used and the host decodes (trw_ties_kernel), so the labels are the host decoder's.
 //
 // A node of a forward sweep needs its left and upper neighbours of the same sweep, so W + H - 1
 // steps follow one another: a sweep is a chain, and what bounds it is the time of a step.  One
@@ -27,6 +28,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "phimvs_internal.h"
 
@@ -50,6 +52,10 @@ __device__ __forceinline__ double edge_energy(double h1, double h2, double k3) {
   const double m = rel < 1.0 ? rel : 1.0;
   return -log((k3 - m) * (k3 - m));
 }
+
+// labels within this of each other (for up to 8 iterations, and times the largest energy, taken to
+// be at least kTieScale) are left to the host (trw_ties_kernel)
+constexpr double kTieGap = 4e-14, kTieScale = 4.0;
 
 // info of a node: its states (3 bits), whether its upper and left neighbours have any
 constexpr int kLiveUp = 8, kLiveLeft = 16;
@@ -110,6 +116,7 @@ __global__ __launch_bounds__(256) void trw_setup_kernel(Nodes g, TrwBuffers B, d
       un = -log(phi);
       if (!(phi > 0.0)) atomicOr(B.flag, kTrwInvalid);
       else if (!(fabs(un) < __builtin_inf())) atomicOr(B.flag, kTrwInfinite);
+      else if (fabs(un) > kTieScale) atomicMax(B.flag + 1, __float_as_int((float)fabs(un)));
     }
     float w[4];
     const int up = node_states(g, B.W, B.H, X, Y - 1, w), left = node_states(g, B.W, B.H, X - 1, Y, w);
@@ -347,6 +354,90 @@ __global__ __launch_bounds__(2 * kRows) void trw_sweep_kernel(TrwBuffers B, int 
   }
 }
 
+// Whether the labels hang on rounding.  The energies here and on the host differ by an ulp of a
+// logarithm; the messages then by 1e-15 of the largest energy after 8 iterations and by up to 1e-14
+// of it after 200 (measured on the CPU, one-ulp changes of every energy, k3 from 1 + 1e-7 to 1000).
+// So a node decides alike in both unless another state's energy lies within kTieGap times that
+// energy (at least 4, the common potentials' 2.3 among them) of the least, 40 times what was
+// measured.  Left out: states of the same depth (the label does not show), and states that nothing
+// tells apart in either: the same cost, and what the neighbours contribute goes through equal
+// relative distances (saturated ones as a rule), so they tie exactly in both.  What remains in
+// filled 1600 x 1066 maps are hypotheses that agree to six digits: one map of 80 went to the host.
+// One quad of lanes per position, lane l: state l.  23 us at 1600 x 1066.
+__device__ __forceinline__ double edge_distance(double h1, double h2) {
+  const double rel = h1 > h2 ? (h1 - h2) / h2 : (h2 - h1) / h1;
+  return rel < 1.0 ? rel : 1.0;
+}
+__device__ float state_cost(const Nodes& g, int X, int Y, int l) {
+  const size_t p = (size_t)(2 * Y) * g.W + 2 * X, plane = (size_t)g.W * g.H;
+  int i = 0;
+  for (int k = 0; k < 4; ++k)
+    if (g.hyp[k * plane + p] > 0.0f && i++ == l) return g.cost[k * plane + p];
+  return 0.0f;
+}
+__global__ __launch_bounds__(256) void trw_ties_kernel(Nodes g, TrwBuffers B, double gap, double scale, bool sent,
+                                                       const float* __restrict__ dec) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, at = t >> 2;
+  if (at >= B.positions) return;  // whole quads
+  const int l = (int)threadIdx.x & 3;
+  const int r = (int)(at % kRows);
+  const int64_t bs = at / kRows;
+  const int X = (int)(bs % B.S) - r, Y = (int)(bs / B.S) * kRows + r;
+  const int info = B.info[at], n = info & 7;
+  if (n < 2) return;
+  // the state a node took: the first of its depth (states of one depth have the same edges)
+  auto taken = [&](int64_t a, int x, int y) {
+    const float d = dec[(size_t)y * B.W + x];
+    int k = 0;
+    while (k < 3 && B.val[4 * a + k] != d) ++k;
+    return k;
+  };
+  double e = B.un[t];
+  const int64_t above = r > 0 ? at - kRows - 1 : at - ((int64_t)B.S - kRows + 1) * kRows + kRows - 1;
+  if (info & kLiveUp) e += B.ed[16 * above + 4 * taken(above, X, Y - 1) + l];
+  if (info & kLiveLeft) e += B.er[16 * (at - kRows) + 4 * taken(at - kRows, X - 1, Y) + l];
+  e = (e + B.msg[2][t]) + B.msg[3][t];
+  const float v = B.val[t];
+  const int p = taken(at, X, Y);
+  const double ep = __shfl(e, p, 4);
+  const float vp = __shfl(v, p, 4);
+  const double near = gap * fmax(scale, (double)__int_as_float(B.flag[1]));
+  if (l >= n || v == vp || fabs(e - ep) > near) return;
+  bool differs = state_cost(g, X, Y, l) != state_cost(g, X, Y, p);
+  float w[4] = {0.f, 0.f, 0.f, 0.f};
+  if (info & kLiveUp) {
+    node_states(g, B.W, B.H, X, Y - 1, w);
+    const float u = w[taken(above, X, Y - 1)];
+    differs = differs || edge_distance(v, u) != edge_distance(vp, u);
+  }
+  if (info & kLiveLeft) {
+    node_states(g, B.W, B.H, X - 1, Y, w);
+    const float u = w[taken(at - kRows, X - 1, Y)];
+    differs = differs || edge_distance(v, u) != edge_distance(vp, u);
+  }
+  // the last messages from the right and from below: every state there that is, or nearly is, the
+  // least for either state here has to lie at the same distance from both
+  for (int d = 2; d < 4 && sent; ++d) {
+    const int m = node_states(g, B.W, B.H, X + (d == 2), Y + (d == 3), w);
+    const int64_t a = d == 2 ? at + kRows : (r < kRows - 1 ? at + kRows + 1 : at + ((int64_t)B.S - kRows + 1) * kRows - kRows + 1);
+    double to_l[4], to_p[4], least_l = __builtin_inf(), least_p = __builtin_inf();
+    for (int k = 0; k < m; ++k) {
+      const int64_t q = 4 * a + k;
+      const double back = B.msg[d == 2 ? 1 : 0][q];
+      const double sends = B.gamma[a] * ((((B.un[q] + B.msg[0][q]) + B.msg[1][q]) + B.msg[2][q]) + B.msg[3][q]) - back;
+      const double* e = (d == 2 ? B.er : B.ed) + 16 * at + k;
+      to_l[k] = sends + e[4 * l];
+      to_p[k] = sends + e[4 * p];
+      least_l = fmin(least_l, to_l[k]);
+      least_p = fmin(least_p, to_p[k]);
+    }
+    for (int k = 0; k < m; ++k)
+      if (to_l[k] <= least_l + near || to_p[k] <= least_p + near)
+        differs = differs || edge_distance(v, w[k]) != edge_distance(vp, w[k]);
+  }
+  if (differs) atomicOr(B.flag, kTrwTie);
+}
+
 }  // namespace pmt
 
 namespace phimvs_internal {
@@ -428,6 +519,10 @@ hipError_t launch_trw(const float* depth, const float* hyp, const float* cost, i
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(pmt::trw_sweep_kernel<2>, grid, block, 0, st, B, sweep, dec);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const double edge = 2.0 * std::max(std::fabs(std::log(k3 - 1.0)), std::log(k3));  // the largest of an edge
+  hipLaunchKernelGGL(pmt::trw_ties_kernel, dim3((unsigned)((4 * B.positions + 255) / 256)), dim3(256), 0, st, g, B,
+                     pmt::kTieGap * std::max(1.0, iterations / 8.0), std::max(pmt::kTieScale, edge), iterations > 0, dec);
   return hipGetLastError();
 }
 

@@ -85,3 +85,32 @@ def test_refused_and_infinite_potentials(ctx):
         best = np.take_along_axis(h, dist.argmin(0)[None], 0)[0]
         want = np.where(d > 0, d, np.where((ref > 0) & np.isfinite(dist.min(0)), best, 0.0)).astype(np.float32)
         assert np.array_equal(select(ctx, d, h, cost, k3=k3), want)
+
+
+def test_labels_that_tie_to_within_rounding(ctx):
+    """Two states whose energies are equal but for the rounding of their logarithms (potentials in
+    the ratio of 1 to 4 edges' potentials): the host's logarithms decide, whatever the size."""
+    W = H = 256
+    n2 = W // 2
+    Y, X = np.mgrid[:n2, :n2]
+    for seed in range(60):
+        r = np.random.default_rng(seed)
+        s = np.float32(r.uniform(0.5, 3))
+        fixed = ((X + Y) % 2 == 0) & (r.random((n2, n2)) < 0.7)
+        f = np.pad(fixed, 1).astype(int)
+        m = f[:-2, 1:-1] + f[2:, 1:-1] + f[1:-1, :-2] + f[1:-1, 2:]
+        free = ((X + Y) % 2 == 1) & (m > 0)
+        # edges of (2 - 1/2)^2 and (2 - 1/4)^2 to each of m fixed nodes, potentials 49^m and 36^m
+        k = 2.0 ** -np.ceil(np.log2(49.0**m)) * 2.0 ** -r.integers(0, 6, (n2, n2))
+        d, h, c = np.zeros((H, W), np.float32), np.zeros((4, H, W), np.float32), np.zeros((4, H, W), np.float32)
+        d[::2, ::2] = np.where(fixed, 4 * s, 0)
+        for i, (v, base) in enumerate(((6 * s, 49.0), (5 * s, 36.0))):
+            h[i, ::2, ::2] = np.where(free, v, 0)
+            c[i, ::2, ::2] = 2 - base**m * k
+        p = dict(k1=float(r.uniform(0.3, 3)), k2=1e-300, iterations=int(r.integers(0, 4)))
+        _, dec = pm.phi_decode_host(d[::2, ::2].copy(), h[:, ::2, ::2].copy(), c[:, ::2, ::2].copy(), pm.PhiParams(**p))
+        ref = dec[np.arange(H)[:, None] // 2, np.arange(W)[None, :] // 2].astype(np.float64)
+        dist = np.where(h > 0, np.abs(h.astype(np.float64) - ref), np.inf)
+        best = np.take_along_axis(h, dist.argmin(0)[None], 0)[0]
+        want = np.where(d > 0, d, np.where((ref > 0) & np.isfinite(dist.min(0)), best, 0.0)).astype(np.float32)
+        assert np.array_equal(select(ctx, d, h, c, **p), want), seed
