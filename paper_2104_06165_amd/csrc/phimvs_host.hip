@@ -923,10 +923,10 @@ static void free_views(phimvs_ctx* c) {
 }
 
 // The scene's arrays, in the old scene's where an array holds at most twice the pixels (going
-// from scene to scene allocates nothing), and the images through one staging buffer: rows of
-// host memory go over as they lie, padding included, when that is at most twice the image
-// (row by row the copies of 1600 x 1066 images took most of the call); device images are read
-// where they are.
+// from scene to scene allocates nothing), and the images through one staging buffer in one copy
+// each (row by row the copies of 1600 x 1066 images took most of the call); rows of host memory
+// that do not follow each other are packed first, since only the rows are the caller's to give.
+// Device images are read where they are.
 static int take_views(phimvs_ctx* c, int n_views, const phimvs_image* images, const double* K, const double* R,
                       const double* t, const double* depth_range) {
   std::vector<ViewData> old;
@@ -945,9 +945,7 @@ static int take_views(phimvs_ctx* c, int n_views, const phimvs_image* images, co
         break;
       }
     }
-    const int64_t stride = images[i].stride_bytes ? images[i].stride_bytes : images[i].width;
-    if (!images[i].on_device)
-      staged = std::max(staged, stride <= 2 * (int64_t)images[i].width ? (size_t)stride * images[i].height : npx);
+    if (!images[i].on_device) staged = std::max(staged, npx);
   }
   for (ViewData& o : old) {
     if (o.plain) (void)hipFree(o.plain);
@@ -955,6 +953,7 @@ static int take_views(phimvs_ctx* c, int n_views, const phimvs_image* images, co
   }
   int rc = staged ? fit(c, c->io_u8, staged) : PHIMVS_OK;
   if (rc) return rc;
+  std::vector<uint8_t> packed;
   for (int i = 0; i < n_views; ++i) {
     const phimvs_image& im = images[i];
     ViewData& v = c->views[i];
@@ -974,13 +973,18 @@ static int take_views(phimvs_ctx* c, int n_views, const phimvs_image* images, co
     int64_t stride = im.stride_bytes ? im.stride_bytes : im.width;
     const uint8_t* src = static_cast<const uint8_t*>(im.data);
     if (!im.on_device) {
-      if (stride <= 2 * (int64_t)v.W) {
-        const size_t bytes = (size_t)stride * (v.H - 1) + v.W;
-        HIPCHECK(c, hipMemcpyAsync(c->io_u8.p, src, bytes, hipMemcpyHostToDevice, c->stream));
-      } else {
-        HIPCHECK(c, hipMemcpy2DAsync(c->io_u8.p, v.W, src, stride, v.W, v.H, hipMemcpyHostToDevice, c->stream));
+      if (stride != v.W) {
+        try {
+          packed.resize(npx);
+        } catch (const std::bad_alloc&) {
+          return fail(c, PHIMVS_E_OOM, "out of host memory for an image's rows");
+        }
+        for (int y = 0; y < v.H; ++y) std::memcpy(packed.data() + (size_t)y * v.W, src + y * stride, v.W);
+        src = packed.data();
         stride = v.W;
       }
+      HIPCHECK(c, hipMemcpyAsync(c->io_u8.p, src, npx, hipMemcpyHostToDevice, c->stream));
+      if (src == packed.data()) HIPCHECK(c, hipStreamSynchronize(c->stream));  // before it is filled again
       src = c->io_u8.p;
     }
     HIPCHECK(c, launch_build_view(src, stride, v.W, v.H, v.plain, v.quad, c->stream));

@@ -1,0 +1,112 @@
+"""The host side of the library without a GPU: its calls over a stand-in for the HIP runtime
+(hip_stub.cpp: memory with a limit, copies on the host, launches recorded and not run).  Each
+case is a process of its own, in which the stand-in's functions take the runtime's place."""
+import ctypes as C
+import mmap
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+if ROOT not in sys.path:
+    sys.path.insert(0, ROOT)
+
+import paper_2104_06165_amd as pm  # noqa: E402
+
+CASES = {}
+
+
+def case(f):
+    CASES[f.__name__] = f
+    return f
+
+
+class Calls:
+    """A context over the stand-in."""
+
+    def __init__(self, stub):
+        self.stub = stub
+        self.L = pm.lib()
+        self.h = C.c_void_p()
+        assert self.L.phimvs_create(C.byref(self.h), 0, None) == 0
+
+    def err(self):
+        return self.L.phimvs_last_error(self.h).decode()
+
+    def images(self, *sizes):
+        """(width, height) or (width, height, stride, address, on_device)"""
+        ims, keep = (pm._Image * len(sizes))(), []
+        for i, s in enumerate(sizes):
+            if len(s) == 2:
+                a = np.zeros(s[::-1], np.uint8)
+                keep.append(a)
+                s = (*s, 0, a.ctypes.data, 0)
+            ims[i] = pm._Image(s[0], s[1], s[2], 0, s[3], s[4])
+        return ims, keep
+
+    def set_views(self, *sizes, t=None):
+        ims, keep = self.images(*sizes)
+        n = len(sizes)
+        dp = C.POINTER(C.c_double)
+        K = [np.array([[s[0], 0, s[0] / 2], [0, s[0], s[1] / 2], [0, 0, 1.0]]) for s in sizes]
+        arr = [np.ascontiguousarray(a, np.float64) for a in
+               (K, [np.eye(3)] * n, [[0.1 * i, 0, 0] for i in range(n)] if t is None else t, [[2.0, 8.0]] * n)]
+        return self.L.phimvs_set_views(self.h, n, ims, *[a.ctypes.data_as(dp) for a in arr])
+
+    def batch(self, *refs, iters=1, srcs=None):
+        jobs, keep = (pm._Job * len(refs))(), []
+        for i, r in enumerate(refs):
+            s = (C.c_int32 * 1)(*(srcs or [1 if r == 0 else 0]))
+            keep.append(s)
+            jobs[i] = pm._Job(r, s, 1, 7, 1, pm.default_params()._c(), None, None, None)
+        return self.L.phimvs_patchmatch_batch(self.h, len(refs), jobs, iters, 0)
+
+    def patchmatch(self, ref=0, srcs=(1,), iters=1):
+        s = (C.c_int * len(srcs))(*srcs)
+        return self.L.phimvs_patchmatch(self.h, ref, s, len(srcs), 7, 1, iters, None, None, None, None, 1)
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "libhipstub.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-I/opt/rocm/include",
+                    os.path.join(ROOT, "tests", "hip_stub.cpp"), "-o", so], check=True)
+    return so
+
+
+# ---------------------------------------------------------------------------- images
+@case
+def rows_alone_are_read(c):
+    """What lies between an image's rows may belong to someone else: here it cannot be read."""
+    page, W, H = mmap.PAGESIZE, 2 * mmap.PAGESIZE, 5
+    libc = C.CDLL(None, use_errno=True)
+    libc.mmap.restype = C.c_void_p
+    libc.mmap.argtypes = [C.c_void_p, C.c_size_t, C.c_int, C.c_int, C.c_int, C.c_long]
+    libc.mprotect.argtypes = [C.c_void_p, C.c_size_t, C.c_int]
+    for gap in (1, 2, 4):
+        stride = W + gap * page
+        p = libc.mmap(None, H * stride, 3, 0x22, -1, 0)
+        for y in range(H):
+            assert libc.mprotect(p + y * stride + W, gap * page, 0) == 0
+        assert c.set_views((W, H, stride, p, 0), (64, 48)) == 0, c.err()
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_call(stub, name):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), name, stub], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, f"exit status {r.returncode}\n{r.stderr[-3000:]}"
+
+
+if __name__ == "__main__":
+    lib = C.CDLL(sys.argv[2], mode=C.RTLD_GLOBAL)
+    for f, a, res in (("stub_limit", [C.c_size_t], None), ("stub_live", [], C.c_size_t), ("stub_pointers_on", [C.c_int], None),
+                      ("stub_device_syncs", [], C.c_long), ("stub_table_bytes", [], C.c_size_t),
+                      ("stub_forget_launches", [], None), ("stub_launches", [], C.c_size_t),
+                      ("stub_launched", [C.c_size_t], C.c_void_p), ("stub_first", [C.c_size_t], C.c_uint64),
+                      ("hipMalloc", [C.POINTER(C.c_void_p), C.c_size_t], C.c_int)):
+        getattr(lib, f).argtypes = a
+        getattr(lib, f).restype = res
+    CASES[sys.argv[1]](Calls(lib))
