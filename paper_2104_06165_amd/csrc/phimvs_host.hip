@@ -107,12 +107,16 @@ int fail(phimvs_ctx* c, int code, const std::string& msg) {
   return code;
 }
 
+// an error is reported once: the runtime keeps it for the next hipGetLastError, which the next
+// call's launches would take for their own
 #define HIPCHECK(ctx, call)                                                                        \
   do {                                                                                             \
     hipError_t e_ = (call);                                                                        \
-    if (e_ != hipSuccess)                                                                          \
+    if (e_ != hipSuccess) {                                                                        \
+      (void)hipGetLastError();                                                                     \
       return fail(ctx, e_ == hipErrorOutOfMemory ? PHIMVS_E_OOM : PHIMVS_E_DEVICE,                 \
                   std::string(#call) + ": " + hipGetErrorString(e_));                               \
+    }                                                                                              \
   } while (0)
 
 template <typename T>

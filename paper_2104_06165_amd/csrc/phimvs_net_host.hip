@@ -76,9 +76,11 @@ int fail(phimvs_net* n, int code, const std::string& msg) {
 #define NCHECK(net, call)                                                                          \
   do {                                                                                             \
     hipError_t e_ = (call);                                                                        \
-    if (e_ != hipSuccess)                                                                          \
+    if (e_ != hipSuccess) {                                                                        \
+      (void)hipGetLastError();  /* reported once */                                                \
       return fail(net, e_ == hipErrorOutOfMemory ? PHIMVS_E_OOM : PHIMVS_E_DEVICE,                 \
                   std::string(#call) + ": " + hipGetErrorString(e_));                               \
+    }                                                                                              \
   } while (0)
 
 template <typename T>

@@ -94,6 +94,17 @@ def rows_alone_are_read(c):
         assert c.set_views((W, H, stride, p, 0), (64, 48)) == 0, c.err()
 
 
+# ---------------------------------------------------------------------------- errors
+@case
+def errors_are_reported_once(c):
+    """A call that ran out of memory is no reason for the next one to fail."""
+    assert c.set_views((64, 48), (64, 48)) == 0, c.err()
+    c.stub.stub_limit(c.stub.stub_live())
+    assert c.patchmatch() == -4
+    c.stub.stub_limit(1 << 40)
+    assert c.patchmatch() == 0, c.err()
+
+
 @pytest.mark.parametrize("name", sorted(CASES))
 def test_call(stub, name):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), name, stub], capture_output=True, text=True, timeout=300)
