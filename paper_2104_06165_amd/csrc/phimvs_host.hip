@@ -926,19 +926,37 @@ static void free_views(phimvs_ctx* c) {
   c->views.clear();
 }
 
+// whether a kernel of this context may read `bytes` bytes at p: device memory of its own GPU, all
+// within one allocation
+static bool readable_here(const phimvs_ctx* c, const void* p, size_t bytes) {
+  hipPointerAttribute_t a{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  const bool ok = hipPointerGetAttributes(&a, p) == hipSuccess && a.type == hipMemoryTypeDevice && a.device == c->device &&
+                  hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) == hipSuccess &&
+                  static_cast<const char*>(p) + bytes <= static_cast<const char*>(base) + size;
+  (void)hipGetLastError();  // of a pointer the runtime does not know
+  return ok;
+}
+
 // The scene's arrays, in the old scene's where an array holds at most twice the pixels (going
 // from scene to scene allocates nothing), and the images through one staging buffer in one copy
 // each (row by row the copies of 1600 x 1066 images took most of the call); rows of host memory
 // that do not follow each other are packed first, since only the rows are the caller's to give.
-// Device images are read where they are.
+// Images in this GPU's memory are read where they are; what is given as a device pointer and is
+// not (another GPU's, the host's) goes through a copy, which the runtime carries out or refuses.
 static int take_views(phimvs_ctx* c, int n_views, const phimvs_image* images, const double* K, const double* R,
                       const double* t, const double* depth_range) {
   std::vector<ViewData> old;
   old.swap(c->views);
   c->views.resize(n_views);
   size_t staged = 0;
+  std::vector<char> in_place(n_views, 0);
   for (int i = 0; i < n_views; ++i) {
     const size_t npx = (size_t)images[i].width * images[i].height;
+    const int64_t stride = images[i].stride_bytes ? images[i].stride_bytes : images[i].width;
+    in_place[i] = images[i].on_device &&
+                  readable_here(c, images[i].data, (size_t)stride * (images[i].height - 1) + images[i].width);
     const size_t n_old = old.size();
     for (size_t k = 0; k < n_old; ++k) {
       ViewData& o = old[(i + k) % n_old];
@@ -949,7 +967,7 @@ static int take_views(phimvs_ctx* c, int n_views, const phimvs_image* images, co
         break;
       }
     }
-    if (!images[i].on_device) staged = std::max(staged, npx);
+    if (!in_place[i]) staged = std::max(staged, npx);
   }
   for (ViewData& o : old) {
     if (o.plain) (void)hipFree(o.plain);
@@ -976,7 +994,11 @@ static int take_views(phimvs_ctx* c, int n_views, const phimvs_image* images, co
     }
     int64_t stride = im.stride_bytes ? im.stride_bytes : im.width;
     const uint8_t* src = static_cast<const uint8_t*>(im.data);
-    if (!im.on_device) {
+    if (im.on_device && !in_place[i]) {
+      HIPCHECK(c, hipMemcpy2DAsync(c->io_u8.p, v.W, src, stride, v.W, v.H, hipMemcpyDeviceToDevice, c->stream));
+      src = c->io_u8.p;
+      stride = v.W;
+    } else if (!im.on_device) {
       if (stride != v.W) {
         try {
           packed.resize(npx);

@@ -89,6 +89,13 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
   a->device = block_of(p) ? device_of_pointers : 0;
   return hipSuccess;
 }
+hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDeviceptr_t p) {
+  const auto* b = block_of(p);
+  if (!b) return result(hipErrorNotFound);
+  *base = b->first;
+  *size = b->second;
+  return hipSuccess;
+}
 hipError_t hipGetLastError() {
   const hipError_t e = last;
   last = hipSuccess;

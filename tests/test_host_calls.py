@@ -94,6 +94,32 @@ def rows_alone_are_read(c):
         assert c.set_views((W, H, stride, p, 0), (64, 48)) == 0, c.err()
 
 
+@case
+def device_images_elsewhere(c):
+    """What is called a device image is read in place only if it is all in this GPU's memory."""
+    W, H = 64, 48
+
+    def upload(p, stride=0):
+        c.stub.stub_forget_launches()
+        rc = c.set_views((W, H, stride, p, 1), (W, H))
+        return rc, [c.stub.stub_first(i) for i in range(c.stub.stub_launches())]
+
+    p = C.c_void_p()
+    assert c.stub.hipMalloc(C.byref(p), W * H) == 0
+    rc, firsts = upload(p.value)
+    assert rc == 0 and p.value in firsts  # this GPU's
+    rc, firsts = upload(p.value, W + 16)
+    assert rc == 0 and p.value not in firsts  # rows beyond the allocation: the copy's to judge
+    c.stub.stub_pointers_on(1)
+    rc, firsts = upload(p.value)
+    assert rc == 0 and p.value not in firsts  # another GPU's: copied
+    c.stub.stub_pointers_on(0)
+    host = np.zeros((H, W), np.uint8)
+    rc, firsts = upload(host.ctypes.data)
+    assert rc == -3 and host.ctypes.data not in firsts  # host memory: the copy is refused
+    assert c.set_views((W, H), (W, H)) == 0 and c.patchmatch() == 0, c.err()  # and leaves nothing behind
+
+
 # ---------------------------------------------------------------------------- errors
 @case
 def errors_are_reported_once(c):
