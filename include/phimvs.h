@@ -126,7 +126,11 @@ int phimvs_sync(phimvs_ctx* ctx);
 /* Upload the images and cameras of a scene (paper Sec. III: "images and camera
  * parameters" are the input).  K, R: n_views*9; t: n_views*3; depth_range:
  * n_views*2 (d_lo, d_hi per view, used when that view is the reference; requires
- * 0 < d_lo < d_hi).  Replaces any previous scene. */
+ * 0 < d_lo < d_hi).  Replaces any previous scene.  Of that one the context keeps view
+ * arrays that serve the new views (each at most twice its need) and up to 4 GiB of
+ * solver state for the next problem, which is cut to four times that problem's need when
+ * it is prepared; the state is given back when device memory runs out.  Of host images only
+ * the rows themselves are read, not the bytes between them. */
 int phimvs_set_views(phimvs_ctx* ctx, int n_views, const phimvs_image* images, const double* K,
                      const double* R, const double* t, const double* depth_range);
 
@@ -343,11 +347,14 @@ void phimvs_default_phi_params(phimvs_phi_params* p);
  * without depth takes its hypothesis closest to the reference (lowest k on ties; stays
  * empty without hypothesis or reference).  Pixels with depth keep it.  depth, depth_out:
  * device H*W; hyp, cost: device planar 4*H*W.  Graphs with many nodes for their length
- * are decoded on the device (about 450 bytes of the context's scratch per node, and 10
- * floats); small or narrow ones, those whose energies are not all finite, those in which
- * labels of different depth tie to within 2e-13 in energy (which rounding then decides)
- * and those that device memory does not hold are gathered (9 floats per node), copied to
- * the host and decoded there.  Both take the same FP64 steps but for the logarithms, which
+ * are decoded on the device.  That takes 448 bytes for each place of ceil(H2 / 32) bands of
+ * 32 rows by S columns (W2 x H2 the half size, S = W2 + 31 rounded up to a multiple of 16;
+ * 3200 x 2130 pixels: 795 MB), 4 KB for each of S columns ahead of them, and 10 floats per
+ * node.  The context keeps scratch of up to 1 GiB of it for the next selection (and gives it
+ * back when device memory runs out).  Small or narrow graphs, those whose energies are not
+ * all finite, those in which labels of different depth tie to within 2e-13 in energy (which
+ * rounding then decides) and those that device memory does not hold are gathered (9 floats
+ * per node), copied to the host and decoded there.  Both take the same FP64 steps but for the logarithms, which
  * are each platform's own; the labels are the same.  Synchronises the stream.
  * PHIMVS_E_ARG also for a cost above C_max + k1 k2 at a sampled hypothesis (no positive
  * potential). */

@@ -82,6 +82,7 @@ struct phimvs_ctx {
   std::string err;
   std::vector<ViewData> views;
   bool prepared = false;
+  bool state_idle = false;        // single's state is of an earlier scene and waits for the next problem
   Batch single;                   // the step-wise interface's job
   Batch multi;                    // phimvs_patchmatch_batch
   phimvs_tuning tuning{4, 1, 4, 0, 0.0};  // persistent, 4 workgroups per CU (the occupancy limit)
@@ -119,6 +120,23 @@ int fail(phimvs_ctx* c, int code, const std::string& msg) {
     }                                                                                              \
   } while (0)
 
+// What a context keeps for later calls is bounded: a selection's scratch up to kKeepScratch (795
+// MB at 3200 x 2130 pixels, where taking it anew and giving it back would add 0.6 to 19.5 ms), and
+// solver state across scenes up to kKeepState.
+constexpr size_t kKeepScratch = (size_t)1 << 30, kKeepState = (size_t)4 << 30;
+
+// device memory; where it has run out, what only waits for a later call is given back first
+void give_back(phimvs_ctx* c);
+hipError_t device_alloc(phimvs_ctx* c, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    give_back(c);
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
 template <typename T>
 int ensure(phimvs_ctx* c, DevBuf<T>& b, size_t n) {
   if (b.n >= n && b.p) return PHIMVS_OK;
@@ -127,7 +145,7 @@ int ensure(phimvs_ctx* c, DevBuf<T>& b, size_t n) {
     b.p = nullptr;
     b.n = 0;
   }
-  HIPCHECK(c, hipMalloc((void**)&b.p, std::max<size_t>(n, 1) * sizeof(T)));
+  HIPCHECK(c, device_alloc(c, (void**)&b.p, std::max<size_t>(n, 1) * sizeof(T)));
   b.n = n;
   return PHIMVS_OK;
 }
@@ -175,6 +193,23 @@ void resize_jobs(Batch& b, size_t n) {
   for (size_t i = n; i < b.state.size(); ++i) release_state(b.state[i]);
   b.state.resize(n);
   b.jobs.resize(n);
+}
+
+size_t state_bytes(const Batch& b) {
+  size_t n = 0;
+  for (const JobState& s : b.state) {
+    for (int k = 0; k < 2; ++k) n += s.plane[k].n * sizeof(float4) + s.cost[k].n * sizeof(float);
+    n += (s.cand.n + s.hist.n) * sizeof(float4);
+  }
+  return n;
+}
+
+// the scratch of the calls that end before they return or take it anew, and the state of a
+// scene that is gone
+void give_back(phimvs_ctx* c) {
+  release(c->trw);
+  release(c->fuse_scratch);
+  if (c->state_idle) resize_jobs(c->single, 0);
 }
 
 void release_batch(Batch& b) {
@@ -542,7 +577,7 @@ int upload_jobs(phimvs_ctx* c, Batch& b) {
     if (b.d_jobs) HIPCHECK(c, hipFree(b.d_jobs));
     b.d_jobs = nullptr;
     b.uploaded.clear();
-    HIPCHECK(c, hipMalloc((void**)&b.d_jobs, bytes));
+    HIPCHECK(c, device_alloc(c, (void**)&b.d_jobs, bytes));
     b.d_cap = bytes;
   }
   // the table is read by work already queued: wait for it before overwriting
@@ -712,6 +747,7 @@ int prepare_single(phimvs_ctx* c, int ref, const int* srcs, int n_srcs, int wind
   if (key != b.layout_key || b.jobs.size() != 1) {
     // a recorded sequence stays: its key says whether it fits the new problem's launches
     b.layout_key.clear();
+    c->state_idle = false;
     resize_jobs(b, 1);
     b.ref_valid[0] = b.ref_valid[1] = false;
     if ((rc = setup_job(c, P, b.jobs[0], b.state[0]))) return rc;
@@ -988,8 +1024,8 @@ static int take_views(phimvs_ctx* c, int n_views, const phimvs_image* images, co
     v.d_hi = depth_range[2 * i + 1];
     const size_t npx = (size_t)v.W * v.H;
     if (!v.plain) {
-      HIPCHECK(c, hipMalloc((void**)&v.plain, npx * sizeof(__half)));
-      HIPCHECK(c, hipMalloc((void**)&v.quad, npx * sizeof(uint32_t)));
+      HIPCHECK(c, device_alloc(c, (void**)&v.plain, npx * sizeof(__half)));
+      HIPCHECK(c, device_alloc(c, (void**)&v.quad, npx * sizeof(uint32_t)));
       v.cap = npx;
     }
     int64_t stride = im.stride_bytes ? im.stride_bytes : im.width;
@@ -1086,6 +1122,8 @@ int phimvs_set_views(phimvs_ctx* c, int n_views, const phimvs_image* images, con
   HIPCHECK(c, hipDeviceSynchronize());
   release_batch(c->multi);
   c->single.layout_key.clear();  // its state stays allocated for the next problem
+  c->state_idle = true;
+  if (state_bytes(c->single) > kKeepState) resize_jobs(c->single, 0);
   c->prepared = false;
   const int rc = take_views(c, n_views, images, K, R, t, depth_range);
   if (rc) {
@@ -1524,6 +1562,7 @@ int phimvs_phi_select(phimvs_ctx* c, int width, int height, const float* depth, 
     HIPCHECK(c, launch_phi_select(depth, hyp, dec, W, H, flag, depth_out, c->stream));
     HIPCHECK(c, hipMemcpyAsync(&got, flag, sizeof got, hipMemcpyDeviceToHost, c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
+    if (c->trw.n * sizeof(uint64_t) > kKeepScratch) release(c->trw);
     if (got & kTrwInvalid) return fail(c, PHIMVS_E_ARG, invalid);
     if (!got) return PHIMVS_OK;
   }

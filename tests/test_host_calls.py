@@ -120,6 +120,56 @@ def device_images_elsewhere(c):
     assert c.set_views((W, H), (W, H)) == 0 and c.patchmatch() == 0, c.err()  # and leaves nothing behind
 
 
+# ---------------------------------------------------------------------------- memory
+def select(c, W, H):
+    a = np.zeros(1, np.float32).ctypes.data  # nothing reads it
+    assert c.L.phimvs_phi_select(c.h, W, H, a, a, a, None, a) == 0, c.err()
+
+
+@case
+def a_selection_gives_its_scratch_back(c):
+    n = 2400 * 1600
+    select(c, 4800, 3200)
+    assert c.stub.stub_live() < 64 * n  # 10 floats per node stay; the graph takes over 400 bytes
+
+
+@case
+def a_selection_leaves_room_for_later_calls(c):
+    assert c.set_views((1200, 800), (1200, 800)) == 0, c.err()
+    before = c.stub.stub_live()
+    assert c.patchmatch() == 0, c.err()
+    need = c.stub.stub_live() - before
+    for lim in (need - 1, need):  # the second time it fits
+        d = Calls(c.stub)
+        assert d.set_views((1200, 800), (1200, 800)) == 0, d.err()
+        base = c.stub.stub_live()
+        select(d, 800, 532)
+        io = 40 * 400 * 266
+        c.stub.stub_limit(base + io + lim)
+        assert d.patchmatch() == (0 if lim == need else -4)
+        c.stub.stub_limit(1 << 40)
+
+
+@case
+def an_earlier_scene_leaves_room_for_a_batch(c):
+    assert c.set_views((2000, 1500), (2000, 1500)) == 0, c.err()
+    assert c.patchmatch() == 0, c.err()
+    assert c.set_views((300, 200), (300, 200)) == 0, c.err()
+    c.stub.stub_limit(c.stub.stub_live() + (1 << 20))
+    assert c.batch(0, 1) == 0, c.err()
+    assert c.patchmatch() == 0, c.err()
+
+
+@case
+def state_kept_across_scenes_is_bounded(c):
+    assert c.set_views((5200, 4400), (64, 48)) == 0, c.err()
+    assert c.patchmatch() == 0, c.err()
+    assert c.stub.stub_live() > 4 << 30
+    assert c.set_views((300, 200), (300, 200)) == 0, c.err()
+    assert c.stub.stub_live() < 1 << 30
+    assert c.patchmatch() == 0, c.err()
+
+
 # ---------------------------------------------------------------------------- errors
 @case
 def errors_are_reported_once(c):
