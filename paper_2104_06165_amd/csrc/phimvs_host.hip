@@ -576,6 +576,7 @@ int upload_jobs(phimvs_ctx* c, Batch& b) {
   if (b.d_cap < bytes) {
     if (b.d_jobs) HIPCHECK(c, hipFree(b.d_jobs));
     b.d_jobs = nullptr;
+    b.d_cap = 0;
     b.uploaded.clear();
     HIPCHECK(c, device_alloc(c, (void**)&b.d_jobs, bytes));
     b.d_cap = bytes;
@@ -1629,6 +1630,7 @@ int phimvs_patchmatch_batch(phimvs_ctx* c, int n_jobs, const phimvs_job* jobs, i
   int rc;
   if (key != b.layout_key) {
     release_graph(b);
+    b.layout_key.clear();  // until all jobs are set up
     resize_jobs(b, (size_t)n_jobs);
     for (int i = 0; i < n_jobs; ++i)
       if ((rc = setup_job(c, probs[i], b.jobs[i], b.state[i]))) return rc;

@@ -170,6 +170,18 @@ def state_kept_across_scenes_is_bounded(c):
     assert c.patchmatch() == 0, c.err()
 
 
+@case
+def a_batch_that_found_no_memory_is_set_up_anew(c):
+    """What it left half made must not pass for the batch before it."""
+    assert c.set_views((300, 200), (300, 200), (2000, 1500)) == 0, c.err()
+    assert c.batch(0) == 0, c.err()
+    table = c.stub.stub_table_bytes()
+    c.stub.stub_limit(c.stub.stub_live() + (1 << 20))
+    assert c.batch(0, 2) == -4
+    assert c.batch(0) == 0, c.err()
+    assert c.stub.stub_table_bytes() == table  # one job's
+
+
 # ---------------------------------------------------------------------------- errors
 @case
 def errors_are_reported_once(c):
