@@ -56,7 +56,7 @@ def measured_traffic(kernel_file: str, profile: str):
 
 def parse_tuning(pm, text):
     """ROWS,PERSISTENT,WGS[,ORDER_BY_DEPTH] -> the library's launch configuration (the order
-    a mask: 1 initialisation, 2 propagation, 4 refinement)."""
+    a mask: 1 initialisation, 2 propagation, 4 refinement, 8 by the cameras)."""
     v = [int(x) for x in text.split(",")]
     if len(v) not in (3, 4):
         raise SystemExit("--tuning takes ROWS,PERSISTENT,WGS[,ORDER_BY_DEPTH]")

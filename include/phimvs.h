@@ -205,11 +205,11 @@ int phimvs_patchmatch_batch(phimvs_ctx* ctx, int n_jobs, const phimvs_job* jobs,
  * order of the candidate's inverse depth instead of pixel order (results are the same
  * either way; it pays where the candidates' depths scatter the source gathers most, as
  * with converging cameras; the split-lane path of phimvs_params.lanes > 1 has no work list
- * and ignores it).  ms is the time measured by
- * phimvs_autotune.  A new context starts with tile_rows 4, persistent, 4 workgroups per
- * compute unit, order_by_depth 0; until phimvs_set_tuning or phimvs_autotune is called, a
- * job whose sources' epipolar lines cross many of their rows takes depth order all the same
- * (the results do not depend on it), and order_by_depth = 0 given there means pixel order. */
+ * and ignores it); 8 in the mask leaves the launches it does not name to each job's cameras:
+ * depth order where the sources' epipolar lines cross many of their rows, else pixel order,
+ * which 0 asks for.  ms is the time measured by phimvs_autotune.  A new context starts with
+ * tile_rows 4, persistent, 4 workgroups per compute unit, order_by_depth 8.  A tuning read
+ * with phimvs_get_tuning and set again is the one that was there. */
 typedef struct {
   int32_t tile_rows;
   int32_t persistent;

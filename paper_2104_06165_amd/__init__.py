@@ -115,7 +115,7 @@ class Tuning:
     persistent: bool = False
     wgs_per_cu: int = 0
     ms: float = 0.0
-    order_by_depth: int = 0  # mask: 1 initialisation, 2 propagation, 4 refinement (True: all)
+    order_by_depth: int = 0  # mask: 1 initialisation, 2 propagation, 4 refinement (True: these), 8 by the cameras
 
 
 @dataclass

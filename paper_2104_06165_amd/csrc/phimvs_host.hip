@@ -74,6 +74,8 @@ struct Batch {
 
 }  // namespace
 
+constexpr int kOrderByCameras = 8;  // of phimvs_tuning.order_by_depth
+
 struct phimvs_ctx {
   int device = 0;
   int n_cu = 256;
@@ -85,8 +87,8 @@ struct phimvs_ctx {
   bool state_idle = false;        // single's state is of an earlier scene and waits for the next problem
   Batch single;                   // the step-wise interface's job
   Batch multi;                    // phimvs_patchmatch_batch
-  phimvs_tuning tuning{4, 1, 4, 0, 0.0};  // persistent, 4 workgroups per CU (the occupancy limit)
-  bool order_auto = true;                 // work-list order by each job's cameras until the caller sets a tuning
+  // persistent, 4 workgroups per CU (the occupancy limit), work lists in the order of each job's cameras
+  phimvs_tuning tuning{4, 1, 4, kOrderByCameras, 0.0};
   size_t eval_lds_max = 0;                // largest dynamic LDS of an evaluate launch on this device
   DevBuf<float> io_a, io_b, io_c, io_d;  // staging for host inputs / outputs
   DevBuf<FuseMap> fuse_maps;              // fusion: map table
@@ -385,7 +387,7 @@ int validate_problem(phimvs_ctx* c, const Problem& P) {
   return PHIMVS_OK;
 }
 
-// Whether a job's work lists go by depth when the caller has set no tuning: the mean number
+// Whether a job's work lists go by depth where the cameras decide it: the mean number
 // of rows of a source image that a reference pixel's epipolar segment crosses over the
 // depth range (at five points of the reference) is at least kDepthOrderRows.  A source
 // row's texels share cache lines (32 a line), so candidates of scattered depths cost a
@@ -611,11 +613,11 @@ int run_eval(phimvs_ctx* c, Batch& b, Launch L, unsigned int* queue) {
   const bool persistent = c->tuning.persistent != 0;
   L.persistent = persistent ? 1 : 0;
   // the depth-ordered instance for the launch kinds the tuning names (mask: 1 initialisation,
-  // 2 propagation, 4 refinement), or where no tuning was set and a job's cameras call for it
-  // (mode 2 has no work list)
+  // 2 propagation, 4 refinement), or where it leaves the order to the cameras and a job's call for
+  // it (mode 2 has no work list)
   const int kind_bit = L.mode == 0 ? 1 : (L.ncand > 3 ? 2 : 4);
   L.order_by_depth = (c->tuning.order_by_depth & kind_bit) ? 1 : 0;
-  if (c->order_auto && L.mode != 2)
+  if ((c->tuning.order_by_depth & kOrderByCameras) && !L.order_by_depth && L.mode != 2)
     for (const Job& J : b.jobs)
       if (J.A.by_depth) L.order_by_depth = 2;
   L.queue = queue;
@@ -825,7 +827,7 @@ std::string sequence_key(const phimvs_ctx* c, const Batch& b, int iters) {
                       (long long)A.n_taps, (long long)L.n_jobs, (long long)L.tile_rows, (long long)L.total_tiles,
                       (long long)L.total_cblk, (long long)L.frac, (long long)b.max_r, (long long)b.max_taps,
                       (long long)iters, (long long)c->tuning.persistent, (long long)c->tuning.wgs_per_cu,
-                      (long long)c->tuning.order_by_depth, (long long)c->order_auto})
+                      (long long)c->tuning.order_by_depth})
     add(v);
   for (int x : L.xcd_len) add(x);
   add((long long)reinterpret_cast<uintptr_t>(b.d_jobs));
@@ -1662,14 +1664,14 @@ int phimvs_set_tuning(phimvs_ctx* c, const phimvs_tuning* t) {
     return fail(c, PHIMVS_E_ARG, "tile_rows must be 1, 2 or 4");
   if (t->persistent && (t->wgs_per_cu < 1 || t->wgs_per_cu > 16))
     return fail(c, PHIMVS_E_ARG, "wgs_per_cu must be in [1, 16] for persistent launches");
-  if (t->order_by_depth < 0 || t->order_by_depth > 7)
-    return fail(c, PHIMVS_E_ARG, "order_by_depth is a mask of 1 (initialisation), 2 (propagation), 4 (refinement)");
+  if (t->order_by_depth < 0 || t->order_by_depth > 15)
+    return fail(c, PHIMVS_E_ARG,
+                "order_by_depth is a mask of 1 (initialisation), 2 (propagation), 4 (refinement), 8 (by the cameras)");
   HIPCHECK(c, hipSetDevice(c->device));
   HIPCHECK(c, hipStreamSynchronize(c->stream));
   const bool shape = t->tile_rows != c->tuning.tile_rows;
   c->tuning = *t;
   c->tuning.ms = 0.0;
-  c->order_auto = false;
   if (shape) {
     // the tile shape changes the layout of every job: rebuild on next use
     c->prepared = false;
@@ -1696,7 +1698,6 @@ int phimvs_autotune(phimvs_ctx* c, int n_jobs, const phimvs_job* jobs, int iters
                            {2, 1, 4, 0, 0}, {1, 1, 4, 0, 0}, {4, 1, 4, 1, 0}};
   const int n = (int)(sizeof(cands) / sizeof(cands[0]));
   const phimvs_tuning prev = c->tuning;
-  const bool prev_auto = c->order_auto;
   phimvs_tuning best{};
   double best_ms = HUGE_VAL;
   std::string failures;
@@ -1744,7 +1745,6 @@ int phimvs_autotune(phimvs_ctx* c, int n_jobs, const phimvs_job* jobs, int iters
   if (n_results) *n_results = std::min(*n_results, n);
   if (!(best_ms < HUGE_VAL)) {
     (void)phimvs_set_tuning(c, &prev);
-    c->order_auto = prev_auto;
     return fail(c, PHIMVS_E_DEVICE, "autotune: no configuration ran:" + failures);
   }
   int rc = phimvs_set_tuning(c, &best);

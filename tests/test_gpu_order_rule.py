@@ -50,3 +50,22 @@ def test_default_order_changes_no_result(grid, pick, use_graph):
         finally:
             ctx.close()
     assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+@pytest.mark.parametrize("pick", [[0], [1], [2], [0, 1, 2]])
+def test_every_order_gives_the_same_maps(grid, pick):
+    """The cameras' choice (a new context's tuning), pixel order, depth order and the cameras' choice
+    with one kind of launch in depth order."""
+    res = []
+    ctx = pm.Context(0)
+    try:
+        ctx.set_views(grid.images, grid.K, grid.R, grid.t, grid.depth_ranges)
+        t = ctx.get_tuning()
+        assert t.order_by_depth == 8
+        for order in (8, 0, 7, 9, 10, 12, 8):
+            ctx.set_tuning(pm.Tuning(t.tile_rows, t.persistent, t.wgs_per_cu, order_by_depth=order))
+            out = ctx.patchmatch_batch([jobs(grid)[i] for i in pick], 3)
+            res.append([x.clone() for o in out for x in o])
+    finally:
+        ctx.close()
+    assert all(torch.equal(a, b) for r in res[1:] for a, b in zip(res[0], r))

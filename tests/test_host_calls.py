@@ -182,6 +182,45 @@ def a_batch_that_found_no_memory_is_set_up_anew(c):
     assert c.stub.stub_table_bytes() == table  # one job's
 
 
+# ---------------------------------------------------------------------------- tuning
+@case
+def tuning_goes_out_and_back(c):
+    """A tuning read, kept and set again is the one that was there, the work-list order by the
+    cameras included; order 0 asks for pixel order."""
+    # a vertical baseline: the epipolar lines run down the images
+    assert c.set_views((400, 900), (400, 900), t=[[0, 0, 0], [0, 1, 0]]) == 0, c.err()
+
+    def functions():
+        c.stub.stub_forget_launches()
+        assert c.batch(0) == 0, c.err()
+        return [c.stub.stub_launched(i) for i in range(c.stub.stub_launches())]
+
+    def get():
+        t = pm._Tuning()
+        assert c.L.phimvs_get_tuning(c.h, C.byref(t)) == 0
+        return t
+
+    def put(t):
+        assert c.L.phimvs_set_tuning(c.h, C.byref(t)) == 0, c.err()
+
+    fresh, first = get(), functions()
+    put(fresh)
+    assert functions() == first
+    put(pm._Tuning(fresh.tile_rows, fresh.persistent, fresh.wgs_per_cu, 7, 0.0))
+    assert functions() == first  # all by depth: the same kernels
+    put(pm._Tuning(fresh.tile_rows, fresh.persistent, fresh.wgs_per_cu, 0, 0.0))
+    assert functions() != first
+    put(fresh)
+    assert functions() == first
+    t = get()
+    t.wgs_per_cu = 2
+    put(t)
+    assert functions() == first
+    for bad in (-1, 16):
+        t.order_by_depth = bad
+        assert c.L.phimvs_set_tuning(c.h, C.byref(t)) == -1
+
+
 # ---------------------------------------------------------------------------- errors
 @case
 def errors_are_reported_once(c):
