@@ -284,27 +284,28 @@ __global__ __launch_bounds__(kWgBlock) void conv3x3_wgrad_kernel(WgradArgs a, in
       for (int v = 0; v < NCO; ++v) acc[t][u][v] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int v = 0; v < NCO; ++v) accb[v] = v4f{0.f, 0.f, 0.f, 0.f};
-  // this lane's chunks of a row: element offset within the row, and whether the column exists
+  // this lane's chunks of a row: element offset from the strip's first column (a row can hold more
+  // than 2^31 elements), and whether the column exists
   int xo[kXl], go[kGl];
   bool xi[kXl], gi[kGl];
 #pragma unroll
   for (int k = 0; k < kXl; ++k) {
-    const int q = lane + 64 * k, c = seg * 32 - 1 + q / (CI / 8);
-    xi[k] = q < kXc && c >= 0 && c < a.w;
+    const int q = lane + 64 * k, c = q / (CI / 8) - 1;
+    xi[k] = q < kXc && seg * 32 + c >= 0 && seg * 32 + c < a.w;
     xo[k] = xi[k] ? c * CI + (q % (CI / 8)) * 8 : 0;
   }
 #pragma unroll
   for (int k = 0; k < kGl; ++k) {
-    const int q = lane + 64 * k, c = seg * 32 + q / (CO / 8);
-    gi[k] = c < a.w;
+    const int q = lane + 64 * k, c = q / (CO / 8);
+    gi[k] = seg * 32 + c < a.w;
     go[k] = gi[k] ? c * CO + (q % (CO / 8)) * 8 : 0;
   }
   uint4 xr[kXl], gr[kGl];
   // input row i and gradient row i + 1 (zero outside the image, and outside the band)
   auto load_rows = [&](int i) {
     const bool xin = i >= 0 && i < a.h, gin = i + 1 >= r0 && i + 1 < r1;
-    const uint16_t* xp = a.x + ((size_t)b * a.h + (xin ? i : 0)) * a.w * CI;
-    const uint16_t* gp = a.g + ((size_t)b * a.h + (gin ? i + 1 : 0)) * a.w * CO;
+    const uint16_t* xp = a.x + (((size_t)b * a.h + (xin ? i : 0)) * a.w + seg * 32) * CI;
+    const uint16_t* gp = a.g + (((size_t)b * a.h + (gin ? i + 1 : 0)) * a.w + seg * 32) * CO;
 #pragma unroll
     for (int k = 0; k < kXl; ++k) {
       xr[k] = make_uint4(0u, 0u, 0u, 0u);

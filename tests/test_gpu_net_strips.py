@@ -103,3 +103,33 @@ def test_unaligned_output():
         assert rc == 0 and torch.equal(raw[off:off + 5 * 19 * 4].reshape(5, 19, 4), ref[0])
         assert raw[:off].abs().sum() == 0 and raw[off + 5 * 19 * 4:].abs().sum() == 0
     net.close()
+
+
+def test_a_row_of_more_than_2_to_the_31_elements():
+    """A row of 2^26 pixels (32 channels: 2^31 elements) whose content and loss lie at its end, against
+    a row of 128 with the same end: the gradients differ by the ratio of the pixel counts, a power
+    of two (which bfloat16 and FP32 carry exactly), and by the order of the sums over some 40 columns,
+    40 x 2^-24 of their terms; a strip read from elsewhere would change them by their own size."""
+    W = 1 << 26
+    if torch.cuda.mem_get_info()[0] < 120 << 30:
+        pytest.skip("needs 120 GB of device memory")
+    g = torch.Generator().manual_seed(26)
+    net = pm.Net(0, np.load(pm.LIB_PATH.replace("libphimvs.so", "weights/proposal_net.npy")).astype(np.float32))
+    end = torch.randn((64, 5), generator=g).cuda()
+    tgt = torch.cat([2.0 + torch.rand((32, 1), generator=g), torch.nn.functional.normalize(torch.randn((32, 3), generator=g), dim=-1)], -1).cuda()
+    grads = []
+    for w in (128, W):
+        x = torch.zeros((1, 1, w, 5), device="cuda")
+        x[0, 0, -64:] = end
+        target = torch.ones((1, 1, w, 4), device="cuda")
+        target[0, 0, -32:] = tgt
+        mask = torch.zeros((1, 1, w), device="cuda")
+        mask[0, 0, -32:] = 1
+        print(f"a row of {w} pixels", flush=True)
+        _, grad = net.loss_grad(x, target, mask, torch.tensor([[1.0, 9.0]], device="cuda"), 1.0, True, True)
+        grads.append(grad.double().clone() * w)
+        del x, target, mask
+    net.close()
+    scale = grads[0].abs().max()
+    assert float((grads[1] - grads[0]).abs().max()) <= float(scale) * 2.0 ** -10
+    assert float(scale) > 0
