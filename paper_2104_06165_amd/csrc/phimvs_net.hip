@@ -265,14 +265,8 @@ __global__ __launch_bounds__(kWgBlock) void conv3x3_wgrad_kernel(WgradArgs a, in
   constexpr int kWaves = kWgBlock / 64, kRegs = 3 * NCI * NCO * 4;
   constexpr int kStageBytes = kWaves * (kXc + kGc) * 16, kRedBytes = kWaves * (kRegs + NCO) * 64 * 4;
   __shared__ uint4 lds[(kStageBytes > kRedBytes ? kStageBytes : kRedBytes) / 16];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int lr = lane & 15, lk = lane >> 4;
-  const int task = blockIdx.x * (kWgBlock / 64) + wave;  // (b, band, seg)
-  const bool work = task < a.B * bands * segs;
-  const int seg = task % segs;
-  const int bb = task / segs;
-  const int band = bb % bands, b = work ? bb / bands : 0;
-  const int r0 = band * rb, r1 = work ? min(r0 + rb, a.h) : r0 - 2;
   uint4* xs = lds + wave * (kXc + kGc);
   uint4* gs = xs + kXc;
   v4f acc[9][NCI][NCO], accb[NCO];
@@ -284,79 +278,87 @@ __global__ __launch_bounds__(kWgBlock) void conv3x3_wgrad_kernel(WgradArgs a, in
       for (int v = 0; v < NCO; ++v) acc[t][u][v] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int v = 0; v < NCO; ++v) accb[v] = v4f{0.f, 0.f, 0.f, 0.f};
-  // this lane's chunks of a row: element offset from the strip's first column (a row can hold more
-  // than 2^31 elements), and whether the column exists
-  int xo[kXl], go[kGl];
-  bool xi[kXl], gi[kGl];
-#pragma unroll
-  for (int k = 0; k < kXl; ++k) {
-    const int q = lane + 64 * k, c = q / (CI / 8) - 1;
-    xi[k] = q < kXc && seg * 32 + c >= 0 && seg * 32 + c < a.w;
-    xo[k] = xi[k] ? c * CI + (q % (CI / 8)) * 8 : 0;
-  }
-#pragma unroll
-  for (int k = 0; k < kGl; ++k) {
-    const int q = lane + 64 * k, c = q / (CO / 8);
-    gi[k] = seg * 32 + c < a.w;
-    go[k] = gi[k] ? c * CO + (q % (CO / 8)) * 8 : 0;
-  }
-  uint4 xr[kXl], gr[kGl];
-  // input row i and gradient row i + 1 (zero outside the image, and outside the band)
-  auto load_rows = [&](int i) {
-    const bool xin = i >= 0 && i < a.h, gin = i + 1 >= r0 && i + 1 < r1;
-    const uint16_t* xp = a.x + (((size_t)b * a.h + (xin ? i : 0)) * a.w + seg * 32) * CI;
-    const uint16_t* gp = a.g + (((size_t)b * a.h + (gin ? i + 1 : 0)) * a.w + seg * 32) * CO;
+  Frag<32> ones;
+  ones.v = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
+  // (b, band, seg): one for a wave, more where there are more strips than waves
+  const int tasks = a.B * bands * segs;
+  for (int task = blockIdx.x * (kWgBlock / 64) + wave; task < tasks; task += gridDim.x * (kWgBlock / 64)) {
+    const int seg = task % segs;
+    const int bb = task / segs;
+    const int band = bb % bands, b = bb / bands;
+    const int r0 = band * rb, r1 = min(r0 + rb, a.h);
+    // this lane's chunks of a row: element offset from the strip's first column (a row can hold more
+    // than 2^31 elements), and whether the column exists
+    int xo[kXl], go[kGl];
+    bool xi[kXl], gi[kGl];
 #pragma unroll
     for (int k = 0; k < kXl; ++k) {
-      xr[k] = make_uint4(0u, 0u, 0u, 0u);
-      if (xin && xi[k]) xr[k] = *reinterpret_cast<const uint4*>(xp + xo[k]);
+      const int q = lane + 64 * k, c = q / (CI / 8) - 1;
+      xi[k] = q < kXc && seg * 32 + c >= 0 && seg * 32 + c < a.w;
+      xo[k] = xi[k] ? c * CI + (q % (CI / 8)) * 8 : 0;
     }
 #pragma unroll
     for (int k = 0; k < kGl; ++k) {
-      gr[k] = make_uint4(0u, 0u, 0u, 0u);
-      if (gin && gi[k]) gr[k] = *reinterpret_cast<const uint4*>(gp + go[k]);
+      const int q = lane + 64 * k, c = q / (CO / 8);
+      gi[k] = seg * 32 + c < a.w;
+      go[k] = gi[k] ? c * CO + (q % (CO / 8)) * 8 : 0;
     }
-  };
-  Frag<32> ones;
-  ones.v = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
-  Frag<32> g0[NCO], g1[NCO], g2[NCO];  // gradient rows i + 1, i, i - 1
+    uint4 xr[kXl], gr[kGl];
+    // input row i and gradient row i + 1 (zero outside the image, and outside the band)
+    auto load_rows = [&](int i) {
+      const bool xin = i >= 0 && i < a.h, gin = i + 1 >= r0 && i + 1 < r1;
+      const uint16_t* xp = a.x + (((size_t)b * a.h + (xin ? i : 0)) * a.w + seg * 32) * CI;
+      const uint16_t* gp = a.g + (((size_t)b * a.h + (gin ? i + 1 : 0)) * a.w + seg * 32) * CO;
 #pragma unroll
-  for (int v = 0; v < NCO; ++v) g1[v].v = g2[v].v = make_uint4(0u, 0u, 0u, 0u);
-  if (r0 <= r1) load_rows(r0 - 1);
-  for (int i = r0 - 1; i <= r1; ++i) {
-    // the staged row is this wave's own: its LDS operations stay in order
+      for (int k = 0; k < kXl; ++k) {
+        xr[k] = make_uint4(0u, 0u, 0u, 0u);
+        if (xin && xi[k]) xr[k] = *reinterpret_cast<const uint4*>(xp + xo[k]);
+      }
 #pragma unroll
-    for (int k = 0; k < kXl; ++k)
-      if (lane + 64 * k < kXc) xs[lane + 64 * k] = xr[k];
+      for (int k = 0; k < kGl; ++k) {
+        gr[k] = make_uint4(0u, 0u, 0u, 0u);
+        if (gin && gi[k]) gr[k] = *reinterpret_cast<const uint4*>(gp + go[k]);
+      }
+    };
+    Frag<32> g0[NCO], g1[NCO], g2[NCO];  // gradient rows i + 1, i, i - 1
 #pragma unroll
-    for (int k = 0; k < kGl; ++k) gs[lane + 64 * k] = gr[k];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (i < r1) load_rows(i + 1);
-    Frag<32> X[3][NCI];
+    for (int v = 0; v < NCO; ++v) g1[v].v = g2[v].v = make_uint4(0u, 0u, 0u, 0u);
+    load_rows(r0 - 1);
+    for (int i = r0 - 1; i <= r1; ++i) {
+      // the staged row is this wave's own: its LDS operations stay in order
 #pragma unroll
-    for (int d = 0; d < 3; ++d)
+      for (int k = 0; k < kXl; ++k)
+        if (lane + 64 * k < kXc) xs[lane + 64 * k] = xr[k];
 #pragma unroll
-      for (int u = 0; u < NCI; ++u)
-        X[d][u] = read_columns<CI>(reinterpret_cast<const uint16_t*>(xs), d, 16 * u, lr, lk);
+      for (int k = 0; k < kGl; ++k) gs[lane + 64 * k] = gr[k];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (i < r1) load_rows(i + 1);
+      Frag<32> X[3][NCI];
 #pragma unroll
-    for (int v = 0; v < NCO; ++v)
-      g0[v] = read_columns<CO>(reinterpret_cast<const uint16_t*>(gs), 0, 16 * v, lr, lk);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+      for (int d = 0; d < 3; ++d)
 #pragma unroll
-    for (int v = 0; v < NCO; ++v) {
-      accb[v] = mfma(ones, g0[v], accb[v]);
+        for (int u = 0; u < NCI; ++u)
+          X[d][u] = read_columns<CI>(reinterpret_cast<const uint16_t*>(xs), d, 16 * u, lr, lk);
 #pragma unroll
-      for (int u = 0; u < NCI; ++u)
+      for (int v = 0; v < NCO; ++v)
+        g0[v] = read_columns<CO>(reinterpret_cast<const uint16_t*>(gs), 0, 16 * v, lr, lk);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          acc[d][u][v] = mfma(X[d][u], g0[v], acc[d][u][v]);
-          acc[3 + d][u][v] = mfma(X[d][u], g1[v], acc[3 + d][u][v]);
-          acc[6 + d][u][v] = mfma(X[d][u], g2[v], acc[6 + d][u][v]);
-        }
-      g2[v] = g1[v];
-      g1[v] = g0[v];
+      for (int v = 0; v < NCO; ++v) {
+        accb[v] = mfma(ones, g0[v], accb[v]);
+#pragma unroll
+        for (int u = 0; u < NCI; ++u)
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            acc[d][u][v] = mfma(X[d][u], g0[v], acc[d][u][v]);
+            acc[3 + d][u][v] = mfma(X[d][u], g1[v], acc[3 + d][u][v]);
+            acc[6 + d][u][v] = mfma(X[d][u], g2[v], acc[6 + d][u][v]);
+          }
+        g2[v] = g1[v];
+        g1[v] = g0[v];
+      }
     }
   }
   // The waves' sums, three taps at a time: every wave lays its registers out lane by lane, then
@@ -670,10 +672,12 @@ hipError_t wgrad_launch(const WgradArgs& a, int n_partial, hipStream_t st) {
 
 int wgrad_partials(int B, int h, int w, int* rb, int* segs, int* bands) {
   *segs = (w + 31) / 32;
-  *rb = band_rows((int64_t)B * *segs, h, 2048);  // 2 waves per SIMD by registers
+  constexpr int waves = 2048, per_wg = pmn::kWgBlock / 64;  // 2 waves per SIMD by registers
+  *rb = band_rows((int64_t)B * *segs, h, waves);
   *bands = (h + *rb - 1) / *rb;
-  const int64_t tasks = (int64_t)B * *bands * *segs;
-  return (int)((tasks + pmn::kWgBlock / 64 - 1) / (pmn::kWgBlock / 64));
+  // more strips than waves are walked by these, so that the partial sums (148 KB for all layers of
+  // one) do not grow with the images
+  return (int)((std::min<int64_t>((int64_t)B * *bands * *segs, waves) + per_wg - 1) / per_wg);
 }
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t st) {

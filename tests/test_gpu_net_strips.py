@@ -105,6 +105,11 @@ def test_unaligned_output():
     net.close()
 
 
+@pytest.mark.parametrize("B,h,w", [(2049, 2, 5), (700, 3, 97), (5000, 1, 33)])
+def test_more_strips_than_waves(B, h, w):
+    test_strips(B, h, w)
+
+
 def test_a_row_of_more_than_2_to_the_31_elements():
     """A row of 2^26 pixels (32 channels: 2^31 elements) whose content and loss lie at its end, against
     a row of 128 with the same end: the gradients differ by the ratio of the pixel counts, a power

@@ -182,6 +182,18 @@ def a_batch_that_found_no_memory_is_set_up_anew(c):
     assert c.stub.stub_table_bytes() == table  # one job's
 
 
+@case
+def weight_gradients_sums_are_bounded(c):
+    """The partial sums of a weight gradient (148 KB each) do not grow with the images: wide ones of
+    few rows had more of them than activations."""
+    f = c.L._ZN19phimvs_net_internal14wgrad_partialsEiiiPiS0_S0_
+    for B, h, w in ((1, 1, 1), (8, 267, 400), (1, 1, 1 << 28), (1, 2, 1 << 27), (1 << 28, 1, 1), (1 << 20, 2, 128)):
+        rb, segs, bands = C.c_int(), C.c_int(), C.c_int()
+        n = f(B, h, w, C.byref(rb), C.byref(segs), C.byref(bands))
+        assert 1 <= n <= 256 and n * 8 <= max(2048, B * segs.value * bands.value + 7)
+        assert segs.value == (w + 31) // 32 and bands.value * rb.value >= h
+
+
 # ---------------------------------------------------------------------------- tuning
 @case
 def tuning_goes_out_and_back(c):
