@@ -1121,8 +1121,9 @@ int phimvs_set_views(phimvs_ctx* c, int n_views, const phimvs_image* images, con
       return fail(c, PHIMVS_E_ARG, "depth range of view " + std::to_string(i) + " needs 0 < d_lo < d_hi");
   }
   HIPCHECK(c, hipSetDevice(c->device));
-  // the old views' arrays are written over below: nothing may still read them, on any stream
-  HIPCHECK(c, hipDeviceSynchronize());
+  // the old views' arrays are written over below: nothing may still read them, on any stream (a
+  // first scene has none, and other contexts' work is none of its business)
+  HIPCHECK(c, c->views.empty() ? hipStreamSynchronize(c->stream) : hipDeviceSynchronize());
   release_batch(c->multi);
   c->single.layout_key.clear();  // its state stays allocated for the next problem
   c->state_idle = true;

@@ -120,6 +120,15 @@ def device_images_elsewhere(c):
     assert c.set_views((W, H), (W, H)) == 0 and c.patchmatch() == 0, c.err()  # and leaves nothing behind
 
 
+@case
+def a_first_scene_waits_for_no_other_work(c):
+    """Only a scene that takes over arrays has to wait for the whole GPU."""
+    assert c.set_views((64, 48), (64, 48)) == 0, c.err()
+    assert c.stub.stub_device_syncs() == 0
+    assert c.set_views((64, 48), (64, 48)) == 0, c.err()
+    assert c.stub.stub_device_syncs() == 1
+
+
 # ---------------------------------------------------------------------------- memory
 def select(c, W, H):
     a = np.zeros(1, np.float32).ctypes.data  # nothing reads it
