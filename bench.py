@@ -321,7 +321,7 @@ def bench_phi(ctx, mv, jobs, outs, size=None):
     model) and normals, and the filled maps are filtered again against
     each other.  Reported: completeness (pixels with depth) and accuracy against the
     rendered depth at each stage, the GPU time of hypotheses + costs + normals and the
-    time of the selection (host_selection_ms; small graphs are decoded on the host)."""
+    time of the selection (selection_ms; small graphs are decoded on the host)."""
     import torch
 
     import paper_2104_06165_amd as pm
@@ -336,7 +336,7 @@ def bench_phi(ctx, mv, jobs, outs, size=None):
         d, n, _ = ctx.filter(maps, i, nb, fparams)
         filtered[i] = (d, n)
     torch.cuda.synchronize()
-    gpu_ms = host_ms = 0.0
+    gpu_ms = select_ms = 0.0
     filled = {}
     for i in sel:
         j = jobs[i]
@@ -356,7 +356,7 @@ def bench_phi(ctx, mv, jobs, outs, size=None):
         torch.cuda.synchronize()
         t3 = time.perf_counter()
         gpu_ms += (t1 - t0 + t3 - t2) * 1e3
-        host_ms += (t2 - t1) * 1e3
+        select_ms += (t2 - t1) * 1e3
         filled[i] = (dp, nf)
     # second filter pass over the filled maps (the others keep their filtered maps)
     maps2 = [(j["ref"],) + (filled[i] if i in filled else filtered[i]) for i, j in enumerate(jobs)]
@@ -383,7 +383,7 @@ def bench_phi(ctx, mv, jobs, outs, size=None):
     return {"references": len(sel), "pixels": int(sum(mv.images[jobs[i]["ref"]].size for i in sel)),
             "raw": stats(lambda i: outs[i]["depth"]), "filtered": stats(lambda i: filtered[i][0]),
             "phi_filled": stats(lambda i: filled[i][0]), "phi_filtered_again": stats(lambda i: final[i]),
-            "gpu_ms": gpu_ms, "host_selection_ms": host_ms,
+            "gpu_ms": gpu_ms, "selection_ms": select_ms,
             "fusion": bench_fusion(ctx, mv, [(jobs[i]["ref"], final[i]) for i in sel])}
 
 

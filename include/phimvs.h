@@ -260,8 +260,8 @@ void phimvs_default_filter_params(phimvs_filter_params* p);
  * max_angle_deg, and view j's point at d' must re-project within max_reproj_px of x.  A
  * neighbour is not consistent when the projection leaves its image, lies behind it or
  * touches a texel without depth.  Outputs (device, reference size): depth and normal
- * kept or zeroed, and the count of consistent neighbours per pixel (uint8).  All
- * arithmetic is FP64.  p = NULL uses the defaults. */
+ * kept or zeroed, and the count of consistent neighbours per pixel (uint8).  Every
+ * decision is that of FP64 arithmetic.  p = NULL uses the defaults. */
 int phimvs_filter(phimvs_ctx* ctx, int n_maps, const phimvs_depth_map* maps, int ref_map, const int32_t* nbrs,
                   int n_nbrs, const phimvs_filter_params* p, float* depth_out, float* normal_out,
                   uint8_t* count_out);
@@ -292,14 +292,15 @@ void phimvs_default_fuse_params(phimvs_fuse_params* p);
  *   owner   (int64 per pixel): the concatenated index of the point the pixel ended in,
  *           -1 for pixels without depth.
  * All arithmetic is FP64.  Work is queued on the context's stream; the library keeps
- * scratch of 12 bytes per concatenated pixel.  p = NULL uses the default threshold. */
+ * scratch of 12 bytes per concatenated pixel and 152 for each pair of maps, up to 65536 of
+ * them at a time (n_maps squared for up to 256 maps).  p = NULL uses the default threshold. */
 int phimvs_fuse(phimvs_ctx* ctx, int n_maps, const phimvs_depth_map* maps, const phimvs_fuse_params* p,
                 float* points, int32_t* support, int64_t* owner);
 
 /* ---- plane hypothesis inference (Sec. III-E) ----
  * Depth hypotheses for the pixels a filtered depth map leaves empty, their matching
  * costs, the selection of one hypothesis per pixel through a pairwise graph model (the
- * part the paper runs on the CPU, here too), and normals for the filled pixels. */
+ * part the paper runs on the CPU), and normals for the filled pixels. */
 
 /* Four hypotheses per pixel without depth (depth <= 0): for each direction (horizontal,
  * vertical, 45 degrees below (1, 1), 45 degrees above (1, -1)) the value at the pixel of

@@ -1307,8 +1307,8 @@ int phimvs_eval_cost(phimvs_ctx* c, const float* planes, float* cost, float* per
   if ((rc = upload_jobs(c, b))) return rc;
   Launch L = base_launch(b);
   L.mode = 2;
-  // both colours' queues cleared by one launch: a clear between the two launches left the chip
-  // idle for some microseconds (961 x 643: 476 -> 472 us a call)
+  // both colours' queues cleared by one launch in place of two (961 x 643, 485 us a call: the
+  // difference is within the noise)
   if ((rc = ensure(c, b.queues, 16))) return rc;
   HIPCHECK(c, launch_zero(b.queues.p, 16, c->stream));
   for (int colour = 0; colour < 2; ++colour) {

@@ -929,7 +929,7 @@ __global__ __launch_bounds__(128) void cand_prop_kernel(const Job* __restrict__ 
 // that is left empty itself equals what that one equals, so comparing with the candidates as
 // computed gives the same result.
 // A launch over 160 x 120 pixels takes 7.5 us in place of 20.5, where the one-thread form is a chain
-// of eight such steps; the map's time goes from 885 to 786 us (3 iterations, 16 lanes per pixel).
+// of eight such steps; the map's time (3 iterations, 16 lanes per pixel) goes from 885 to 786 us.
 constexpr int kPropPx = 64;
 __global__ __launch_bounds__(8 * kPropPx) void cand_prop_split_kernel(const Job* __restrict__ jobs, Launch L) {
   __shared__ float4 fresh[8][kPropPx], old[8][kPropPx];
@@ -1322,8 +1322,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
 // other), workgroups and lanes per pair planned for one round (lanes_plan), loads issued ahead, a
 // window corner per lane, butterflies over DPP, the reference sums loaded.  The order of every
 // sum is unchanged.  160 x 120, 4 sources, 11 x 11 taps, 16 lanes: propagation launches 130 -> 72
-// us, refinement 83 -> 36 us, a depth map of 3 iterations 1305 -> 864 us; 300 x 200, 8 sources: 5016 ->
-// 3532 us.
+// us, refinement 83 -> 36 us, a depth map of 3 iterations 1305 -> 864 us (780-790 with
+// cand_prop_split_kernel); 300 x 200, 8 sources: 5016 -> 3532 us.
 // Modes as in eval_tile.  Dynamic LDS: lanes_lds(px) floats (reference data, costs, list), the
 // spatial weights, the reference tile.
 constexpr int kLanesBlock = 2 * kBlock;
@@ -1663,7 +1663,7 @@ hipError_t launch_eval(const Job* d_jobs, const Launch& L, int grid, size_t lds,
 // spare is bound by the length of a pair's chain, and the part of it that does not split is
 // repeated in every lane where there are none.  160 x 120 (80 compacted columns), 16 ways: 4 / 8 /
 // 16 lanes per pair for the propagation / refinement / initialisation launches and 20 pixels per
-// workgroup, 864 us per depth map; 1124-1189 us with 16 to 64 pixels (workgroups of one size split
+// workgroup, 864 us per depth map then; 1124-1189 us with 16 to 64 pixels (workgroups of one size split
 // a row unevenly, or need a second round) whatever the lanes.
 LanesPlan lanes_plan(int lanes, int H, int Wc, int ncand, int n_cu) {
   LanesPlan p;
