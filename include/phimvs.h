@@ -353,10 +353,12 @@ void phimvs_default_phi_params(phimvs_phi_params* p);
  * 3200 x 2130 pixels: 795 MB), 4 KB for each of S columns ahead of them, and 10 floats per
  * node.  The context keeps scratch of up to 1 GiB of it for the next selection (and gives it
  * back when device memory runs out).  Small or narrow graphs, those whose energies are not
- * all finite, those in which labels of different depth tie to within 2e-13 in energy (which
- * rounding then decides) and those that device memory does not hold are gathered (9 floats
- * per node), copied to the host and decoded there.  Both take the same FP64 steps but for the logarithms, which
- * are each platform's own; the labels are the same.  Synchronises the stream.
+ * all finite and those that device memory does not hold are gathered (9 floats per node),
+ * copied to the host and decoded there.  Both take the same FP64 steps but for the
+ * logarithms, which are each platform's own; where labels of different depth tie to within
+ * 4e-14 in energy, so that rounding decides, the device decodes once more with the host's
+ * logarithms (16 bytes of scratch for each of them): the labels are the host decoder's.
+ * Synchronises the stream.
  * PHIMVS_E_ARG also for a cost above C_max + k1 k2 at a sampled hypothesis (no positive
  * potential). */
 int phimvs_phi_select(phimvs_ctx* ctx, int width, int height, const float* depth, const float* hyp,

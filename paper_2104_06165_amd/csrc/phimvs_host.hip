@@ -13,6 +13,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -1537,6 +1538,47 @@ void phimvs_default_phi_params(phimvs_phi_params* p) {
   p->iterations = 8;
 }
 
+// The labels of a graph whose decoding hangs on rounding: the sweeps once more, over energies whose
+// logarithms the host has taken.  False: no memory for them.
+static int decode_with_host_logs(phimvs_ctx* c, const float* depth, const float* hyp, const float* cost, int W, int H,
+                                 const TrwParams& p, float* dec, int** flag, bool* done) {
+  *done = false;
+  unsigned long long *n_dev = nullptr, n = 0;
+  HIPCHECK(c, launch_trw_potentials(depth, hyp, cost, W, H, p, c->trw.p, nullptr, &n_dev, c->stream));
+  HIPCHECK(c, hipMemcpyAsync(&n, n_dev, sizeof n, hipMemcpyDeviceToHost, c->stream));
+  HIPCHECK(c, hipStreamSynchronize(c->stream));
+  struct List {
+    DevBuf<int64_t> at;
+    DevBuf<double> x;
+    ~List() {
+      release(at);
+      release(x);
+    }
+  } list;
+  // (not give_back's to free the graph: it is in use)
+  if (hipMalloc((void**)&list.at.p, n * sizeof(int64_t)) != hipSuccess ||
+      hipMalloc((void**)&list.x.p, n * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
+    return PHIMVS_OK;
+  }
+  const TrwLogs logs{(int64_t)n, list.at.p, list.x.p};
+  const std::unique_ptr<double[]> x(new (std::nothrow) double[n]);
+  if (!x) return PHIMVS_OK;
+  HIPCHECK(c, launch_trw_potentials(depth, hyp, cost, W, H, p, c->trw.p, &logs, &n_dev, c->stream));
+  HIPCHECK(c, hipMemcpyAsync(x.get(), logs.x, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  HIPCHECK(c, hipStreamSynchronize(c->stream));
+  try {
+    host_energies(x.get(), n);
+  } catch (...) {
+    return PHIMVS_OK;
+  }
+  HIPCHECK(c, hipMemcpyAsync(logs.x, x.get(), n * sizeof(double), hipMemcpyHostToDevice, c->stream));
+  HIPCHECK(c, launch_trw(depth, hyp, cost, W, H, p, c->trw.p, &logs, dec, flag, c->stream));
+  HIPCHECK(c, hipStreamSynchronize(c->stream));  // the lists go out of scope
+  *done = true;
+  return PHIMVS_OK;
+}
+
 int phimvs_phi_select(phimvs_ctx* c, int width, int height, const float* depth, const float* hyp, const float* cost,
                       const phimvs_phi_params* pp, float* depth_out) {
   if (!c) return PHIMVS_E_ARG;
@@ -1560,18 +1602,27 @@ int phimvs_phi_select(phimvs_ctx* c, int width, int height, const float* depth, 
   if (trw_on_gpu(W2, H2) && p.k3 < 1e150 && fit(c, c->trw, trw_words(W2, H2)) == PHIMVS_OK) {
     float* dec = c->io_a.p;
     int *flag = nullptr, got = 0;
-    HIPCHECK(c, launch_trw(depth, hyp, cost, W, H, p.k1, p.k2, p.k3, PHIMVS_COST_MAX, p.iterations, c->trw.p, dec,
-                           &flag, c->stream));
+    const TrwParams tp{p.k1, p.k2, p.k3, PHIMVS_COST_MAX, p.iterations};
+    HIPCHECK(c, launch_trw(depth, hyp, cost, W, H, tp, c->trw.p, nullptr, dec, &flag, c->stream));
     // back to full size in the kernel: pixel (x, y) reads node (x / 2, y / 2)
     HIPCHECK(c, launch_phi_select(depth, hyp, dec, W, H, flag, depth_out, c->stream));
     HIPCHECK(c, hipMemcpyAsync(&got, flag, sizeof got, hipMemcpyDeviceToHost, c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
+    if (got == kTrwTie) {
+      bool done = false;
+      if ((rc = decode_with_host_logs(c, depth, hyp, cost, W, H, tp, dec, &flag, &done))) return rc;
+      if (done) {
+        HIPCHECK(c, launch_phi_select(depth, hyp, dec, W, H, nullptr, depth_out, c->stream));
+        HIPCHECK(c, hipStreamSynchronize(c->stream));
+        got = 0;
+      }
+    }
     if (c->trw.n * sizeof(uint64_t) > kKeepScratch) release(c->trw);
     if (got & kTrwInvalid) return fail(c, PHIMVS_E_ARG, invalid);
     if (!got) return PHIMVS_OK;
   }
-  // a small or narrow graph, infinite energies, labels that hang on rounding, or no device memory
-  // for a large graph: the GPU gathers the nodes' inputs (depth, 4 hypotheses, 4 costs) and the host decodes
+  // a small or narrow graph, infinite energies, or no device memory for a large graph: the GPU
+  // gathers the nodes' inputs (depth, 4 hypotheses, 4 costs) and the host decodes
   (void)hipGetLastError();  // of an allocation that failed
   float* half = c->io_a.p;
   float* dec_d = c->io_a.p + 9 * n2;

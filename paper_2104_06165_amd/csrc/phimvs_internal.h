@@ -234,11 +234,28 @@ struct TrwBuffers {
 bool trw_on_gpu(int W2, int H2);    // whether the GPU is the faster decoder of W2 x H2 nodes
 size_t trw_words(int W2, int H2);  // 64-bit words of scratch for W2 x H2 nodes
 // what the device flag reports: a potential that is not positive; a unary term that is infinite,
-// labels that tie to within rounding, both of which the host decodes
+// which the host decodes; labels that tie to within rounding
 constexpr int kTrwInvalid = 1, kTrwInfinite = 2, kTrwTie = 4;
-// decodes the half-size graph of full-size maps into dec (W2 H2)
-hipError_t launch_trw(const float* depth, const float* hyp, const float* cost, int W, int H, double k1, double k2,
-                      double k3, double cost_max, int iterations, uint64_t* words, float* dec, int** flag, hipStream_t st);
+struct TrwParams {
+  double k1, k2, k3, cost_max;
+  int iterations;
+};
+// the energies that are logarithms: where each lies, and its potential or the energy itself
+struct TrwLogs {
+  int64_t n;
+  int64_t* at;
+  double* x;
+};
+// decodes the half-size graph of full-size maps into dec (W2 H2), with the GPU's logarithms, then
+// looking for ties, or with the energies of `logs`
+hipError_t launch_trw(const float* depth, const float* hyp, const float* cost, int W, int H, const TrwParams& p,
+                      uint64_t* words, const TrwLogs* logs, float* dec, int** flag, hipStream_t st);
+// the number of energies that are logarithms (*n, on the device), and with `logs` their places and
+// potentials
+hipError_t launch_trw_potentials(const float* depth, const float* hyp, const float* cost, int W, int H, const TrwParams& p,
+                                 uint64_t* words, const TrwLogs* logs, unsigned long long** n, hipStream_t st);
+// x[i] = -log(x[i]) with the host's logarithm, on up to 16 threads
+void host_energies(double* x, size_t n);
 // dec: the decoded half-size depth ((W+1)/2 x (H+1)/2); skip: nullptr, or a device flag that, set,
 // leaves out as it is
 hipError_t launch_phi_select(const float* depth, const float* hyp, const float* dec, int W, int H, const int* skip,

@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "phimvs.h"
+#include "phimvs_internal.h"
 
 namespace {
 
@@ -161,6 +162,20 @@ void wavefront(Team& team, const Tiling& tl, int W, int H, bool forward, F&& vis
 }
 
 }  // namespace
+
+namespace phimvs_internal {
+
+void host_energies(double* x, size_t n) {
+  Team team(worker_count(n));
+  std::atomic<size_t> next{0};
+  constexpr size_t kPart = 4096;
+  team.run([&] {
+    for (size_t i; (i = next.fetch_add(kPart)) < n;)
+      for (const size_t end = std::min(n, i + kPart); i < end; ++i) x[i] = -std::log(x[i]);
+  });
+}
+
+}  // namespace phimvs_internal
 
 // Sequential TRW-S visits the nodes in raster order (forward sweep: each node sends to its
 // right and lower neighbours) and then in reverse raster order (backward sweep: to its upper

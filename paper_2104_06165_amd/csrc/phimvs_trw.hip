@@ -2,8 +2,9 @@
 // model of phimvs_mrf.hip (node states, potentials, sequential tree-reweighted message passing
 // in raster order, labelling in raster order), with the same FP64 operations in the same order
 // per node.  Only the logarithms are each platform's own (3% of them differ, by an ulp), which
-// can tell apart labels that tie to within rounding; where a node has such a tie the result is
-// not used and the host decodes (trw_ties_kernel), so the labels are the host decoder's.
+// can tell apart labels that tie to within rounding; where a node has such a tie the host takes
+// the logarithms (trw_ties_kernel, launch_trw_potentials) and the sweeps run again, so the labels are the
+// host decoder's.
 //
 // A node of a forward sweep needs its left and upper neighbours of the same sweep, so W + H - 1
 // steps follow one another: a sweep is a chain, and what bounds it is the time of a step.  One
@@ -47,15 +48,18 @@ __device__ __forceinline__ bool is_empty(double x) {
   return __builtin_bit_cast(unsigned long long, x) == __builtin_bit_cast(unsigned long long, kEmpty);
 }
 
-__device__ __forceinline__ double edge_energy(double h1, double h2, double k3) {
+__device__ __forceinline__ double edge_distance(double h1, double h2) {
   const double rel = h1 > h2 ? (h1 - h2) / h2 : (h2 - h1) / h1;
-  const double m = rel < 1.0 ? rel : 1.0;
-  return -log((k3 - m) * (k3 - m));
+  return rel < 1.0 ? rel : 1.0;
+}
+__device__ __forceinline__ double edge_potential(double h1, double h2, double k3) {
+  const double m = edge_distance(h1, h2);
+  return (k3 - m) * (k3 - m);
 }
 
 // labels within this of each other (for up to 8 iterations, and times the largest energy, taken to
-// be at least kTieScale) are left to the host (trw_ties_kernel)
-constexpr double kTieGap = 4e-14, kTieScale = 4.0;
+// be at least kTieScale) are settled with the host's logarithms (trw_ties_kernel)
+constexpr double kTieGap = 1e-14, kTieScale = 4.0;
 
 // info of a node: its states (3 bits), whether its upper and left neighbours have any
 constexpr int kLiveUp = 8, kLiveLeft = 16;
@@ -122,10 +126,10 @@ __global__ __launch_bounds__(256) void trw_setup_kernel(Nodes g, TrwBuffers B, d
     const int up = node_states(g, B.W, B.H, X, Y - 1, w), left = node_states(g, B.W, B.H, X - 1, Y, w);
     const int right = node_states(g, B.W, B.H, X + 1, Y, w);
     if (l < n)
-      for (int j = 0; j < right; ++j) er[j] = n * right > 1 ? edge_energy(mine, w[j], k3) : 0.0;
+      for (int j = 0; j < right; ++j) er[j] = n * right > 1 ? -log(edge_potential(mine, w[j], k3)) : 0.0;
     const int down = node_states(g, B.W, B.H, X, Y + 1, w);
     if (l < n)
-      for (int j = 0; j < down; ++j) ed[j] = n * down > 1 ? edge_energy(mine, w[j], k3) : 0.0;
+      for (int j = 0; j < down; ++j) ed[j] = n * down > 1 ? -log(edge_potential(mine, w[j], k3)) : 0.0;
     if ((up && left) || (right && down)) gamma = 0.5;
     info = n | (up ? kLiveUp : 0) | (left ? kLiveLeft : 0);
   }
@@ -358,16 +362,13 @@ __global__ __launch_bounds__(2 * kRows) void trw_sweep_kernel(TrwBuffers B, int 
 // logarithm; the messages then by 1e-15 of the largest energy after 8 iterations and by up to 1e-14
 // of it after 200 (measured on the CPU, one-ulp changes of every energy, k3 from 1 + 1e-7 to 1000).
 // So a node decides alike in both unless another state's energy lies within kTieGap times that
-// energy (at least 4, the common potentials' 2.3 among them) of the least, 40 times what was
+// energy (at least 4, the common potentials' 2.3 among them) of the least, 10 times what was
 // measured.  Left out: states of the same depth (the label does not show), and states that nothing
 // tells apart in either: the same cost, and what the neighbours contribute goes through equal
 // relative distances (saturated ones as a rule), so they tie exactly in both.  What remains in
-// filled 1600 x 1066 maps are hypotheses that agree to six digits: one map of 80 went to the host.
-// One quad of lanes per position, lane l: state l.  23 us at 1600 x 1066.
-__device__ __forceinline__ double edge_distance(double h1, double h2) {
-  const double rel = h1 > h2 ? (h1 - h2) / h2 : (h2 - h1) / h1;
-  return rel < 1.0 ? rel : 1.0;
-}
+// filled maps are hypotheses that agree to six digits, on either side of which the energy is flat:
+// one map of 24 (960 x 640 to 3200 x 2130), none of 80 of 1600 x 1066.  One quad of lanes per
+// position, lane l: state l.  23 us at 1600 x 1066.
 __device__ float state_cost(const Nodes& g, int X, int Y, int l) {
   const size_t p = (size_t)(2 * Y) * g.W + 2 * X, plane = (size_t)g.W * g.H;
   int i = 0;
@@ -438,6 +439,59 @@ __global__ __launch_bounds__(256) void trw_ties_kernel(Nodes g, TrwBuffers B, do
   if (differs) atomicOr(B.flag, kTrwTie);
 }
 
+// The arguments of all logarithms of the energies, in any order: where each energy lies (in doubles
+// from er) and its potential.  at null: counted only.
+__global__ __launch_bounds__(256) void trw_potentials_kernel(Nodes g, TrwBuffers B, double k1, double k2, double k3,
+                                                             double cost_max, unsigned long long* __restrict__ n_out,
+                                                             int64_t* __restrict__ at_out, double* __restrict__ out) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, at = t >> 2;
+  const int l = (int)threadIdx.x & 3;
+  const int r = (int)(at % kRows);
+  const int64_t bs = at / kRows;
+  const int X = (int)(bs % B.S) - r, Y = (int)(bs / B.S) * kRows + r;
+  double x[9];
+  int64_t to[9];
+  int count = 0;
+  float v[4] = {0.f, 0.f, 0.f, 0.f}, w[4];
+  const int n = at < B.positions ? node_states(g, B.W, B.H, X, Y, v) : 0;
+  if (l < n) {
+    const float mine = l == 0 ? v[0] : (l == 1 ? v[1] : (l == 2 ? v[2] : v[3]));
+    if (!(g.depth[(size_t)(2 * Y) * g.W + 2 * X] > 0.0f)) {
+      x[count] = (cost_max - (double)state_cost(g, X, Y, l)) / k1 + k2;
+      to[count++] = B.un + t - B.er;
+    }
+    for (int d = 0; d < 2; ++d) {
+      const int m = node_states(g, B.W, B.H, X + (d == 0), Y + (d == 1), w);
+      for (int j = 0; j < m && n * m > 1; ++j) {
+        x[count] = edge_potential(mine, w[j], k3);
+        to[count++] = (d == 0 ? B.er : B.ed) + 4 * t + j - B.er;
+      }
+    }
+  }
+  // places in the list: a wave's entries together
+  const int lane = threadIdx.x & 63;
+  int before = count;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int other = __shfl_up(before, o);
+    if (lane >= o) before += other;
+  }
+  const int all = __shfl(before, 63);
+  unsigned long long base = 0;
+  if (lane == 0 && all) base = atomicAdd(n_out, (unsigned long long)all);
+  base = __shfl(base, 0) + (before - count);
+  if (!at_out) return;
+  for (int i = 0; i < count; ++i) {
+    at_out[base + i] = to[i];
+    out[base + i] = x[i];
+  }
+}
+
+__global__ __launch_bounds__(256) void trw_energies_kernel(double* __restrict__ er, const int64_t* __restrict__ at,
+                                                           const double* __restrict__ energy, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) er[at[i]] = energy[i];
+}
+
 }  // namespace pmt
 
 namespace phimvs_internal {
@@ -473,8 +527,7 @@ size_t trw_words(int W2, int H2) {
   return (size_t)trw_positions(W2, H2) * kWordsPerPosition + trw_room_er() + trw_room_ed(W2) + nb * trw_steps(W2) * 4 + 2;
 }
 
-hipError_t launch_trw(const float* depth, const float* hyp, const float* cost, int W, int H, double k1, double k2,
-                      double k3, double cost_max, int iterations, uint64_t* words, float* dec, int** flag, hipStream_t st) {
+static TrwBuffers trw_buffers(int W, int H, uint64_t* words) {
   TrwBuffers B{};
   B.W = (W + 1) / 2;
   B.H = (H + 1) / 2;
@@ -500,29 +553,50 @@ hipError_t launch_trw(const float* depth, const float* hyp, const float* cost, i
   B.flag = reinterpret_cast<int*>(take(1));
   B.gamma = reinterpret_cast<double*>(take(n));
   B.info = reinterpret_cast<int*>(take(n));
+  return B;
+}
+
+hipError_t launch_trw(const float* depth, const float* hyp, const float* cost, int W, int H, const TrwParams& p,
+                      uint64_t* words, const TrwLogs* logs, float* dec, int** flag, hipStream_t st) {
+  const TrwBuffers B = trw_buffers(W, H, words);
   *flag = B.flag;
   // the flag lies after the ticket
   hipError_t e = launch_zero(reinterpret_cast<unsigned int*>(B.ticket), 4, st);
   if (e != hipSuccess) return e;
   const pmt::Nodes g{depth, hyp, cost, W, H};
-  hipLaunchKernelGGL(pmt::trw_setup_kernel, dim3((unsigned)((4 * B.positions + 255) / 256)), dim3(256), 0, st, g, B, k1, k2,
-                     k3, cost_max);
+  const dim3 places((unsigned)((4 * B.positions + 255) / 256));
+  hipLaunchKernelGGL(pmt::trw_setup_kernel, places, dim3(256), 0, st, g, B, p.k1, p.k2, p.k3, p.cost_max);
+  if (logs)
+    hipLaunchKernelGGL(pmt::trw_energies_kernel, dim3((unsigned)((logs->n + 255) / 256)), dim3(256), 0, st, B.er, logs->at,
+                       logs->x, logs->n);
   const dim3 grid(B.NB), block(2 * pmt::kRows);
   // a launch that failed ends it: the ones after it would take their band numbers from its share
   // of the ticket
   if ((e = hipGetLastError()) != hipSuccess) return e;
   int sweep = 0;
-  for (int it = 0; it < iterations; ++it) {
+  for (int it = 0; it < p.iterations; ++it) {
     hipLaunchKernelGGL(pmt::trw_sweep_kernel<0>, grid, block, 0, st, B, sweep++, dec);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(pmt::trw_sweep_kernel<1>, grid, block, 0, st, B, sweep++, dec);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(pmt::trw_sweep_kernel<2>, grid, block, 0, st, B, sweep, dec);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const double edge = 2.0 * std::max(std::fabs(std::log(k3 - 1.0)), std::log(k3));  // the largest of an edge
-  hipLaunchKernelGGL(pmt::trw_ties_kernel, dim3((unsigned)((4 * B.positions + 255) / 256)), dim3(256), 0, st, g, B,
-                     pmt::kTieGap * std::max(1.0, iterations / 8.0), std::max(pmt::kTieScale, edge), iterations > 0, dec);
+  if ((e = hipGetLastError()) != hipSuccess || logs) return e;
+  const double edge = 2.0 * std::max(std::fabs(std::log(p.k3 - 1.0)), std::log(p.k3));  // the largest of an edge
+  hipLaunchKernelGGL(pmt::trw_ties_kernel, places, dim3(256), 0, st, g, B,
+                     pmt::kTieGap * std::max(1.0, p.iterations / 8.0), std::max(pmt::kTieScale, edge), p.iterations > 0, dec);
+  return hipGetLastError();
+}
+
+hipError_t launch_trw_potentials(const float* depth, const float* hyp, const float* cost, int W, int H, const TrwParams& p,
+                                 uint64_t* words, const TrwLogs* logs, unsigned long long** n, hipStream_t st) {
+  const TrwBuffers B = trw_buffers(W, H, words);
+  *n = B.ticket;
+  const hipError_t e = launch_zero(reinterpret_cast<unsigned int*>(B.ticket), 2, st);
+  if (e != hipSuccess) return e;
+  const pmt::Nodes g{depth, hyp, cost, W, H};
+  hipLaunchKernelGGL(pmt::trw_potentials_kernel, dim3((unsigned)((4 * B.positions + 255) / 256)), dim3(256), 0, st, g, B, p.k1,
+                     p.k2, p.k3, p.cost_max, B.ticket, logs ? logs->at : nullptr, logs ? logs->x : nullptr);
   return hipGetLastError();
 }
 

@@ -114,3 +114,20 @@ def test_labels_that_tie_to_within_rounding(ctx):
         best = np.take_along_axis(h, dist.argmin(0)[None], 0)[0]
         want = np.where(d > 0, d, np.where((ref > 0) & np.isfinite(dist.min(0)), best, 0.0)).astype(np.float32)
         assert np.array_equal(select(ctx, d, h, c, **p), want), seed
+
+
+@pytest.mark.parametrize("W,H,it", [(226, 194, 8), (401, 131, 3), (160, 300, 1), (130, 130, 0)])
+def test_a_tie_among_other_nodes(ctx, W, H, it):
+    """One pair of states that ties to within rounding, in a corner of a graph with up to four states a
+    node: the whole graph is decoded with the host's logarithms."""
+    for seed in range(3):
+        d, h, c = maps(W, H, "any", 10 * W + seed)
+        s = np.float32(np.random.default_rng(seed).uniform(0.5, 3))
+        d[-14:, -14:], h[:, -14:, -14:] = 0, 0
+        y, x = (H - 7) // 2 * 2, (W - 7) // 2 * 2  # a node and its left neighbour, alone
+        d[y, x - 2] = 4 * s
+        h[:2, y, x] = 6 * s, 5 * s
+        c[:2, y, x] = 2 - 49 / 64, 2 - 36 / 64
+        p = dict(k1=float(np.random.default_rng(seed).uniform(0.3, 3)), k2=1e-300, iterations=it)
+        o = oracle.phi_select(d, h.transpose(1, 2, 0), c.transpose(1, 2, 0), **p)
+        assert np.array_equal(select(ctx, d, h, c, **p), o)
