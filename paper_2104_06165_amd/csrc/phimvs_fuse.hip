@@ -19,10 +19,10 @@
 // together with a bound of the difference between the two; a lane whose test lies within that
 // bound of the other outcome (a rounding boundary of the pixel position, the distance limit)
 // takes the expressions as written, so the decisions are theirs.  Nine 961 x 640 maps (5.5 M pixels):
-// 422 us with both launches in every step (init 47, claims refilled 64, claim 142, merge 154 us)
-// and the written form throughout, 302 us so (init 12, claim 181, merge 84 us: the merge issues
-// FP64 on 75% of its cycles; the first claim launch, 50 us, has 18 us of atomics, which memory
-// carries out).
+// 404-422 us a call with both launches in every step (init 47, claims refilled 64, claim 142, merge
+// 154 us) and the written form throughout, 273-298 us so, depending on the machine (init 12, claim
+// 180, merge 84 us: the merge issues FP64 on 75% of its cycles; the first claim launch, 50 us, has
+// 18 us of atomics, which memory carries out).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
