@@ -337,10 +337,15 @@ struct Problem {
 };
 
 std::string problem_key(const Problem& P) {
+  // the doubles by their bits: decimals would take parameters for each other
+  auto bits = [](double v) {
+    uint64_t b;
+    std::memcpy(&b, &v, sizeof b);
+    return std::to_string(b) + ",";
+  };
   std::string k = std::to_string(P.ref) + "," + std::to_string(P.window) + "," + std::to_string(P.dilation) + "," +
                   std::to_string(P.p.top_k) + "," + std::to_string(P.p.bilateral) + "," + std::to_string(P.p.seed) +
-                  "," + std::to_string(P.p.sigma_color) + "," + std::to_string(P.p.sigma_spatial_px) + "," +
-                  std::to_string(P.p.eps_var) + "," + std::to_string(P.p.eps_cost) + "," +
+                  "," + bits(P.p.sigma_color) + bits(P.p.sigma_spatial_px) + bits(P.p.eps_var) + bits(P.p.eps_cost) +
                   std::to_string(P.p.tap_radius) + "," + std::to_string(P.p.lanes) + "," +
                   std::to_string(P.p.score_all);
   for (int s : P.srcs) k += ";" + std::to_string(s);

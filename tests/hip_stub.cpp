@@ -15,7 +15,7 @@ size_t live = 0, limit = (size_t)1 << 40;
 hipError_t last = hipSuccess;
 int device_of_pointers = 0;
 long device_syncs = 0;
-size_t table_bytes = 0;
+std::vector<char> table;  // what the last plain copy carried
 std::vector<const void*> launched;       // functions
 std::vector<unsigned long long> firsts;  // first 8 bytes of their arguments
 dim3 grid, block;
@@ -41,7 +41,8 @@ void stub_limit(size_t bytes) { limit = bytes; }
 size_t stub_live() { return live; }
 void stub_pointers_on(int device) { device_of_pointers = device; }
 long stub_device_syncs() { return device_syncs; }
-size_t stub_table_bytes() { return table_bytes; }
+size_t stub_table_bytes() { return table.size(); }
+const void* stub_table() { return table.data(); }
 void stub_forget_launches() { launched.clear(), firsts.clear(); }
 size_t stub_launches() { return launched.size(); }
 const void* stub_launched(size_t i) { return launched[i]; }
@@ -68,7 +69,7 @@ hipError_t hipFree(void* p) {
   return hipSuccess;
 }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
-  table_bytes = n;
+  table.assign((const char*)s, (const char*)s + n);
   std::memcpy(d, s, n);
   return hipSuccess;
 }

@@ -129,6 +129,26 @@ def a_first_scene_waits_for_no_other_work(c):
     assert c.stub.stub_device_syncs() == 1
 
 
+# ---------------------------------------------------------------------------- problems
+@case
+def parameters_that_nearly_agree_are_not_the_same_problem(c):
+    """Parameters differing beyond the sixth decimal: the job table has to carry the new ones."""
+    assert c.set_views((64, 48), (64, 48)) == 0, c.err()
+
+    def table():
+        return C.string_at(c.stub.stub_table(), c.stub.stub_table_bytes())
+
+    s = (C.c_int * 1)(1)
+    for field in ("eps_var", "eps_cost"):
+        for v in (1e-7, 2e-7):
+            p = pm.Params(**{field: v})._c()
+            assert c.L.phimvs_patchmatch(c.h, 0, s, 1, 7, 1, 1, C.byref(p), None, None, None, 1) == 0, c.err()
+            assert np.float32(v).tobytes() in table()
+            job = pm._Job(0, (C.c_int32 * 1)(1), 1, 7, 1, p, None, None, None)
+            assert c.L.phimvs_patchmatch_batch(c.h, 1, C.byref(job), 1, 0) == 0, c.err()
+            assert np.float32(v).tobytes() in table()
+
+
 # ---------------------------------------------------------------------------- memory
 def select(c, W, H):
     a = np.zeros(1, np.float32).ctypes.data  # nothing reads it
@@ -262,7 +282,7 @@ def test_call(stub, name):
 if __name__ == "__main__":
     lib = C.CDLL(sys.argv[2], mode=C.RTLD_GLOBAL)
     for f, a, res in (("stub_limit", [C.c_size_t], None), ("stub_live", [], C.c_size_t), ("stub_pointers_on", [C.c_int], None),
-                      ("stub_device_syncs", [], C.c_long), ("stub_table_bytes", [], C.c_size_t),
+                      ("stub_device_syncs", [], C.c_long), ("stub_table_bytes", [], C.c_size_t), ("stub_table", [], C.c_void_p),
                       ("stub_forget_launches", [], None), ("stub_launches", [], C.c_size_t),
                       ("stub_launched", [C.c_size_t], C.c_void_p), ("stub_first", [C.c_size_t], C.c_uint64),
                       ("hipMalloc", [C.POINTER(C.c_void_p), C.c_size_t], C.c_int)):
