@@ -121,3 +121,10 @@ def test_rotations_that_are_not_exact(how, far):
             break
     # distances spread about the limit
     run(K, R, t, [noisy(rng, 240, 320, spread=0.006, empty=0.0) for _ in range(3)], 0.01)
+
+
+def test_more_maps_than_the_pair_table_holds():
+    # 300 maps: the table takes 218 rows at a time, so there are two merges
+    rng = np.random.default_rng(300)
+    K, R, t = cams(300, 50.0, (15.0, 8.0), t=0.004 * rng.standard_normal((300, 3)))
+    run(K, R, t, [noisy(rng, 17, 31, empty=0.3) for _ in range(300)], 0.01)
